@@ -577,10 +577,10 @@ __global__ __launch_bounds__(512) void prefill_attn_kernel(PrefillAttnArgs a) {
     for (int i = 0; i < 4; ++i) {
       const int row = q0 + mt * 16 + grp * 4 + i;
       if (row >= P) continue;
-      uint16_t *dst = (uint16_t *)a.out + (row_base + row) * a.ld_out + h * HD;
       const float inv = 1.f / lrun[mt][i];
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) dst[dt * 16 + r16] = pf_f2bf(o[mt][dt][i] * inv);
+      for (int dt = 0; dt < DT; ++dt)
+        ((uint16_t *)a.out)[prefill_out_off(a, row_base + row, h * HD + dt * 16 + r16)] = pf_f2bf(o[mt][dt][i] * inv);
     }
 }
 
@@ -809,10 +809,9 @@ __global__ __launch_bounds__(64 * G) __attribute__((amdgpu_waves_per_eu(2))) voi
     const int query = q0 + mt * 16 + r16;
     if (query >= P) continue;
     const float inv = 1.f / lrun[mt];
-    uint16_t *dst = (uint16_t *)a.out + (row_base + query) * a.ld_out + h * HD + grp * 4;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
-      *(uint2 *)(dst + dt * 16) = make_uint2(pf_pack_bf16(o[mt][dt][0] * inv, o[mt][dt][1] * inv),
+      *(uint2 *)((uint16_t *)a.out + prefill_out_off(a, row_base + query, h * HD + dt * 16 + grp * 4)) = make_uint2(pf_pack_bf16(o[mt][dt][0] * inv, o[mt][dt][1] * inv),
                                              pf_pack_bf16(o[mt][dt][2] * inv, o[mt][dt][3] * inv));
   }
 }

@@ -19,6 +19,14 @@ __device__ __forceinline__ int qkv_col(int tile, int r16, int hd) {
 
 typedef uint16_t bf16;
 
+// Element offset of (row m, column k) in the packed block layout of `steps`
+// k-steps per 16-row block (bf16): block (m / 16, k / 32) is 1 KB, one
+// matrix-core fragment in lane order -- 16 bytes of row m % 16, k group
+// (k % 32) / 8 at lane 16 (k % 32) / 8 + m % 16.
+__device__ __forceinline__ size_t pk_off(int m, int k, int steps) {
+  return ((size_t)(m >> 4) * steps + (k >> 5)) * 512 + ((k & 31) >> 3) * 128 + (m & 15) * 8 + (k & 7);
+}
+
 // Step of an LDS ring filled by direct global -> LDS transfers
 // (global_load_lds): wait until at most VMCNT of this wave's vector-memory
 // operations are outstanding (the oldest transfers have landed in LDS), then
@@ -108,6 +116,9 @@ struct GemmArgs {
   // SWIGLU
   void *act;                  // [M][ld_act] (T)
   int ld_act;
+  // Prompt GEMMs (launch_gemm_tiled): x, xb and act are in the packed block
+  // layout (pk_off): x with nsteps_w k-steps, the output with pk_steps
+  int pk_steps;
   // LOGITS
   const int *mask_tok;        // [M][mask_stride]
   const int *mask_n;          // [M]
@@ -229,10 +240,16 @@ struct PrefillAttnArgs {
   const void *kc, *vc;        // this layer's cache base
   int kv_entries, n_kv_heads, n_heads, head_dim, batch, prompt_len;
   float scale;
-  void *out;                  // [batch * prompt_len][ld_out] (bf16)
+  void *out;                  // [batch * prompt_len][ld_out] (bf16), or
   int ld_out;
+  int out_steps;              // > 0: in the packed block layout with that many k-steps
 };
 hipError_t launch_prefill_attention(const PrefillAttnArgs &a, hipStream_t s);
+
+// Element offset of (row, column) of a prompt attention's output.
+__device__ __forceinline__ size_t prefill_out_off(const PrefillAttnArgs &a, size_t row, int col) {
+  return a.out_steps > 0 ? pk_off((int)row, col, a.out_steps) : row * a.ld_out + col;
+}
 
 // Weight packing.  mode 0: rows in order; 1: QKV, the three segments w0/w1/w2
 // concatenated with each tile holding RoPE partner dimensions (i, i + hd/2)
@@ -249,11 +266,12 @@ hipError_t launch_pack(int dtype, const PackArgs &a, hipStream_t s);
 
 // Launchers (return the HIP status of the launch).
 hipError_t launch_gemm(int dtype, int epi, const GemmArgs &a, int m_blocks, hipStream_t s);
-// Prompt-prefill GEMM (bf16, M-tiled: 128 weight rows x 128 input rows per
-// workgroup) with the QKV / RESID / SWIGLU / PLAIN epilogues.  Requires N a
-// multiple of 16, K a multiple of 8, 16-byte aligned rows and no boundary
-// rows (gemm_tiled_supported); launch_gemm_tiled returns hipErrorInvalidValue
-// otherwise.  A normed GEMM takes its row scales from row_rsc.
+// Prompt-prefill GEMM (bf16, M-tiled) with the QKV / RESID / SWIGLU / PLAIN
+// epilogues.  x is in the packed block layout (zeros in the columns past K up
+// to the k-step), and so are the xb and act it writes; N a multiple of 16
+// except for SWIGLU, no boundary rows (gemm_tiled_supported);
+// launch_gemm_tiled returns hipErrorInvalidValue otherwise.  A normed GEMM
+// takes its row scales from row_rsc.
 bool gemm_tiled_supported(int epi, const GemmArgs &a);
 hipError_t launch_gemm_tiled(int epi, const GemmArgs &a, hipStream_t s);
 // out[m] = 1 / sqrt(sum(part[m][0..n_part)) * inv_d + eps), m < M: the RMSNorm
@@ -284,6 +302,7 @@ struct PrepArgs {
   const float *seg_g[MAX_SEGS];
   float *h, *part;            // [M][d], [M][n_part]
   void *xb;                   // [M][d] (T)
+  int xb_steps;               // > 0: xb in the packed block layout (bf16) with that many k-steps
   const int *row_out;         // nullable: write h/part to row_out[m] instead of m
 };
 hipError_t launch_prep(int dtype, const PrepArgs &a, hipStream_t s);

@@ -1010,6 +1010,12 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   const int G = H / ctx->Hkv;
   // matrix-core prompt attention for bf16 caches; the split kernel otherwise
   const bool mfma_prefill = ctx->dtype == DEX_BF16 && (hd == 64 || hd == 128) && G <= 8;
+  // many prompt rows: the M-tiled GEMMs (bf16) on packed activations; the
+  // decode GEMMs on row-major ones otherwise
+  const bool tiled = ctx->dtype == DEX_BF16 && M > 64;
+  const bool pack_att = tiled && !mfma_prefill;   // the split kernels write row-major
+  const size_t Mp = tiled ? (M + 15) / 16 * 16 : M;
+  const size_t xb_cols = tiled ? (size_t)ctx->ns_d * 32 : d, act_cols = tiled ? (size_t)ctx->ns_F * 32 : ctx->F;
   const int grp_rows = std::max(1, ATT_MAX_PAIRS / G);
   const int jmax = (P + ATT_SPLIT - 1) / ATT_SPLIT;
   // attention row chunk bounded so its split partials stay below ~512 MiB
@@ -1020,7 +1026,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   if (chunk == 0) chunk = grp_rows;
 
   float *h = nullptr, *part = nullptr, *q = nullptr, *apart = nullptr, *rsc = nullptr;
-  void *xb = nullptr, *att = nullptr, *act = nullptr;
+  void *xb = nullptr, *att = nullptr, *att_rows = nullptr, *act = nullptr;
   int *tab = nullptr;
   dex_status st = DEX_OK;
   auto A = [&](void **p, size_t bytes) {
@@ -1028,10 +1034,11 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   };
   A((void **)&h, M * d * 4);
   A((void **)&part, M * ctx->n_part * 4);
-  A(&xb, M * d * es);
+  A(&xb, Mp * xb_cols * es);
   A((void **)&q, M * H * hd * 4);
-  A(&att, M * H * hd * es);
-  A(&act, M * ctx->F * es);
+  A(&att, Mp * H * hd * es);
+  if (pack_att) A(&att_rows, M * H * hd * es);
+  A(&act, Mp * act_cols * es);
   A((void **)&rsc, M * 4);
   if (!mfma_prefill) A((void **)&apart, chunk * per_row);
   const size_t n_groups_total = (size_t)B * ((P + grp_rows - 1) / grp_rows);
@@ -1039,7 +1046,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   A((void **)&tab, tab_ints * 4);
   auto cleanup = [&]() {
     dfree(ctx, h); dfree(ctx, part); dfree(ctx, xb); dfree(ctx, q); dfree(ctx, att); dfree(ctx, act);
-    dfree(ctx, apart); dfree(ctx, tab); dfree(ctx, rsc);
+    dfree(ctx, apart); dfree(ctx, tab); dfree(ctx, rsc); dfree(ctx, att_rows);
   };
   if (st != DEX_OK) { cleanup(); return st; }   // nothing changed yet: not poisoned
 
@@ -1089,28 +1096,27 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   const int *d_exsrc = d_grel + n_groups_total, *d_exzero = d_exsrc + B;
   const int *d_exseq = d_exzero + 2 * B, *d_expos = d_exseq + B;
 
+  // a packed k-step that the columns do not fill ends in zeros
+  if (xb_cols > (size_t)d) HIPCHK(hipMemsetAsync(xb, 0, Mp * xb_cols * es, ctx->stream));
+  if (act_cols > (size_t)ctx->F) HIPCHK(hipMemsetAsync(act, 0, Mp * act_cols * es, ctx->stream));
   {
     PrepArgs p{};
     p.M = (int)M; p.d = d; p.n_part = ctx->n_part; p.embed_rows = (int)M; p.row_tok = d_tok; p.embed = ctx->embed;
     p.g = (const float *)LW(ctx, 0, DEX_P_ATTN_NORM); p.h = h; p.part = part; p.xb = xb;
+    p.xb_steps = tiled ? ctx->ns_d : 0;
     HIPCHK(launch_prep(ctx->dtype, p, ctx->stream));
   }
   const size_t layer_kv = (size_t)B * ctx->Hkv * ctx->E * hd * es;
-  // many prompt rows: the M-tiled kernel (bf16; a normed GEMM first gets
-  // its row scales); the decode kernel otherwise
-  auto prefill_gemm = [&](int epi, const GemmArgs &a) -> hipError_t {
-    if (ctx->dtype == DEX_BF16 && a.M > 64) {
-      GemmArgs t = a;
-      t.row_rsc = a.part != nullptr ? rsc : nullptr;
-      if (gemm_tiled_supported(epi, t)) {
-        if (t.row_rsc != nullptr) {
-          const hipError_t e = launch_row_scale(a.part, a.n_part, a.M, a.inv_d, a.eps, rsc, ctx->stream);
-          if (e != hipSuccess) return e;
-        }
-        return launch_gemm_tiled(epi, t, ctx->stream);
-      }
+  // a normed tiled GEMM first gets its row scales
+  auto prefill_gemm = [&](int epi, GemmArgs a) -> hipError_t {
+    if (!tiled) return launch_gemm(ctx->dtype, epi, a, 1, ctx->stream);
+    if (a.part != nullptr) {
+      a.row_rsc = rsc;
+      const hipError_t e = launch_row_scale(a.part, a.n_part, a.M, a.inv_d, a.eps, rsc, ctx->stream);
+      if (e != hipSuccess) return e;
     }
-    return launch_gemm(ctx->dtype, epi, a, 1, ctx->stream);
+    a.pk_steps = epi == EPI_SWIGLU ? ctx->ns_F : ctx->ns_d;
+    return launch_gemm_tiled(epi, a, ctx->stream);
   };
   for (int l = 0; l < ctx->L; ++l) {
     const float alpha = ctx->rscale * (float)(l + 1) / (float)ctx->L;
@@ -1131,6 +1137,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
       a.kc = (char *)ctx->kc + l * layer_kv; a.vc = (char *)ctx->vc + l * layer_kv;
       a.kv_entries = ctx->E; a.n_kv_heads = ctx->Hkv; a.n_heads = H; a.head_dim = hd; a.batch = B;
       a.prompt_len = P; a.scale = 1.0f / std::sqrt((float)hd); a.out = att; a.ld_out = H * hd;
+      a.out_steps = tiled ? ctx->ns_hhd : 0;
       HIPCHK(launch_prefill_attention(a, ctx->stream));
     } else for (const auto &ch : chunks) {
       const int g_first = ch[0], g_cnt = ch[1], c0 = ch[2], cn = ch[3];
@@ -1147,8 +1154,13 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
       CombineArgs cb{};
       cb.part = apart; cb.stat = split_stats(apart, cn, H, jmax, hd);
       cb.row_pos = d_pos + c0; cb.jmax = jmax; cb.n_heads = H; cb.head_dim = hd;
-      cb.out = (char *)att + (size_t)c0 * H * hd * es; cb.ld_out = H * hd;
+      cb.out = (char *)(pack_att ? att_rows : att) + (size_t)c0 * H * hd * es; cb.ld_out = H * hd;
       HIPCHK(launch_combine(ctx->dtype, cb, cn, ctx->stream));
+    }
+    if (pack_att) {                          // rows as the "weight rows" of a plain pack
+      PackArgs pa{};
+      pa.w0 = att_rows; pa.n0 = pa.N = (int)M; pa.K = H * hd; pa.mode = 0; pa.head_dim = hd; pa.out = att;
+      HIPCHK(launch_pack(ctx->dtype, pa, ctx->stream));
     }
     {
       GemmArgs a{};
@@ -1970,14 +1982,20 @@ dex_status dex_debug_gemm(int32_t dtype, const void *W, int32_t N, int32_t K, co
   if (dtype != DEX_F32 && dtype != DEX_BF16) return DEX_E_INVAL;
   if (M > 64 && (dtype != DEX_BF16 || N % 16)) return DEX_E_INVAL;
   if (K % (dtype == DEX_BF16 ? 8 : 4)) return DEX_E_INVAL;
+  // the M-tiled kernel takes x in the packed layout too
+  const size_t wbytes_packed = packed_bytes(dtype, N, K, 0), xbytes = M > 64 ? packed_bytes(dtype, M, K, 0) : 0;
   void *wp = nullptr;
-  if (hipMalloc(&wp, packed_bytes(dtype, N, K, 0)) != hipSuccess) return DEX_E_NOMEM;
+  if (hipMalloc(&wp, wbytes_packed + xbytes) != hipSuccess) return DEX_E_NOMEM;
   PackArgs pa{};
   pa.w0 = W; pa.n0 = N; pa.N = N; pa.K = K; pa.mode = 0; pa.head_dim = 16; pa.out = wp;
   hipError_t e = launch_pack(dtype, pa, (hipStream_t)stream);
+  if (e == hipSuccess && M > 64) {
+    pa.w0 = x; pa.n0 = pa.N = M; pa.out = (char *)wp + wbytes_packed;
+    e = launch_pack(dtype, pa, (hipStream_t)stream);
+  }
   GemmArgs a{};
   a.wp = wp; a.nsteps_w = (K + (dtype == DEX_BF16 ? 32 : 16) - 1) / (dtype == DEX_BF16 ? 32 : 16);
-  a.N = N; a.K = K; a.x = x; a.ldx = K; a.M = M; a.out = y; a.ld_out = N;
+  a.N = N; a.K = K; a.x = M > 64 ? (const char *)wp + wbytes_packed : x; a.ldx = K; a.M = M; a.out = y; a.ld_out = N;
   if (e == hipSuccess)
     e = M > 64 ? launch_gemm_tiled(EPI_PLAIN, a, (hipStream_t)stream) : launch_gemm(dtype, EPI_PLAIN, a, 1, (hipStream_t)stream);
   if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);

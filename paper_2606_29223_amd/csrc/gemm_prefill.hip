@@ -2,26 +2,35 @@
 //
 //   acc[m][n] = sum_k x[m][k] * W[n][k]
 //
-// With M = batch x prompt length in the tens of thousands the skinny decode
-// kernel would re-read the activations once per 16-column weight tile; here a
-// workgroup of four waves owns 128 weight rows x 128 input rows and each wave
-// a 64 x 64 block of 4 x 4 v_mfma_f32_16x16x32_bf16 tiles (the gate/up pair:
-// 2 tile pairs x 4).  Both operands come straight from memory in fragment
-// order: the packed weight layout stores one MFMA A fragment of a 16-row tile
-// per 1 KB block, and an input fragment is 16 rows x 64 contiguous bytes.
-// Neighbouring waves share operands through L1/L2.  The next k-step is loaded
-// while the current one is multiplied.  When its grid reaches 96 workgroups,
-// a second form (gemm_big_kernel) stages the operands through LDS in
-// 256 x 256 workgroup tiles; it computes every output element from the same
-// MFMA operands in the same order, so the two forms give the same bits.
+// Both operands are read in the packed block layout (1 KB per 16 rows x 32 k,
+// one MFMA fragment in lane order): the weights as dex_create packs them, the
+// activations as the producing kernel wrote them (pk_off).  So every transfer
+// is 1 KB of consecutive bytes and a k-step of a 16-row block follows the one
+// before it; row-major activations were fetched as sixteen 64-byte halves of
+// cache lines per fragment.
+//
+// gemm_ring_kernel: a workgroup owns BNB weight blocks (16 output columns
+// each; a gate/up pair takes two) x BMF input fragments (16 rows each).  The
+// stages (KS k-steps of both operands) move global -> LDS with direct
+// transfers (global_load_lds, 16 bytes per lane at LDS base + 16 x lane) into
+// a ring of NBUF slots, so a workgroup keeps up to (NBUF - 1) stages in
+// flight without a staging register, and each wave waits (vmcnt) only for its
+// own oldest stage before the per-stage barrier.  A stage's fragments are
+// read into registers while the stage before it is multiplied (two register
+// sets): with reads and products of one stage back to back, as the first form
+// of this kernel had it, the matrix cores idle while all waves read.
+//
+// Every output element accumulates its k-steps in increasing order from zero
+// whatever the tile, so the bits do not depend on which tile was chosen, on
+// the number of rows or on the other rows.
 //
 // The epilogues are those of the decode kernel (RMSNorm row scale, RoPE and
 // the key/value cache write; residual add with the next norm's input and its
 // sum-of-squares partials; SwiGLU), applied to the accumulators in registers:
-// lane (g, r) of a tile holds output rows 4g..4g+3 of input row r, so every
-// store covers four consecutive columns.  The row scales of a normed GEMM
-// are computed once beforehand (row_scale_kernel) rather than by each of
-// its column blocks.
+// lane (g, r) of a tile holds output columns 4g..4g+3 of input row r, so a
+// store to the packed layout puts a tile's 16 rows x 16 columns into 512
+// consecutive bytes.  The row scales of a normed GEMM are computed once
+// beforehand (row_scale_kernel) rather than by each of its column blocks.
 #include "dex_kernels.h"
 
 namespace dex {
@@ -30,10 +39,6 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 tb_bf16x8;
 typedef __attribute__((ext_vector_type(4))) float tb_f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int tb_u32x4;
-
-constexpr int TB_THREADS = 256;   // 2 x 2 waves
-constexpr int TB_MF = 4;          // 16-row input fragments per wave (64 rows)
-constexpr int TB_ROWS = 128;      // input rows per workgroup
 
 __device__ __forceinline__ uint32_t tb_f2bf(float f) {
   uint32_t u = __float_as_uint(f);
@@ -44,31 +49,33 @@ __device__ __forceinline__ uint2 tb_pack4(float a, float b, float c, float d) {
   return make_uint2(tb_f2bf(a) | (tb_f2bf(b) << 16), tb_f2bf(c) | (tb_f2bf(d) << 16));
 }
 
-// Sum of a row's n sum-of-squares partials in index order.  The loads go out
-// 32 at a time, so that a batch waits for one memory latency rather than
-// one per partial; the padding terms are +0, which leaves the sum (>= +0)
-// unchanged.
-__device__ __forceinline__ float tb_part_sum(const float *p, int n) {
-  float ss = 0.f;
-  for (int q0 = 0; q0 < n; q0 += 32) {
-    float v[32];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) v[i] = q0 + i < n ? p[q0 + i] : 0.f;
-#pragma unroll
-    for (int i = 0; i < 32; ++i) ss += v[i];
-  }
-  return ss;
-}
-
-// RMSNorm reciprocal scale of every prompt row, once per normed GEMM (each
-// of a GEMM's column blocks would otherwise reduce the row's partials
-// again): one thread per row.
+// RMSNorm reciprocal scale of every prompt row, once per normed GEMM: the
+// row's partials summed in index order by one thread.  A workgroup stages 16
+// rows' partials through LDS in coalesced chunks, so that the loads do not
+// follow the serial sum: one thread reading its own row took 31 us at 512
+// rows of 256 partials.
+constexpr int RS_ROWS = 16, RS_CHUNK = 256;
 __global__ __launch_bounds__(256) void row_scale_kernel(const float *part, int n_part, int M, float inv_d, float eps,
                                                         float *out) {
-  const int m = blockIdx.x * 256 + threadIdx.x;
-  if (m >= M) return;
-  const float ss = tb_part_sum(part + (size_t)m * n_part, n_part);
-  out[m] = 1.0f / sqrtf(ss * inv_d + eps);
+  __shared__ float buf[RS_ROWS][RS_CHUNK + 1];
+  const int m0 = blockIdx.x * RS_ROWS, tid = threadIdx.x;
+  float ss = 0.f;
+  for (int c0 = 0; c0 < n_part; c0 += RS_CHUNK) {
+    const int n = min(RS_CHUNK, n_part - c0);
+    float v[RS_ROWS];
+#pragma unroll
+    for (int r = 0; r < RS_ROWS; ++r)
+      v[r] = (tid < n && m0 + r < M) ? part[(size_t)(m0 + r) * n_part + c0 + tid] : 0.f;
+#pragma unroll
+    for (int r = 0; r < RS_ROWS; ++r) buf[r][tid] = v[r];
+    __syncthreads();
+    if (tid < RS_ROWS) {
+#pragma unroll 16
+      for (int i = 0; i < n; ++i) ss += buf[tid][i];
+    }
+    __syncthreads();
+  }
+  if (tid < RS_ROWS && m0 + tid < M) out[m0 + tid] = 1.0f / sqrtf(ss * inv_d + eps);
 }
 
 // Epilogue of one 16 x 16 output tile held by a wave: lane (g, r) holds
@@ -97,7 +104,7 @@ __device__ __forceinline__ void tb_epilogue(const GemmArgs &a, int tile, int m, 
       *(float4 *)hp = make_float4(hn[0], hn[1], hn[2], hn[3]);
       if (a.xb != nullptr) {
         const float *gn = a.g_next + n0;
-        *(uint2 *)((uint16_t *)a.xb + (size_t)m * a.ld_h + n0) =
+        *(uint2 *)((uint16_t *)a.xb + pk_off(m, n0, a.pk_steps)) =
             tb_pack4(gn[0] * hn[0], gn[1] * hn[1], gn[2] * hn[2], gn[3] * hn[3]);
       }
     }
@@ -115,7 +122,7 @@ __device__ __forceinline__ void tb_epilogue(const GemmArgs &a, int tile, int m, 
         const float gt = acc[0][i] * rsc, up = acc[NT - 1][i] * rsc;
         o[i] = gt / (1.0f + expf(-gt)) * up;
       }
-      *(uint2 *)((uint16_t *)a.act + (size_t)m * a.ld_act + tile * 16 + grp * 4) = tb_pack4(o[0], o[1], o[2], o[3]);
+      *(uint2 *)((uint16_t *)a.act + pk_off(m, tile * 16 + grp * 4, a.pk_steps)) = tb_pack4(o[0], o[1], o[2], o[3]);
     }
   }
 }
@@ -134,7 +141,7 @@ __device__ __forceinline__ void tb_qkv_block(const GemmArgs &a, int T0, int mbas
                                              int grp, Acc acc) {
   const int hd = a.head_dim;
   const int nq = a.n_heads * hd, nk = a.n_kv_heads * hd;
-  const int n_tiles = a.N / 16;
+  const int n_tiles = (a.N + 15) / 16;
   const bool lo = grp < 2;
   int pos[NF], seq[NF], ent[NF];
   bool ok[NF];
@@ -202,151 +209,71 @@ __device__ __forceinline__ void tb_qkv_block(const GemmArgs &a, int T0, int mbas
   }
 }
 
-template <int EPI>
-__global__ __launch_bounds__(TB_THREADS) void gemm_tiled_kernel(GemmArgs a) {
-  constexpr int NT = (EPI == EPI_SWIGLU) ? 2 : 1;   // interleaved gate/up blocks
-  constexpr int TN = 4 / NT;                        // weight tiles per wave
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r16 = lane & 15, grp = lane >> 4;
-  const int n_tiles = a.N / 16;
-  const int tile0 = (blockIdx.x * 2 + (wave & 1)) * TN;
-  const int m_base = blockIdx.y * TB_ROWS + (wave >> 1) * 64;
-  const int nsteps = a.nsteps_w;
+#define RING_LDS(p) ((__attribute__((address_space(3))) void *)(p))
 
-  const char *wp[TN];
-  bool tok[TN];
-#pragma unroll
-  for (int t = 0; t < TN; ++t) {
-    tok[t] = tile0 + t < n_tiles;
-    wp[t] = (const char *)a.wp + (size_t)(tok[t] ? tile0 + t : 0) * nsteps * NT * 1024 + lane * 16;
-  }
-  const uint16_t *xr[TB_MF];
-  bool xok[TB_MF];
-#pragma unroll
-  for (int f = 0; f < TB_MF; ++f) {
-    const int m = m_base + f * 16 + r16;
-    xok[f] = m < a.M;
-    xr[f] = (const uint16_t *)a.x + (size_t)(xok[f] ? m : 0) * a.ldx + grp * 8;
-  }
+// BNB weight blocks x BMF input fragments per workgroup of WN x WM waves,
+// stages of KS k-steps, NBUF ring slots.
+template <int BNB_, int BMF_, int WN_, int WM_, int KS_, int NBUF_>
+struct RingTile {
+  static constexpr int BNB = BNB_, BMF = BMF_, WN = WN_, WM = WM_, KS = KS_, NBUF = NBUF_;
+  static constexpr int NW = WN * WM, WB = BNB / WN, WF = BMF / WM;
+  static constexpr int NBLK = KS * (BNB + BMF);       // 1 KB blocks per stage
+  static constexpr int PT = NBLK / NW;                // transfers per wave and stage
+  static constexpr int LDS_BYTES = NBUF * NBLK * 1024;
+  static_assert(BNB % WN == 0 && BMF % WM == 0 && NBLK % NW == 0 && NBUF >= 2, "ring tile");
+  static_assert((NBUF - 1) * PT < 64, "vmcnt field");
+  static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+};
 
-  tb_f32x4 acc[TN][NT][TB_MF];
-#pragma unroll
-  for (int t = 0; t < TN; ++t)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int f = 0; f < TB_MF; ++f) acc[t][nt][f] = tb_f32x4{0.f, 0.f, 0.f, 0.f};
-
-  tb_u32x4 wa[TN][NT], xa[TB_MF], wb[TN][NT], xb[TB_MF];
-  auto load = [&](int s, tb_u32x4 (&w)[TN][NT], tb_u32x4 (&x)[TB_MF]) {
-    const bool sin = s < nsteps;
-    const bool kin = sin && (s * 32 + grp * 8 < a.K);
-#pragma unroll
-    for (int t = 0; t < TN; ++t)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        w[t][nt] = (sin && tok[t]) ? *(const tb_u32x4 *)(wp[t] + ((size_t)s * NT + nt) * 1024)
-                                   : tb_u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int f = 0; f < TB_MF; ++f)
-      x[f] = (kin && xok[f]) ? *(const tb_u32x4 *)(xr[f] + s * 32) : tb_u32x4{0u, 0u, 0u, 0u};
-  };
-  auto mma = [&](const tb_u32x4 (&w)[TN][NT], const tb_u32x4 (&x)[TB_MF]) {
-#pragma unroll
-    for (int t = 0; t < TN; ++t)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int f = 0; f < TB_MF; ++f)
-          acc[t][nt][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-              __builtin_bit_cast(tb_bf16x8, w[t][nt]), __builtin_bit_cast(tb_bf16x8, x[f]), acc[t][nt][f], 0, 0, 0);
-  };
-  load(0, wa, xa);
-  for (int s = 0; s < nsteps; s += 2) {
-    load(s + 1, wb, xb);
-    mma(wa, xa);
-    if (s + 1 >= nsteps) break;
-    load(s + 2, wa, xa);
-    mma(wb, xb);
-  }
-
-  // RMSNorm scale of each input row (lane j sums the partials of row
-  // m_base + j in order), then handed to the lanes holding that row
-  float rsc[TB_MF];
-#pragma unroll
-  for (int f = 0; f < TB_MF; ++f) {
-    const int m = m_base + f * 16 + r16;
-    rsc[f] = (a.row_rsc != nullptr && m < a.M) ? a.row_rsc[m] : 1.f;
-  }
-
-  if constexpr (EPI == EPI_QKV) {
-    tb_qkv_block<TN, TB_MF>(a, tile0, m_base, rsc, r16, grp, [&](int t, int f) { return acc[t][0][f]; });
-  } else {
-#pragma unroll
-    for (int t = 0; t < TN; ++t) {
-      if (!tok[t]) continue;                  // uniform across the wave
-#pragma unroll
-      for (int f = 0; f < TB_MF; ++f) {
-        const int m = m_base + f * 16 + r16;
-        tb_f32x4 at[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) at[nt] = acc[t][nt][f];
-        tb_epilogue<EPI, NT>(a, tile0 + t, m, m < a.M, at, rsc[f], grp);
-      }
-    }
-  }
+// Per-stage barrier: this wave's transfers are done but for the youngest
+// VMCNT ones and its LDS reads have all returned; then meet the other waves.
+// Unlike __syncthreads() it leaves the younger transfers in flight.  The
+// empty asm statements and the scheduling barriers emit nothing; they keep
+// the compiler from moving anything across the wait.
+template <int VMCNT>
+__device__ __forceinline__ void ring_step() {
+  static_assert(VMCNT >= 0 && VMCNT < 64, "vmcnt field");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0070 | (VMCNT & 15) | ((VMCNT >> 4) << 14));   // lgkmcnt 0, expcnt: no wait
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+}
+// The same with at most `stages` (0 .. NBUF - 1) whole stages outstanding.
+template <typename T, int S = T::NBUF - 1>
+__device__ __forceinline__ void ring_wait(int stages) {
+  if constexpr (S <= 0) ring_step<0>();
+  else if (stages >= S) ring_step<S * T::PT>();
+  else ring_wait<T, S - 1>(stages);
 }
 
-// Large form, taken whenever its grid has at least BG_MIN_WG workgroups
-// (below that the 128 x 128 form keeps more CUs busy).  A workgroup of eight
-// waves owns 256 weight rows (16 packed blocks per k-step: 16 tiles, or 8
-// gate/up pairs) x 256 input rows and stages both operands through LDS in
-// fragment order, so each operand byte fetched from L2 feeds 16 MFMA tiles
-// instead of 2.  The k-steps (32 KB each) move global -> LDS with direct
-// transfers (global_load_lds, 16 bytes per lane at LDS base + 16 x lane)
-// into a ring of four slots, three steps ahead of the products: no staging
-// registers, and each wave waits (vmcnt) only for its own oldest step before
-// the per-step barrier.  Wave (wn, wm) multiplies weight blocks
-// 8 wn .. 8 wn + 7 by input fragments 4 wm .. 4 wm + 3 (128 x 64 outputs)
-// with the operand roles of gemm_tiled_kernel, accumulating the k-steps in
-// order, and hands each tile to the shared epilogue.  Workgroups are
-// numbered so that each XCD takes a contiguous run of tiles, grouped eight
-// input blocks deep, which keeps the operands the XCD's waves share in its
-// own L2.
-constexpr int BG_THREADS = 512;
-constexpr int BG_ROWS = 256;      // input rows per workgroup
-constexpr int BG_BLK = 16;        // weight blocks per k-step per workgroup
-constexpr int BG_NBUF = 4;        // LDS stages in the ring (three in flight)
-constexpr int BG_GROUP = 8;       // input blocks per tile group
-constexpr int BG_MIN_WG = 96;     // smallest grid that takes this form
+template <int EPI, typename T>
+__global__ __launch_bounds__(64 * T::NW) __attribute__((amdgpu_waves_per_eu(2)))
+void gemm_ring_kernel(GemmArgs a, int n_blk_n, int n_wg, int group) {
+  constexpr int NT = (EPI == EPI_SWIGLU) ? 2 : 1;     // interleaved gate/up blocks
+  constexpr int WB = T::WB, WF = T::WF, KS = T::KS, NBUF = T::NBUF, PT = T::PT;
+  constexpr int TPW = T::BNB / NT;                    // output tiles per workgroup
+  static_assert(WB % NT == 0, "a wave owns whole gate/up pairs");
+  __shared__ __attribute__((aligned(16))) char ring[T::LDS_BYTES];   // [slot][stage block][lane] of 16 bytes
 
-__device__ tb_u32x4 bg_zero[64];  // source of the zero lanes outside the operands
-
-#define BG_LDS(p) ((__attribute__((address_space(3))) void *)(p))
-
-template <int EPI>
-__global__ __launch_bounds__(BG_THREADS) void gemm_big_kernel(GemmArgs a, int n_blk_n, int n_wg) {
-  constexpr int NT = (EPI == EPI_SWIGLU) ? 2 : 1;   // interleaved gate/up blocks
-  constexpr int TPW = BG_BLK / NT;                  // output tiles per workgroup
-  constexpr int WB = 8;                             // weight blocks per wave
-  constexpr int WF = 4;                             // input fragments per wave
-  constexpr int NBLK = 2 * BG_BLK;                  // 1 KB blocks per stage
-  __shared__ tb_u32x4 lds[BG_NBUF][NBLK][64];       // [stage slot][weight blocks | fragments][lane]
-
+  // Each XCD takes a contiguous run of tiles, `group` input blocks deep, so
+  // that the operands its workgroups share stay in its own L2.
   const int xcd = blockIdx.x % 8, jx = blockIdx.x / 8;
   const int base = n_wg / 8, rem = n_wg % 8;
   const int t = xcd * base + min(xcd, rem) + jx;
   const int n_blk_m = n_wg / n_blk_n;
-  const int per_group = BG_GROUP * n_blk_n;
-  const int g = t / per_group, first_m = g * BG_GROUP;
-  const int gsize = min(BG_GROUP, n_blk_m - first_m);
+  const int per_group = group * n_blk_n;
+  const int g = t / per_group, first_m = g * group;
+  const int gsize = min(group, n_blk_m - first_m);
   const int mb = first_m + (t % per_group) % gsize, nb = (t % per_group) / gsize;
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r16 = lane & 15, grp = lane >> 4;
-  const int wn = wave & 1, wm = wave >> 1;
-  const int n_tiles = a.N / 16, nsteps = a.nsteps_w;
-  const int tile0 = nb * TPW, m0 = mb * BG_ROWS;
+  const int wn = wave % T::WN, wm = wave / T::WN;
+  const int n_tiles = (a.N + 15) / 16, nsteps = a.nsteps_w;
+  const int tile0 = nb * TPW, f0 = mb * T::BMF, n_frag = (a.M + 15) / 16;
+  const int nst = (nsteps + KS - 1) / KS;             // stages
 
   tb_f32x4 acc[WB][WF];
 #pragma unroll
@@ -354,62 +281,111 @@ __global__ __launch_bounds__(BG_THREADS) void gemm_big_kernel(GemmArgs a, int n_
 #pragma unroll
     for (int f = 0; f < WF; ++f) acc[jb][f] = tb_f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // one k-step into slot `slot`: wave w moves weight blocks w, w + 8 and
-  // input fragments w, w + 8 (1 KB each) global -> LDS, one instruction per
-  // block; lanes outside the operands read zeros.  The source is chosen by
-  // selects, so every wave issues exactly NBLK / 8 transfers per step.
-  const uintptr_t zero = (uintptr_t)(bg_zero + lane);
-  auto issue = [&](int step, int slot) {
+  // this wave's transfers of a stage: block b = wave + NW i is k-step
+  // b / (BNB + BMF) of weight block or input fragment b % (BNB + BMF).  Tiles
+  // and fragments past the operands read the last one (their outputs are not
+  // stored), k-steps past the end the last one too (they are not multiplied).
+  auto issue = [&](int st, int slot) {
 #pragma unroll
-    for (int i = 0; i < NBLK / 8; ++i) {
-      const int b = wave + 8 * i;
-      uintptr_t src;
-      if (i < 2) {                            // weight block b
-        const int tile = tile0 + b / NT, nt = b % NT;
-        const uintptr_t wa = (uintptr_t)a.wp + (((size_t)tile * nsteps + step) * NT + nt) * 1024 + lane * 16;
-        src = tile < n_tiles ? wa : zero;
-      } else {                                // input fragment b - 16
-        const int m = m0 + (b - BG_BLK) * 16 + r16, k = step * 32 + grp * 8;
-        const uintptr_t xa = (uintptr_t)((const uint16_t *)a.x + (size_t)m * a.ldx + k);
-        src = ((m < a.M) & (k < a.K)) ? xa : zero;
+    for (int i = 0; i < PT; ++i) {
+      const int b = wave + T::NW * i, j = b % (T::BNB + T::BMF);
+      const int step = KS == 1 ? st : min(st * KS + b / (T::BNB + T::BMF), nsteps - 1);
+      size_t off;
+      const char *p;
+      if (j < T::BNB) {
+        off = (((size_t)min(tile0 + j / NT, n_tiles - 1) * nsteps + step) * NT + j % NT) * 1024;
+        p = (const char *)a.wp;
+      } else {
+        off = ((size_t)min(f0 + j - T::BNB, n_frag - 1) * nsteps + step) * 1024;
+        p = (const char *)a.x;
       }
-      __builtin_amdgcn_global_load_lds((const void *)src, BG_LDS(&lds[slot][b][0]), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const void *)(p + off + lane * 16),
+                                       RING_LDS(ring + ((size_t)slot * T::NBLK + b) * 1024), 16, 0, 0);
     }
   };
-  for (int s = 0; s < BG_NBUF - 1 && s < nsteps; ++s) issue(s, s);
-  for (int st = 0; st < nsteps; ++st) {
-    // this wave's transfers of step st are done once at most those of the
-    // (up to two) younger steps are outstanding; the barrier makes every
-    // wave's done, and tells that all waves have finished step st - 1
-    const int younger = min(nsteps - 1 - st, BG_NBUF - 2);
-    if (younger >= 2) lds_ring_step<8>();
-    else if (younger == 1) lds_ring_step<4>();
-    else lds_ring_step<0>();
-    if (st + BG_NBUF - 1 < nsteps) issue(st + BG_NBUF - 1, (st + BG_NBUF - 1) % BG_NBUF);
-    const int slot = st % BG_NBUF;
-    tb_u32x4 w[WB], x[WF];
+  struct Set {
+    tb_u32x4 w[KS][WB], x[KS][WF];
+  };
+  auto fetch = [&](int slot, Set &s) {
 #pragma unroll
-    for (int jb = 0; jb < WB; ++jb) w[jb] = lds[slot][wn * WB + jb][lane];
+    for (int k = 0; k < KS; ++k) {
+      const tb_u32x4 *blk = (const tb_u32x4 *)(ring + ((size_t)slot * T::NBLK + k * (T::BNB + T::BMF)) * 1024) + lane;
 #pragma unroll
-    for (int f = 0; f < WF; ++f) x[f] = lds[slot][BG_BLK + wm * WF + f][lane];
+      for (int f = 0; f < WF; ++f) s.x[k][f] = blk[(T::BNB + wm * WF + f) * 64];
+#pragma unroll
+      for (int jb = 0; jb < WB; ++jb) s.w[k][jb] = blk[(wn * WB + jb) * 64];
+    }
+  };
+  auto mma = [&](int k, const Set &s) {
 #pragma unroll
     for (int jb = 0; jb < WB; ++jb)
 #pragma unroll
       for (int f = 0; f < WF; ++f)
-        acc[jb][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(tb_bf16x8, w[jb]),
-                                                             __builtin_bit_cast(tb_bf16x8, x[f]), acc[jb][f], 0, 0, 0);
+        acc[jb][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(tb_bf16x8, s.w[k][jb]),
+                                                             __builtin_bit_cast(tb_bf16x8, s.x[k][f]), acc[jb][f], 0, 0, 0);
+  };
+  // One DS read per PER products, so that the reads of the next stage spread
+  // over this stage's products.
+  constexpr int READS = KS * (WB + WF), PRODS = KS * WB * WF, PER = PRODS / READS > 0 ? PRODS / READS : 1;
+  auto interleave = [&]() {
+    __builtin_amdgcn_sched_group_barrier(0x020, PT, 0);         // transfers first
+#pragma unroll
+    for (int i = 0; i < READS; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, PER, 0);
+    }
+  };
+
+  // stages 0 .. NBUF - 1 in flight; stage 0 landed, its fragments requested
+  for (int s = 0; s < NBUF && s < nst; ++s) issue(s, s);
+  ring_wait<T>(min(nst, NBUF) - 1);
+  Set A, B;
+  fetch(0, A);
+  // Iteration st: stage st + 1 has landed for every wave and every wave holds
+  // stage st in registers, whose slot therefore takes stage st + NBUF; stage
+  // st + 1 is read while stage st is multiplied.
+  int st = 0, slot = 0;                                 // slot of stage st
+  auto full = [&](const Set &cur, Set &nxt) {           // st + NBUF < nst
+    ring_step<(NBUF - 2) * PT>();
+    issue(st + NBUF, slot);
+    slot = slot + 1 == NBUF ? 0 : slot + 1;
+    fetch(slot, nxt);
+#pragma unroll
+    for (int k = 0; k < KS; ++k) mma(k, cur);
+    interleave();
+    ++st;
+  };
+  while (st + NBUF + 1 < nst) {
+    full(A, B);
+    full(B, A);
+  }
+  // the last stages: little or nothing left to request
+  auto tail = [&](const Set &cur, Set &nxt) {
+    if (st + 1 < nst) {
+      ring_wait<T>(min(nst - 2 - st, NBUF - 2));
+      if (st + NBUF < nst) issue(st + NBUF, slot);
+      slot = slot + 1 == NBUF ? 0 : slot + 1;
+      fetch(slot, nxt);
+    }
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+      if (KS == 1 || st * KS + k < nsteps) mma(k, cur);
+    ++st;
+  };
+  while (st < nst) {
+    tail(A, B);
+    if (st >= nst) break;
+    tail(B, A);
   }
 
-  // RMSNorm scale of each input row of the wave (lane j sums the partials of
-  // row m0 + 64 wm + j in order), handed to the lanes holding that row
   float rsc[WF];
 #pragma unroll
   for (int f = 0; f < WF; ++f) {
-    const int m = m0 + wm * 64 + f * 16 + r16;
+    const int m = (f0 + wm * WF + f) * 16 + r16;
     rsc[f] = (a.row_rsc != nullptr && m < a.M) ? a.row_rsc[m] : 1.f;
   }
   if constexpr (EPI == EPI_QKV) {
-    tb_qkv_block<WB, WF>(a, tile0 + wn * WB, m0 + wm * 64, rsc, r16, grp, [&](int p, int f) { return acc[p][f]; });
+    tb_qkv_block<WB, WF>(a, tile0 + wn * WB, (f0 + wm * WF) * 16, rsc, r16, grp, [&](int p, int f) { return acc[p][f]; });
   } else {
 #pragma unroll
     for (int p = 0; p < WB / NT; ++p) {
@@ -417,7 +393,7 @@ __global__ __launch_bounds__(BG_THREADS) void gemm_big_kernel(GemmArgs a, int n_
       if (tile >= n_tiles) continue;          // uniform across the wave
 #pragma unroll
       for (int f = 0; f < WF; ++f) {
-        const int m = m0 + wm * 64 + f * 16 + r16;
+        const int m = (f0 + wm * WF + f) * 16 + r16;
         tb_f32x4 at[NT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) at[nt] = acc[p * NT + nt][f];
@@ -430,54 +406,95 @@ __global__ __launch_bounds__(BG_THREADS) void gemm_big_kernel(GemmArgs a, int n_
 }  // namespace
 
 bool gemm_tiled_supported(int epi, const GemmArgs &a) {
-  if (a.M < 1 || a.N < 16 || a.N % 16 || a.K < 8 || a.K % 8 || a.ldx % 8 || a.row_bnd != nullptr) return false;
+  if (a.M < 1 || a.N < 1 || a.nsteps_w < 1 || a.row_bnd != nullptr) return false;
   if (a.part != nullptr && a.row_rsc == nullptr) return false;   // the row scales come precomputed
-  if ((a.M + TB_ROWS - 1) / TB_ROWS > 65535) return false;
+  if ((a.M + 127) / 128 > 65535) return false;
   switch (epi) {
-    case EPI_PLAIN: return a.ld_out % 4 == 0;
+    case EPI_PLAIN: return a.N % 16 == 0 && a.ld_out % 4 == 0;
     case EPI_QKV: return a.ld_out % 4 == 0 && a.head_dim % 16 == 0;
-    case EPI_RESID: return a.ld_h % 4 == 0;
-    case EPI_SWIGLU: return a.ld_act % 4 == 0;
+    case EPI_RESID: return a.N % 16 == 0 && a.ld_h % 4 == 0;
+    case EPI_SWIGLU: return true;
     default: return false;
   }
 }
 
 hipError_t launch_row_scale(const float *part, int n_part, int M, float inv_d, float eps, float *out, hipStream_t s) {
   if (part == nullptr || out == nullptr || n_part < 1 || M < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(row_scale_kernel, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, part, n_part, M, inv_d, eps,
-                     out);
+  hipLaunchKernelGGL(row_scale_kernel, dim3((unsigned)((M + RS_ROWS - 1) / RS_ROWS)), dim3(256), 0, s, part, n_part, M,
+                     inv_d, eps, out);
   return hipGetLastError();
+}
+
+template <int EPI, typename T>
+static hipError_t launch_ring(const GemmArgs &a, hipStream_t s) {
+  constexpr int GROUP = 2048 / (16 * T::BMF);          // rows of a tile group: 2048
+  const int tpw = T::BNB / (EPI == EPI_SWIGLU ? 2 : 1);
+  const int n_blk_n = ((a.N + 15) / 16 + tpw - 1) / tpw, n_blk_m = ((a.M + 15) / 16 + T::BMF - 1) / T::BMF;
+  const long long n_wg = (long long)n_blk_n * n_blk_m;
+  if (n_wg > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((gemm_ring_kernel<EPI, T>), dim3((unsigned)n_wg), dim3(64 * T::NW), 0, s, a, n_blk_n, (int)n_wg,
+                     GROUP);
+  return hipGetLastError();
+}
+
+// The tiles, largest first, with what one workgroup's k-step costs while a
+// workgroup runs on every compute unit, and its fixed part (first loads,
+// epilogue), both in ns.  Measured on the 4096-wide projections at 97, 512 and
+// 8192 rows from the slope between K = 4096 and K = 14336; a k-step is bound
+// by LDS (fragment reads at 128 and transfers at 64 bytes a clock), which is
+// why a larger tile costs less per output, and the largest by the matrix
+// cores and the card's power.  launch_gemm_tiled takes the tile of the least
+// rounds x (k-steps x step + fixed): small ones where a grid of large ones
+// leaves compute units idle.  At 512 rows (K = 4096 / 4096 / 14336, N = 6144 /
+// 4096 / 4096) 128 x 128, 64 x 128 and 64 x 128 take 39, 28 and 92 us against
+// 86, 83 and 258 us of 256 x 256; at 97 rows 64 x 64, 32 x 64 and 32 x 64 take
+// 21, 14 and 44 us; 8192 rows run 256 x 256 at 1.2-1.36 PFLOP/s.
+typedef RingTile<16, 16, 4, 2, 1, 5> Tile256x256;
+typedef RingTile<16, 8, 2, 2, 1, 3> Tile256x128;
+typedef RingTile<8, 8, 2, 2, 1, 5> Tile128x128;
+typedef RingTile<4, 8, 2, 2, 2, 3> Tile64x128;
+typedef RingTile<4, 4, 1, 4, 2, 4> Tile64x64;
+typedef RingTile<2, 4, 1, 4, 4, 5> Tile32x64;
+struct TileCost {
+  int blocks, frags;          // weight blocks x input fragments
+  int step_ns, fixed_ns;
+};
+static const TileCost kTileCost[] = {{16, 16, 750, 12000}, {16, 8, 400, 7000}, {8, 8, 275, 4000},
+                                     {4, 8, 200, 3000},    {4, 4, 130, 3000},  {2, 4, 100, 2000}};
+
+static int choose_tile(int n_blocks, int n_frag, int nsteps) {
+  int best = 0;
+  double best_ns = 0.0;
+  for (int i = 0; i < (int)(sizeof(kTileCost) / sizeof(kTileCost[0])); ++i) {
+    const TileCost &c = kTileCost[i];
+    const long long n_wg = (long long)((n_blocks + c.blocks - 1) / c.blocks) * ((n_frag + c.frags - 1) / c.frags);
+    const double ns = (double)((n_wg + 255) / 256) * ((double)nsteps * c.step_ns + c.fixed_ns);
+    if (i == 0 || ns < best_ns) { best = i; best_ns = ns; }
+  }
+  return best;
+}
+
+template <int EPI>
+static hipError_t launch_tile(const GemmArgs &a, hipStream_t s) {
+  switch (choose_tile((a.N + 15) / 16 * (EPI == EPI_SWIGLU ? 2 : 1), (a.M + 15) / 16, a.nsteps_w)) {
+    case 0: return launch_ring<EPI, Tile256x256>(a, s);
+    case 1: return launch_ring<EPI, Tile256x128>(a, s);
+    case 2: return launch_ring<EPI, Tile128x128>(a, s);
+    case 3: return launch_ring<EPI, Tile64x128>(a, s);
+    case 4: return launch_ring<EPI, Tile64x64>(a, s);
+    default: return launch_ring<EPI, Tile32x64>(a, s);
+  }
 }
 
 hipError_t launch_gemm_tiled(int epi, const GemmArgs &a, hipStream_t s) {
   if (!gemm_tiled_supported(epi, a)) return hipErrorInvalidValue;
-  const int n_tiles = a.N / 16;
-  const int tpw = BG_BLK / (epi == EPI_SWIGLU ? 2 : 1);
-  const int n_blk_n = (n_tiles + tpw - 1) / tpw, n_blk_m = (a.M + BG_ROWS - 1) / BG_ROWS;
-  const long long n_wg = (long long)n_blk_n * n_blk_m;
-  if (n_wg >= BG_MIN_WG) {
-    if (n_wg > 0x7fffffffLL) return hipErrorInvalidValue;
-    dim3 grid((unsigned)n_wg), block(BG_THREADS);
-    switch (epi) {
-      case EPI_PLAIN: hipLaunchKernelGGL(gemm_big_kernel<EPI_PLAIN>, grid, block, 0, s, a, n_blk_n, (int)n_wg); break;
-      case EPI_QKV: hipLaunchKernelGGL(gemm_big_kernel<EPI_QKV>, grid, block, 0, s, a, n_blk_n, (int)n_wg); break;
-      case EPI_RESID: hipLaunchKernelGGL(gemm_big_kernel<EPI_RESID>, grid, block, 0, s, a, n_blk_n, (int)n_wg); break;
-      case EPI_SWIGLU: hipLaunchKernelGGL(gemm_big_kernel<EPI_SWIGLU>, grid, block, 0, s, a, n_blk_n, (int)n_wg); break;
-      default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-  }
-  const int tiles_per_wg = epi == EPI_SWIGLU ? 4 : 8;
-  dim3 grid((n_tiles + tiles_per_wg - 1) / tiles_per_wg, (a.M + TB_ROWS - 1) / TB_ROWS);
-  dim3 block(TB_THREADS);
   switch (epi) {
-    case EPI_PLAIN: hipLaunchKernelGGL(gemm_tiled_kernel<EPI_PLAIN>, grid, block, 0, s, a); break;
-    case EPI_QKV: hipLaunchKernelGGL(gemm_tiled_kernel<EPI_QKV>, grid, block, 0, s, a); break;
-    case EPI_RESID: hipLaunchKernelGGL(gemm_tiled_kernel<EPI_RESID>, grid, block, 0, s, a); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL(gemm_tiled_kernel<EPI_SWIGLU>, grid, block, 0, s, a); break;
+    case EPI_PLAIN: return launch_tile<EPI_PLAIN>(a, s);
+    case EPI_QKV: return launch_tile<EPI_QKV>(a, s);
+    case EPI_RESID: return launch_tile<EPI_RESID>(a, s);
+    case EPI_SWIGLU: return launch_tile<EPI_SWIGLU>(a, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace dex

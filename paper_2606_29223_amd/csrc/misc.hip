@@ -75,7 +75,9 @@ __global__ __launch_bounds__(PREP_THREADS) void prep_kernel(PrepArgs a) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) h[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
   if (a.xb != nullptr) {
-    uint4 *xb = (uint4 *)((T *)a.xb + (size_t)mo * a.d + c0);
+    const bool packed = sizeof(T) == 2 && a.xb_steps > 0;
+    uint4 *xb = (uint4 *)((T *)a.xb + (packed ? pk_off(mo, c0, a.xb_steps) : (size_t)mo * a.d + c0));
+    const int qs = packed ? 16 : 1;            // a packed row's next 8 columns lie 16 lanes on
 #pragma unroll
     for (int q = 0; q < 16 / EPV; ++q) {
       uint32_t w[4];
@@ -88,7 +90,7 @@ __global__ __launch_bounds__(PREP_THREADS) void prep_kernel(PrepArgs a) {
           w[k] = __float_as_uint(g[q * EPV + k] * v[q * EPV + k]);
         }
       }
-      xb[q] = make_uint4(w[0], w[1], w[2], w[3]);
+      xb[q * qs] = make_uint4(w[0], w[1], w[2], w[3]);
     }
   }
   if (from_embed) {

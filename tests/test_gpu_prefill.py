@@ -1,0 +1,66 @@
+"""GPU: the prompt path's kernels at the sizes where they can go wrong --
+edges of every prompt-GEMM tile, rings with fewer stages than slots, packed
+activations whose last k-step is not full."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import ar
+from synth import configs, gen
+from tests.gpu_common import GAP, LOGIT_RTOL, check_tokens_teacher_forced, max_rel_err, run, torch_cuda
+from tests.test_gpu_gemm import _gemm, _inputs
+
+pytestmark = pytest.mark.gpu
+
+
+# (N, K, M): by the cost rule of the prompt GEMM these take, in turn, the
+# 256 x 256, 256 x 128, 128 x 128, 64 x 128, 64 x 64 and 32 x 64 tile, each
+# with a ragged last block in N and M and a last k-step only partly inside K;
+# then one, two and five k-steps (rings that never fill)
+@pytest.mark.parametrize("N,K,M", [(12304, 264, 2050), (8208, 264, 2050), (4112, 264, 530), (2064, 1096, 500),
+                                   (1552, 776, 500), (784, 776, 65), (4112, 24, 300), (4112, 40, 97), (528, 136, 257)])
+def test_prompt_gemm_tiles(N, K, M):
+    """float64 parity (fp32 accumulation of bf16 products: K eps sqrt-scaled,
+    the bound of the other GEMM tests), and a row's bits do not depend on the
+    tile: the last 70 rows alone take a smaller one."""
+    torch = torch_cuda()
+    Wt, xt, W64, x64 = _inputs(torch, 1, N, K, M, 900 + N + K)
+    y = _gemm(torch, 1, Wt, xt, M)
+    assert np.abs(y - x64 @ W64.T).max() <= 2e-5 * np.sqrt(K) * 0.05 + 1e-6
+    lo = max(0, M - 70)
+    part = _gemm(torch, 1, Wt, xt[lo:].contiguous(), M - lo)
+    if M - lo > 64:                              # both M-tiled (the decode kernel sums in another order)
+        assert np.array_equal(part.view(np.uint32), y[lo:].view(np.uint32))
+
+
+@pytest.mark.parametrize("d,F,H,Hkv,hd,P", [(80, 88, 4, 2, 32, 70), (48, 72, 2, 1, 64, 90), (144, 200, 3, 1, 128, 67)])
+def test_prompt_with_unfilled_k_steps(d, F, H, Hkv, hd, P):
+    """bf16 models whose widths do not fill 32-column k-steps (the packed
+    activations end in zeros), with head_dim 32 (whose attention writes
+    row-major and is packed afterwards) and three query heads per kv head:
+    y_0 and the next tokens follow the oracle, exit logits within 2e-2."""
+    torch = torch_cuda()
+    from paper_2606_29223_amd import dexlib
+    cfg = configs.scaled_down(configs.get("small-12L-d768-bf16"), n_layers=2, d_model=d, d_ffn=F, vocab=512)
+    cfg.update(n_heads=H, n_kv_heads=Hkv, head_dim=hd, prompt_len=P, batch=2, prompt_seeds=[7301, 7302])
+    w = gen.generate_model(cfg)
+    T = 4
+    dec = dexlib.Decoder(cfg, dexlib.device_weights(cfg, w), explored=[2], width_cap=1, max_context=P + T)
+    prompt = gen.prompts(cfg)
+    tap = torch.zeros((2, cfg["vocab"]), dtype=torch.float32, device="cuda")
+    dec.set_logits_tap(tap)
+    toks, _ = run(dec, prompt, T)
+    again = dec.prefill(prompt)
+    first_logits = tap.cpu().numpy()
+    dec.close()
+    m = oracle.Model(cfg, gen.model_as_f64(cfg, w))
+    for b in range(2):
+        pl, seq = [int(t) for t in prompt[b]], [int(t) for t in toks[b]]
+        assert int(again[b]) == seq[0]
+        pf = m.prefill(pl)
+        z0 = m.exit_logits(pf[2])
+        assert max_rel_err(first_logits[b], z0) <= LOGIT_RTOL
+        if seq[0] != int(np.argmax(z0)):
+            assert z0.max() - z0[seq[0]] < GAP
+        z = ar.depth_logits(m, pl, seq, [2], prefill=pf)
+        check_tokens_teacher_forced(z[:, -1], seq)
