@@ -25,8 +25,8 @@
 // position.  Splits of 64 keys keep a long context spread over many waves:
 // 8192 keys x 8 kv heads x 8 sequences is 9216 waves per layer.
 //
-// Prefill: prefill_attn128_kernel (head_dim 128) and prefill_attn_kernel
-// (head_dim 64) compute causal attention over the prompt's own keys.
+// Prefill: prefill_attn_kernel computes causal attention over the prompt's
+// own keys.
 #include "attn_decode.h"
 
 namespace dex {
@@ -389,202 +389,6 @@ hipError_t launch_combine(int dtype, const CombineArgs &a, int rows, hipStream_t
 
 
 // ------------------------------------------------------------------------
-// Causal prompt attention on the matrix cores (bf16 keys/values).
-//
-// Workgroup = (32 query rows, kv head, sequence); wave w is query head
-// kvh * G + w.  Key blocks of 64 positions are staged in LDS -- K as
-// [key][dim] and V transposed as [dim][key], rows padded so the 16-byte
-// operand reads of a wave hit distinct banks -- and each wave runs
-//   S = Q K^T   (v_mfma_f32_16x16x32_bf16, 2 x 4 tiles of 16 x 16),
-// an online softmax per query row (causal mask on the diagonal block),
-//   O += P V    (P rounded to bf16 through a per-wave LDS tile),
-// and finally writes O / l.  Only prompt prefill uses it: its results feed
-// plain and lattice decoding alike.
-// Max and sum over the 16 lanes of a row with DPP moves; the partner order
-// (lane ^ 1, lane ^ 2, then the other quad, then the other half-row) adds
-// exactly the operands of the xor butterfly, so every lane holds the same bits.
-template <int CTRL>
-__device__ __forceinline__ float pf_dpp(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float row16_max(float v) {
-  v = fmaxf(v, pf_dpp<0xB1>(v));
-  v = fmaxf(v, pf_dpp<0x4E>(v));
-  v = fmaxf(v, pf_dpp<0x141>(v));
-  return fmaxf(v, pf_dpp<0x140>(v));
-}
-__device__ __forceinline__ float row16_sum(float v) {
-  v += pf_dpp<0xB1>(v);
-  v += pf_dpp<0x4E>(v);
-  v += pf_dpp<0x141>(v);
-  return v + pf_dpp<0x140>(v);
-}
-
-template <int HD>
-__global__ __launch_bounds__(512) void prefill_attn_kernel(PrefillAttnArgs a) {
-  constexpr int QB = 32, KB = 64;
-  constexpr int KS = HD / 32;          // MFMA k-steps over head dims
-  constexpr int DT = HD / 16;          // 16-wide output tiles over head dims
-  constexpr int KROW = HD + 8;         // bf16 elements per padded K row
-  constexpr int VROW = KB + 8;         // bf16 elements per padded V^T / P row
-  __shared__ __attribute__((aligned(16))) uint16_t ks[KB][KROW];
-  __shared__ __attribute__((aligned(16))) uint16_t vt[HD][VROW];
-  __shared__ __attribute__((aligned(16))) uint16_t pt[8][QB][VROW];
-
-  const int qb = blockIdx.x, kvh = blockIdx.y, seq = blockIdx.z;
-  const int G = a.n_heads / a.n_kv_heads;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int nthr = blockDim.x;
-  const int r16 = lane & 15, grp = lane >> 4;
-  const int h = kvh * G + wave;
-  const int P = a.prompt_len;
-  const int q0 = qb * QB;
-  const size_t row_base = (size_t)seq * P;
-  const uint16_t *kbase = (const uint16_t *)a.kc + ((size_t)seq * a.n_kv_heads + kvh) * a.kv_entries * HD;
-  const uint16_t *vbase = (const uint16_t *)a.vc + ((size_t)seq * a.n_kv_heads + kvh) * a.kv_entries * HD;
-
-  // Q fragments (A operand): lane holds row r16 of each 16-row tile, dims
-  // ks*32 + grp*8 .. +8, rounded to bf16
-  pf_bf16x8 qf[2][KS];
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
-    const int row = q0 + mt * 16 + r16;
-    const bool ok = row < P;
-    const float *src = a.q + (row_base + (ok ? row : 0)) * a.ldq + h * HD;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      uint16_t t[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) t[e] = ok ? pf_f2bf(src[s * 32 + grp * 8 + e]) : (uint16_t)0;
-      uint4 u;
-      u.x = t[0] | ((uint32_t)t[1] << 16); u.y = t[2] | ((uint32_t)t[3] << 16);
-      u.z = t[4] | ((uint32_t)t[5] << 16); u.w = t[6] | ((uint32_t)t[7] << 16);
-      qf[mt][s] = __builtin_bit_cast(pf_bf16x8, u);
-    }
-  }
-  pf_f32x4 o[2][DT];
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) o[mt][dt] = pf_f32x4{0.f, 0.f, 0.f, 0.f};
-  float mrun[2][4], lrun[2][4];
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { mrun[mt][i] = -INFINITY; lrun[mt][i] = 0.f; }
-
-  const int last_row = min(q0 + QB, P) - 1;
-  for (int k0 = 0; k0 <= last_row; k0 += KB) {
-    __syncthreads();
-    // stage K [key][dim] and V^T [dim][key] (zeros past the prompt)
-    for (int e = threadIdx.x; e < KB * (HD / 8); e += nthr) {
-      const int j = e / (HD / 8), c = e % (HD / 8);
-      uint4 kv = make_uint4(0, 0, 0, 0), vv = make_uint4(0, 0, 0, 0);
-      if (k0 + j < P) {
-        kv = *(const uint4 *)(kbase + (size_t)(k0 + j) * HD + c * 8);
-        vv = *(const uint4 *)(vbase + (size_t)(k0 + j) * HD + c * 8);
-      }
-      *(uint4 *)&ks[j][c * 8] = kv;
-      const uint32_t w[4] = {vv.x, vv.y, vv.z, vv.w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        vt[c * 8 + 2 * q][j] = (uint16_t)(w[q] & 0xffffu);
-        vt[c * 8 + 2 * q + 1][j] = (uint16_t)(w[q] >> 16);
-      }
-    }
-    __syncthreads();
-    if (wave < G) {
-      // S = Q K^T
-      pf_f32x4 s[2][4];
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) s[mt][nt] = pf_f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int st = 0; st < KS; ++st) {
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-          const pf_bf16x8 kb = __builtin_bit_cast(pf_bf16x8, *(const uint4 *)&ks[nt * 16 + r16][st * 32 + grp * 8]);
-#pragma unroll
-          for (int mt = 0; mt < 2; ++mt)
-            s[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[mt][st], kb, s[mt][nt], 0, 0, 0);
-        }
-      }
-      // online softmax: lane holds rows mt*16 + grp*4 + i, key nt*16 + r16
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = q0 + mt * 16 + grp * 4 + i;
-          float mx = -INFINITY;
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt) {
-            const int key = k0 + nt * 16 + r16;
-            float v = s[mt][nt][i] * a.scale;
-            if (key > row || key >= P) v = -INFINITY;
-            s[mt][nt][i] = v;
-            mx = fmaxf(mx, v);
-          }
-#pragma unroll
-          for (int off = 1; off < 16; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-          const float mnew = fmaxf(mrun[mt][i], mx);
-          const float alpha = (mnew == -INFINITY) ? 1.f : expf(mrun[mt][i] - mnew);
-          float sum = 0.f;
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt) {
-            const float p = (s[mt][nt][i] == -INFINITY) ? 0.f : expf(s[mt][nt][i] - mnew);
-            s[mt][nt][i] = p;
-            sum += p;
-          }
-#pragma unroll
-          for (int off = 1; off < 16; off <<= 1) sum += __shfl_xor(sum, off, 64);
-          lrun[mt][i] = lrun[mt][i] * alpha + sum;
-          mrun[mt][i] = mnew;
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) o[mt][dt][i] *= alpha;
-        }
-      }
-      // P (bf16) to this wave's LDS tile, then O += P V
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) pt[wave][mt * 16 + grp * 4 + i][nt * 16 + r16] = pf_f2bf(s[mt][nt][i]);
-    }
-    __syncthreads();
-    if (wave < G) {
-#pragma unroll
-      for (int st = 0; st < KB / 32; ++st) {
-        pf_bf16x8 pa[2];
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-          pa[mt] = __builtin_bit_cast(pf_bf16x8, *(const uint4 *)&pt[wave][mt * 16 + r16][st * 32 + grp * 8]);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          const pf_bf16x8 vb = __builtin_bit_cast(pf_bf16x8, *(const uint4 *)&vt[dt * 16 + r16][st * 32 + grp * 8]);
-#pragma unroll
-          for (int mt = 0; mt < 2; ++mt) o[mt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[mt], vb, o[mt][dt], 0, 0, 0);
-        }
-      }
-    }
-  }
-  if (wave >= G) return;
-  // O / l -> bf16; lane holds rows mt*16 + grp*4 + i, dim dt*16 + r16
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = q0 + mt * 16 + grp * 4 + i;
-      if (row >= P) continue;
-      const float inv = 1.f / lrun[mt][i];
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        ((uint16_t *)a.out)[prefill_out_off(a, row_base + row, h * HD + dt * 16 + r16)] = pf_f2bf(o[mt][dt][i] * inv);
-    }
-}
-
-// ------------------------------------------------------------------------
 // Decode attention on the matrix cores (bf16 caches, head_dim 64 or 128): one
 // wave per work item (attn_mfma_item in attn_decode.h).
 template <int HD>
@@ -632,73 +436,100 @@ __global__ __launch_bounds__(64) void attn_mfma_seg_kernel(AttnArgs a, AttnSegs 
   attn_mfma_item<HD>(a, x - g.item0[k], blockIdx.y, vr, prow, ppos);
 }
 
-// Causal prompt attention for head_dim 128 (bf16), G query heads per kv
-// head with G in {1, 2, 4, 8}.  Workgroup = (32 query rows, kv head,
-// sequence), wave w = query head kvh * G + w; blocks of 64 keys stream into
-// a two-slot LDS ring with direct global -> LDS transfers (one block ahead of
-// the products), shared by the G waves.  Per block each wave computes
-//   S^T = K Q^T   four 16-key tiles against its two 16-query tiles, so each
-//                 lane holds 16 keys of one query: the online-softmax
-//                 statistics are that lane's plus an xor butterfly over the
-//                 four quarter-waves, and the rescaling of O needs no
-//                 exchange;
+// Causal prompt attention on the matrix cores (bf16, head_dim 64 or 128).
+// Workgroup = (QW blocks of 16 MT queries, kv head, sequence), wave w = query
+// head kvh * G + w % G of query block w / G, so that the G QW waves share the
+// keys and values: blocks of KB keys stream into a two-slot LDS ring with
+// direct global -> LDS transfers, one block ahead of the products.  Per block
+// each wave computes
+//   S^T = K Q^T   KB / 16 16-key tiles against its MT 16-query tiles, so each
+//                 lane holds KB / 4 keys of one query: the online-softmax
+//                 statistics are that lane's plus the four quarter-waves',
+//                 and the rescaling of O needs no exchange;
 //   O^T += V^T P^T  V^T through the LDS transpose read, P^T straight from
 //                 the S^T accumulators (k-slot e of a lane is key
 //                 32 st + 4 grp + e or 32 st + 16 + 4 grp + e - 4, the keys it
 //                 holds), O^T rows = head dims, columns = queries.
-// K and V rows are 256 bytes with their 16-byte chunks XOR-swizzled (K: by
-// row mod 16, V: by 2 (row mod 8)) so that the 16 rows of a K fragment read
-// and the four rows of a transpose read land in distinct banks.  Query
-// blocks are dispatched longest first (the causal triangle).
-__device__ uint4 pa_zero[64];   // source of the key rows past the prompt
+// The vector work beside the products bounds it (at 8 x 8192, counters: 245
+// vector instructions against 64 products per 64 keys and 32 queries, the two
+// hardly overlapping), so: scale and reference enter through one fused
+// multiply-add; only the last block is masked; a query's reference is raised
+// (and its O rescaled) only once a score exceeds it by 2^8, which leaves
+// every rounding relative; a lane's denominator stays its own until the end;
+// key rows past the prompt repeat its last one instead of reading zeros.
+// KB depends on head_dim alone and every per-query operation on its own keys
+// alone, so a prompt's bits depend neither on the batch nor on MT.
+// Three waves a SIMD hide more than two with longer blocks do: at 8 x 8192,
+// 32 / 8 heads of 128, KB = 32 takes 4.8 ms and KB = 64 5.2 ms (the earlier
+// kernel, masked and rescaled per block: 6.8 ms); at head_dim 64 four waves
+// fit either way and KB = 64 wins (18 against 23 us at 2 x 1100, 12 heads,
+// where one wave per workgroup took 200 us).  Computing block j + 1's scores
+// next to block j's softmax, or alternating the two phases between two
+// groups of four waves, spills or drops to two waves: 6.3 and 8.4 ms.
+// K and V rows have their 16-byte chunks XOR-swizzled (pa_kswz, pa_vswz) so
+// that the 16 rows of a K fragment read and the eight rows that half a wave
+// reads for a transposed V fragment land in distinct banks.  Query blocks are
+// dispatched longest first (the causal triangle), heads and sequences
+// innermost: with a multiple of eight of them, a kv head's blocks share an XCD.
 
-template <int G>
-__global__ __launch_bounds__(64 * G) __attribute__((amdgpu_waves_per_eu(2))) void prefill_attn128_kernel(PrefillAttnArgs a) {
-  constexpr int HD = 128, KS = 4, DT = 8, NKT = 4, QB = 32, KB = 64;
-  constexpr int NTR = 2 * KB * HD * 2 / 1024;      // 1 KB transfers per key block (K then V)
-  constexpr int PER_WAVE = NTR / G;
-  __shared__ __attribute__((aligned(16))) uint4 kl[2][KB * 16];
-  __shared__ __attribute__((aligned(16))) uint4 vl[2][KB * 16];
+// Max over the four lanes r16, r16 + 16, + 32, + 48.
+__device__ __forceinline__ float quarters_max(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+template <int HD> __device__ __forceinline__ int pa_kswz(int row) { return HD == 128 ? (row & 15) : ((row >> 1) & 7); }
+template <int HD> __device__ __forceinline__ int pa_vswz(int row) { return HD == 128 ? 2 * (row & 7) : 2 * ((row >> 1) & 3); }
 
-  const int P = a.prompt_len;
-  const int nqb = (P + QB - 1) / QB;
-  const int qb = nqb - 1 - (int)blockIdx.x;
-  const int kvh = blockIdx.y, seq = blockIdx.z;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+template <int HD, int MT, int KB>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(KB == 32 ? 3 : 2)))
+void prefill_attn_kernel(PrefillAttnArgs a, int QW, int n_pairs) {
+  constexpr int KS = HD / 32, DT = HD / 16, NKT = KB / 16, QB = 16 * MT;
+  constexpr int CPR = HD / 8;                      // 16-byte chunks per key row
+  constexpr int RPT = 64 / CPR;                    // key rows per 1 KB transfer
+  constexpr int NTR = KB / RPT;                    // transfers per block of keys or values
+  __shared__ __attribute__((aligned(16))) uint4 kl[2][KB * CPR];
+  __shared__ __attribute__((aligned(16))) uint4 vl[2][KB * CPR];
+
+  const int P = a.prompt_len, G = a.n_heads / a.n_kv_heads;
+  const int nqb = (P + QB * QW - 1) / (QB * QW);
+  const int pair = blockIdx.x % n_pairs, wg0 = (nqb - 1 - (int)blockIdx.x / n_pairs) * QB * QW;
+  const int kvh = pair % a.n_kv_heads, seq = pair / a.n_kv_heads;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, nw = G * QW;
   const int r16 = lane & 15, grp = lane >> 4;
   const int tq = lane >> 4, ti = (lane & 15) >> 2, tg = lane & 3;
-  const int h = kvh * G + wave;
-  const int q0 = qb * QB;
+  const int h = kvh * G + wave % G;
+  const int q0 = wg0 + wave / G * QB;
   const size_t row_base = (size_t)seq * P;
   const uint16_t *kbase = (const uint16_t *)a.kc + ((size_t)seq * a.n_kv_heads + kvh) * a.kv_entries * HD;
   const uint16_t *vbase = (const uint16_t *)a.vc + ((size_t)seq * a.n_kv_heads + kvh) * a.kv_entries * HD;
-  const int nblk = (min(q0 + QB, P) - 1) / KB + 1;
+  const int nblk = (min(wg0 + QB * QW, P) - 1) / KB + 1;            // key blocks of the workgroup
+  const int mine = q0 < P ? (min(q0 + QB, P) - 1) / KB + 1 : 0;     // and of this wave
 
-  // key block j into ring slot `slot`: transfer c (0..15 K, 16..31 V) moves
-  // rows 4 (c mod 16) .. +3; lane l fills chunk position l mod 16 of row
-  // 4 (c mod 16) + l / 16 with the swizzled global chunk
-  const uintptr_t zero = (uintptr_t)(pa_zero + lane);
-  auto issue = [&](int j, int slot) {
-#pragma unroll
-    for (int t = 0; t < PER_WAVE; ++t) {
-      const int c = wave + G * t;
-      const bool isv = c >= NTR / 2;
-      const int ci = c % (NTR / 2);
-      const int row = ci * 4 + (lane >> 4), pos = lane & 15;
-      const int chunk = isv ? (pos ^ (2 * (row & 7))) : (pos ^ (row & 15));
-      const int key = j * KB + row;
-      const uintptr_t g = (uintptr_t)((isv ? vbase : kbase) + (size_t)key * HD + chunk * 8);
-      const uintptr_t src = key < P ? g : zero;
-      uint4 *dst = isv ? &vl[slot][ci * 64] : &kl[slot][ci * 64];
-      __builtin_amdgcn_global_load_lds((const void *)src, (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+  // block j of the keys (values) into a ring slot: transfer c moves rows
+  // RPT c .. + RPT - 1; lane l fills chunk position l mod CPR of row
+  // RPT c + l / CPR with the swizzled global chunk.  Rows past the prompt
+  // repeat its last one: no stored query sees them.
+  auto issue = [&](const uint16_t *src, uint4 *dst, int j, bool isv) {
+    const char *blk = (const char *)(src + (size_t)j * KB * HD);
+    const int last = P - 1 - j * KB;
+    for (int c = wave; c < NTR; c += nw) {
+      const int row = c * RPT + lane / CPR;
+      const int chunk = lane % CPR ^ (isv ? pa_vswz<HD>(row) : pa_kswz<HD>(row));
+      const unsigned off = (unsigned)min(row, last) * (HD * 2) + chunk * 16;
+      __builtin_amdgcn_global_load_lds((const void *)(blk + off), (__attribute__((address_space(3))) void *)(dst + c * 64),
+                                       16, 0, 0);
     }
   };
+  issue(kbase, kl[0], 0, false);
+  issue(vbase, vl[0], 0, true);
 
   // Q^T fragments (B operand): lane (query r16 of tile mt, grp) holds dims
   // 32 st + 8 grp .. +8, rounded to bf16
-  pf_bf16x8 qf[2][KS];
+  pf_bf16x8 qf[MT][KS];
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
+  for (int mt = 0; mt < MT; ++mt) {
     const int row = q0 + mt * 16 + r16;
     const bool ok = row < P;
     const float *src = a.q + (row_base + (ok ? row : 0)) * a.ldq + h * HD + grp * 8;
@@ -713,72 +544,74 @@ __global__ __launch_bounds__(64 * G) __attribute__((amdgpu_waves_per_eu(2))) voi
                                                             pf_pack_bf16(x1.x, x1.y), pf_pack_bf16(x1.z, x1.w)));
     }
   }
-  pf_f32x4 o[2][DT];
+  pf_f32x4 o[MT][DT], sc[NKT][MT];
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) o[mt][dt] = pf_f32x4{0.f, 0.f, 0.f, 0.f};
-  float mrun[2] = {-INFINITY, -INFINITY}, lrun[2] = {0.f, 0.f};
-  const float sl2 = a.scale * 1.44269504088896341f;   // scores in log2 units
+  float mrun[MT], lrun[MT];                        // reference (log2 units) and this lane's denominator
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) { mrun[mt] = -INFINITY; lrun[mt] = 0.f; }
+  const float sl2 = a.scale * 1.44269504088896341f;
 
-  issue(0, 0);
-  for (int j = 0; j < nblk; ++j) {
-    const int slot = j & 1, k0 = j * KB;
-    lds_ring_step<0>();                      // block j has landed for every wave, and every
-                                             // wave is past block j - 1
-    if (j + 1 < nblk) issue(j + 1, slot ^ 1);
-    const uint4 *K = kl[slot];
-    // S^T = K Q^T
-    pf_f32x4 sc[NKT][2];
+  auto scores = [&](const uint4 *K, pf_f32x4 (&sc)[NKT][MT]) {
 #pragma unroll
     for (int nt = 0; nt < NKT; ++nt)
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt) sc[nt][mt] = pf_f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int mt = 0; mt < MT; ++mt) sc[nt][mt] = pf_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int st = 0; st < KS; ++st)
 #pragma unroll
       for (int nt = 0; nt < NKT; ++nt) {
-        const pf_bf16x8 kfr = __builtin_bit_cast(pf_bf16x8, K[(nt * 16 + r16) * 16 + ((st * 4 + grp) ^ r16)]);
+        const int row = nt * 16 + r16;
+        const pf_bf16x8 kfr = __builtin_bit_cast(pf_bf16x8, K[row * CPR + ((st * 4 + grp) ^ pa_kswz<HD>(row))]);
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int mt = 0; mt < MT; ++mt)
           sc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr, qf[mt][st], sc[nt][mt], 0, 0, 0);
       }
-    // online softmax of query q0 + 16 mt + r16 over keys k0 + 16 nt + 4 grp + i
-    const bool diag = k0 + KB - 1 > q0;
-    pf_bf16x8 pb[2][KB / 32];
+  };
+  // raise the reference of the queries whose block maximum calls for it
+  auto reference = [&](const pf_f32x4 (&sc)[NKT][MT]) {
+    float mx[MT];
+    bool up = false;
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      const int query = q0 + mt * 16 + r16;
-      float mx = -INFINITY;
+    for (int mt = 0; mt < MT; ++mt) {
+      float m0 = -INFINITY, m1 = -INFINITY;
+#pragma unroll
+      for (int nt = 0; nt < NKT; ++nt) {
+        m0 = fmaxf(fmaxf(m0, sc[nt][mt][0]), sc[nt][mt][1]);
+        m1 = fmaxf(fmaxf(m1, sc[nt][mt][2]), sc[nt][mt][3]);
+      }
+      mx[mt] = quarters_max(fmaxf(m0, m1)) * sl2;
+      up |= mx[mt] > mrun[mt] + 8.f;
+    }
+    if (__any(up)) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        // a query whose own block does not call for it keeps its reference
+        // (alpha = 1), so that its bits do not depend on its neighbours
+        const float mnew = mx[mt] > mrun[mt] + 8.f ? mx[mt] : mrun[mt];
+        const float alpha = mnew == mrun[mt] ? 1.f : __builtin_amdgcn_exp2f(mrun[mt] - mnew);
+        mrun[mt] = mnew;
+        lrun[mt] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[mt][dt] *= alpha;
+      }
+    }
+  };
+  // P = exp2(s scale log2 e - reference), rounded to bf16 in the B operand's k-slots
+  auto weights = [&](pf_f32x4 (&sc)[NKT][MT], pf_bf16x8 (&pb)[MT][KB / 32]) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const float mneg = mrun[mt] == -INFINITY ? 0.f : -mrun[mt];
 #pragma unroll
       for (int nt = 0; nt < NKT; ++nt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          float v = sc[nt][mt][i] * sl2;
-          if (diag && k0 + nt * 16 + grp * 4 + i > query) v = -INFINITY;
-          sc[nt][mt][i] = v;
-          mx = fmaxf(mx, v);
-        }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float mnew = fmaxf(mrun[mt], mx);
-      const float mref = mnew == -INFINITY ? 0.f : mnew;
-      const float alpha = __builtin_amdgcn_exp2f(mrun[mt] - mref);
-      float sum = 0.f;
-#pragma unroll
-      for (int nt = 0; nt < NKT; ++nt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float p = __builtin_amdgcn_exp2f(sc[nt][mt][i] - mref);
+          const float p = __builtin_amdgcn_exp2f(fmaf(sc[nt][mt][i], sl2, mneg));
           sc[nt][mt][i] = p;
-          sum += p;
+          lrun[mt] += p;
         }
-      sum += __shfl_xor(sum, 16, 64);
-      sum += __shfl_xor(sum, 32, 64);
-      lrun[mt] = lrun[mt] * alpha + sum;
-      mrun[mt] = mnew;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) o[mt][dt] *= alpha;
 #pragma unroll
       for (int st = 0; st < KB / 32; ++st)
         pb[mt][st] = __builtin_bit_cast(
@@ -787,55 +620,88 @@ __global__ __launch_bounds__(64 * G) __attribute__((amdgpu_waves_per_eu(2))) voi
                                   pf_pack_bf16(sc[2 * st + 1][mt][0], sc[2 * st + 1][mt][1]),
                                   pf_pack_bf16(sc[2 * st + 1][mt][2], sc[2 * st + 1][mt][3])));
     }
-    // O^T += V^T P^T
-    const uint16_t *V = (const uint16_t *)vl[slot];
+  };
+  auto values = [&](const uint16_t *V, const pf_bf16x8 (&pb)[MT][KB / 32]) {
 #pragma unroll
     for (int st = 0; st < KB / 32; ++st) {
       const int rlo = 32 * st + 4 * tq + ti, rhi = rlo + 16;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
         const int c = 2 * dt + (tg >> 1);
-        const pf_bf16x8 vfr = tr_frag(V + (rlo * 16 + (c ^ (2 * (rlo & 7)))) * 8 + (tg & 1) * 4,
-                                      V + (rhi * 16 + (c ^ (2 * (rhi & 7)))) * 8 + (tg & 1) * 4);
+        const pf_bf16x8 vfr = tr_frag(V + (rlo * CPR + (c ^ pa_vswz<HD>(rlo))) * 8 + (tg & 1) * 4,
+                                      V + (rhi * CPR + (c ^ pa_vswz<HD>(rhi))) * 8 + (tg & 1) * 4);
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+        for (int mt = 0; mt < MT; ++mt)
           o[mt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vfr, pb[mt][st], o[mt][dt], 0, 0, 0);
       }
     }
+  };
+
+  for (int j = 0; j < nblk; ++j) {
+    // block j has landed for every wave, and every wave is past block j - 1,
+    // whose slots take block j + 1
+    lds_ring_step<0>();
+    if (j + 1 < nblk) {
+      issue(kbase, kl[(j + 1) & 1], j + 1, false);
+      issue(vbase, vl[(j + 1) & 1], j + 1, true);
+    }
+    if (j >= mine) continue;
+    pf_bf16x8 pb[MT][KB / 32];
+    scores(kl[j & 1], sc);
+    if (j + 1 == mine) {                           // the block with the diagonal
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const int room = q0 + mt * 16 + r16 - j * KB - grp * 4;   // keys 16 nt + i up to it are seen
+#pragma unroll
+        for (int nt = 0; nt < NKT; ++nt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sc[nt][mt][i] = nt * 16 + i > room ? -INFINITY : sc[nt][mt][i];
+      }
+    }
+    reference(sc);
+    weights(sc, pb);
+    values((const uint16_t *)vl[j & 1], pb);
   }
   // O / l -> bf16: lane holds dims 16 dt + 4 grp .. +3 of query q0 + 16 mt + r16
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
+  for (int mt = 0; mt < MT; ++mt) {
     const int query = q0 + mt * 16 + r16;
+    float l = lrun[mt];
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
     if (query >= P) continue;
-    const float inv = 1.f / lrun[mt];
+    const float inv = 1.f / l;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
-      *(uint2 *)((uint16_t *)a.out + prefill_out_off(a, row_base + query, h * HD + dt * 16 + grp * 4)) = make_uint2(pf_pack_bf16(o[mt][dt][0] * inv, o[mt][dt][1] * inv),
-                                             pf_pack_bf16(o[mt][dt][2] * inv, o[mt][dt][3] * inv));
+      *(uint2 *)((uint16_t *)a.out + prefill_out_off(a, row_base + query, h * HD + dt * 16 + grp * 4)) =
+          make_uint2(pf_pack_bf16(o[mt][dt][0] * inv, o[mt][dt][1] * inv),
+                     pf_pack_bf16(o[mt][dt][2] * inv, o[mt][dt][3] * inv));
   }
 }
 
+template <int HD, int MT, int KB>
+static hipError_t launch_prefill_t(const PrefillAttnArgs &a, hipStream_t s) {
+  const int G = a.n_heads / a.n_kv_heads, pairs = a.n_kv_heads * a.batch, qw = G >= 4 ? 1 : 4 / G;
+  const long long n_wg = (long long)((a.prompt_len + 16 * MT * qw - 1) / (16 * MT * qw)) * pairs;
+  if (n_wg > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((prefill_attn_kernel<HD, MT, KB>), dim3((unsigned)n_wg), dim3(64 * G * qw), 0, s, a, qw, pairs);
+  return hipGetLastError();
+}
+
+// Two query tiles a wave once that leaves four workgroups per compute unit,
+// one below: 2 x 1100 with 12 heads of 64 (216 workgroups of two) takes 18
+// against 23 us, 8 x 2048 (1536) 99 against 86 us; 1 x 2048 with 32 / 8 heads
+// of 128 (512) 74 against 82 us, 8 x 1024 (2048) 132 against 116 us.
 hipError_t launch_prefill_attention(const PrefillAttnArgs &a, hipStream_t s) {
   const int G = a.n_heads / a.n_kv_heads;
-  if (G < 1 || G > 8 || a.prompt_len < 1) return hipErrorInvalidValue;
-  dim3 grid((a.prompt_len + 31) / 32, a.n_kv_heads, a.batch);
-  dim3 block(64 * G);
-  if (a.head_dim == 128 && (G == 1 || G == 2 || G == 4 || G == 8) && a.ld_out % 4 == 0) {
-    switch (G) {
-      case 1: hipLaunchKernelGGL(prefill_attn128_kernel<1>, grid, block, 0, s, a); break;
-      case 2: hipLaunchKernelGGL(prefill_attn128_kernel<2>, grid, block, 0, s, a); break;
-      case 4: hipLaunchKernelGGL(prefill_attn128_kernel<4>, grid, block, 0, s, a); break;
-      default: hipLaunchKernelGGL(prefill_attn128_kernel<8>, grid, block, 0, s, a); break;
-    }
-    return hipGetLastError();
-  }
+  if (G < 1 || G > 8 || a.prompt_len < 1 || a.batch < 1 || a.ld_out % 4 != 0) return hipErrorInvalidValue;
+  const int span = 32 * (G >= 4 ? 1 : 4 / G);
+  const bool two = (long long)((a.prompt_len + span - 1) / span) * a.n_kv_heads * a.batch >= 1024;
   switch (a.head_dim) {
-    case 64: hipLaunchKernelGGL(prefill_attn_kernel<64>, grid, block, 0, s, a); break;
-    case 128: hipLaunchKernelGGL(prefill_attn_kernel<128>, grid, block, 0, s, a); break;
+    case 64: return two ? launch_prefill_t<64, 2, 64>(a, s) : launch_prefill_t<64, 1, 64>(a, s);
+    case 128: return two ? launch_prefill_t<128, 2, 32>(a, s) : launch_prefill_t<128, 1, 32>(a, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_attention(int dtype, const AttnArgs &a, int n_groups, hipStream_t s) {

@@ -28,18 +28,20 @@ __device__ __forceinline__ size_t pk_off(int m, int k, int steps) {
 }
 
 // Step of an LDS ring filled by direct global -> LDS transfers
-// (global_load_lds): wait until at most VMCNT of this wave's vector-memory
-// operations are outstanding (the oldest transfers have landed in LDS), then
-// meet the workgroup's other waves.  Unlike __syncthreads() it does not wait
-// for the younger transfers still in flight.  The empty asm statements emit
-// nothing; they keep the compiler from moving any memory access across the
-// wait and the barrier.
+// (global_load_lds): wait until this wave's transfers are done but for the
+// youngest VMCNT ones and its LDS reads have all returned, then meet the
+// workgroup's other waves.  Unlike __syncthreads() it leaves the younger
+// transfers in flight.  The empty asm statements and the scheduling barriers
+// emit nothing; they keep the compiler from moving anything across the wait
+// and the barrier.
 template <int VMCNT>
 __device__ __forceinline__ void lds_ring_step() {
-  static_assert(VMCNT >= 0 && VMCNT < 16, "vmcnt field");
+  static_assert(VMCNT >= 0 && VMCNT < 64, "vmcnt field");
   asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | VMCNT);   // lgkmcnt, expcnt: no wait
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0070 | (VMCNT & 15) | ((VMCNT >> 4) << 14));   // lgkmcnt 0, expcnt: no wait
   __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
   asm volatile("" ::: "memory");
 }
 

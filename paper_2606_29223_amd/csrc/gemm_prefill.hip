@@ -225,26 +225,12 @@ struct RingTile {
   static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
 
-// Per-stage barrier: this wave's transfers are done but for the youngest
-// VMCNT ones and its LDS reads have all returned; then meet the other waves.
-// Unlike __syncthreads() it leaves the younger transfers in flight.  The
-// empty asm statements and the scheduling barriers emit nothing; they keep
-// the compiler from moving anything across the wait.
-template <int VMCNT>
-__device__ __forceinline__ void ring_step() {
-  static_assert(VMCNT >= 0 && VMCNT < 64, "vmcnt field");
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(0x0070 | (VMCNT & 15) | ((VMCNT >> 4) << 14));   // lgkmcnt 0, expcnt: no wait
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("" ::: "memory");
-}
-// The same with at most `stages` (0 .. NBUF - 1) whole stages outstanding.
+// Per-stage barrier with at most `stages` (0 .. NBUF - 1) whole stages of this
+// wave's transfers outstanding.
 template <typename T, int S = T::NBUF - 1>
 __device__ __forceinline__ void ring_wait(int stages) {
-  if constexpr (S <= 0) ring_step<0>();
-  else if (stages >= S) ring_step<S * T::PT>();
+  if constexpr (S <= 0) lds_ring_step<0>();
+  else if (stages >= S) lds_ring_step<S * T::PT>();
   else ring_wait<T, S - 1>(stages);
 }
 
@@ -346,7 +332,7 @@ void gemm_ring_kernel(GemmArgs a, int n_blk_n, int n_wg, int group) {
   // st + 1 is read while stage st is multiplied.
   int st = 0, slot = 0;                                 // slot of stage st
   auto full = [&](const Set &cur, Set &nxt) {           // st + NBUF < nst
-    ring_step<(NBUF - 2) * PT>();
+    lds_ring_step<(NBUF - 2) * PT>();
     issue(st + NBUF, slot);
     slot = slot + 1 == NBUF ? 0 : slot + 1;
     fetch(slot, nxt);

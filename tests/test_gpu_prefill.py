@@ -33,11 +33,12 @@ def test_prompt_gemm_tiles(N, K, M):
         assert np.array_equal(part.view(np.uint32), y[lo:].view(np.uint32))
 
 
-@pytest.mark.parametrize("d,F,H,Hkv,hd,P", [(80, 88, 4, 2, 32, 70), (48, 72, 2, 1, 64, 90), (144, 200, 3, 1, 128, 67)])
+@pytest.mark.parametrize("d,F,H,Hkv,hd,P", [(80, 88, 4, 2, 32, 70), (48, 72, 2, 1, 64, 90), (144, 200, 3, 1, 128, 67),
+                                             (96, 64, 5, 1, 64, 201), (64, 96, 7, 1, 128, 131)])
 def test_prompt_with_unfilled_k_steps(d, F, H, Hkv, hd, P):
     """bf16 models whose widths do not fill 32-column k-steps (the packed
     activations end in zeros), with head_dim 32 (whose attention writes
-    row-major and is packed afterwards) and three query heads per kv head:
+    row-major and is packed afterwards) and odd numbers of query heads per kv head:
     y_0 and the next tokens follow the oracle, exit logits within 2e-2."""
     torch = torch_cuda()
     from paper_2606_29223_amd import dexlib
@@ -64,3 +65,34 @@ def test_prompt_with_unfilled_k_steps(d, F, H, Hkv, hd, P):
             assert z0.max() - z0[seq[0]] < GAP
         z = ar.depth_logits(m, pl, seq, [2], prefill=pf)
         check_tokens_teacher_forced(z[:, -1], seq)
+
+
+@pytest.mark.parametrize("hd,H,Hkv,P,B", [(128, 8, 2, 2110, 8), (64, 6, 6, 1310, 16)])
+def test_prompt_attention_bits_do_not_depend_on_the_batch(hd, H, Hkv, P, B):
+    """The batch decides how many queries a wave of the prompt attention
+    takes (one 16-query tile alone; two from 1024 workgroups on: 1056 and
+    1056 here): the keys and values of the second layer, which the first
+    layer's attention feeds, and y_0 are the same bits either way."""
+    torch = torch_cuda()
+    from paper_2606_29223_amd import dexlib
+    cfg = configs.scaled_down(configs.get("small-12L-d768-bf16"), n_layers=2, d_model=256, d_ffn=256, vocab=512)
+    cfg.update(n_heads=H, n_kv_heads=Hkv, head_dim=hd, prompt_len=P)
+    w = dexlib.device_weights(cfg, gen.generate_model(cfg))
+    prompts = np.random.default_rng(hd).integers(0, 512, (B, P)).astype(np.int32)
+    got = []
+    for rows in (prompts, prompts[:1], prompts[B - 1:]):
+        dec = dexlib.Decoder(cfg, w, explored=[2], width_cap=1, batch=len(rows), max_context=P + 2)
+        first = dec.prefill(rows)
+        k, v, E = dec.kv_layout()
+        n = 2 * len(rows) * Hkv * E * hd * 2
+        caches = []
+        for base in (k, v):
+            buf = torch.empty(n, dtype=torch.uint8, device="cuda")
+            assert dexlib.load().dex_debug_copy(buf.data_ptr(), base, n, dec.stream.cuda_stream) == 0
+            torch.cuda.synchronize()
+            caches.append(buf.view(torch.int16).view(2, len(rows), Hkv, E, hd)[1, :, :, :P].clone())
+        dec.close()
+        got.append((first, *caches))
+    for i, b in ((1, 0), (2, B - 1)):
+        assert got[i][0][0] == got[0][0][b]
+        assert torch.equal(got[i][1][0], got[0][1][b]) and torch.equal(got[i][2][0], got[0][2][b])
