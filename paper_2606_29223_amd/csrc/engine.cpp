@@ -1042,7 +1042,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   A((void **)&rsc, M * 4);
   if (!mfma_prefill) A((void **)&apart, chunk * per_row);
   const size_t n_groups_total = (size_t)B * ((P + grp_rows - 1) / grp_rows);
-  const size_t tab_ints = M * 8 + n_groups_total * 4 + 6 * B + 64;
+  const size_t tab_ints = M * 8 + n_groups_total * 4 + 8 * B + 64;
   A((void **)&tab, tab_ints * 4);
   auto cleanup = [&]() {
     dfree(ctx, h); dfree(ctx, part); dfree(ctx, xb); dfree(ctx, q); dfree(ctx, att); dfree(ctx, act);
@@ -1057,7 +1057,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   int *g_row0 = t_zero + M, *g_nrows = g_row0 + n_groups_total, *g_seq = g_nrows + n_groups_total;
   int *g_rel = g_seq + n_groups_total;
   int *ex_src = g_rel + n_groups_total, *ex_zero = ex_src + B, *ex_cidx = ex_zero + B;
-  int *ex_seq = ex_cidx + B, *ex_pos = ex_seq + B;
+  int *ex_seq = ex_cidx + B, *ex_pos = ex_seq + B, *ex_one = ex_pos + B, *ex_nc = ex_one + B;
   for (int s = 0; s < B; ++s)
     for (int p = 0; p < P; ++p) {
       const size_t r = (size_t)s * P + p;
@@ -1087,6 +1087,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   }
   for (int s = 0; s < B; ++s) {
     ex_src[s] = s * P + P - 1; ex_zero[s] = 0; ex_cidx[s] = 0; ex_seq[s] = s; ex_pos[s] = P - 1;
+    ex_one[s] = 1; ex_nc[s] = P;
   }
   HIPCHK(hipMemcpyAsync(tab, host.data(), tab_ints * 4, hipMemcpyHostToDevice, ctx->stream));
   const int *d_seq = tab, *d_pos = tab + M, *d_entry = d_pos + M, *d_tok = d_entry + M, *d_nc = d_tok + M,
@@ -1094,7 +1095,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   const int *d_g0 = d_zero + M, *d_gn = d_g0 + n_groups_total, *d_gs = d_gn + n_groups_total;
   const int *d_grel = d_gs + n_groups_total;
   const int *d_exsrc = d_grel + n_groups_total, *d_exzero = d_exsrc + B;
-  const int *d_exseq = d_exzero + 2 * B, *d_expos = d_exseq + B;
+  const int *d_exseq = d_exzero + 2 * B, *d_expos = d_exseq + B, *d_exone = d_expos + B, *d_exnc = d_exone + B;
 
   // a packed k-step that the columns do not fill ends in zeros
   if (xb_cols > (size_t)d) HIPCHK(hipMemsetAsync(xb, 0, Mp * xb_cols * es, ctx->stream));
@@ -1118,19 +1119,28 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
     a.pk_steps = epi == EPI_SWIGLU ? ctx->ns_F : ctx->ns_d;
     return launch_gemm_tiled(epi, a, ctx->stream);
   };
+  // Nothing reads the last layer's output but the exit head, at the last
+  // position: there the other positions need their keys and values only (an
+  // eighth of the layer's work at 32 / 8 heads and d_ffn 3.5 d), and the last
+  // ones run the layer as decode rows.
+  const int last_layer = ctx->L - 1;
   for (int l = 0; l < ctx->L; ++l) {
+    if (l == last_layer && P == 1) break;            // every row is a last row
     const float alpha = ctx->rscale * (float)(l + 1) / (float)ctx->L;
     {
+      const int q_cols = l == last_layer ? 0 : H * hd;   // the packed tiles hold q, then k, then v
       GemmArgs a{};
-      a.wp = ctx->p_qkv[l]; a.nsteps_w = ctx->ns_d;
-      a.N = (H + 2 * ctx->Hkv) * hd; a.K = d; a.x = xb; a.ldx = d; a.M = (int)M;
+      a.wp = (const char *)ctx->p_qkv[l] + (l == last_layer ? (size_t)H * hd / 16 * ctx->ns_d * 1024 : 0);
+      a.nsteps_w = ctx->ns_d;
+      a.N = q_cols + 2 * ctx->Hkv * hd; a.K = d; a.x = xb; a.ldx = d; a.M = (int)M;
       a.part = part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d; a.eps = ctx->eps;
       a.out = q; a.ld_out = H * hd;
       a.kc = (char *)ctx->kc + l * layer_kv; a.vc = (char *)ctx->vc + l * layer_kv;
-      a.kv_entries = ctx->E; a.n_heads = H; a.n_kv_heads = ctx->Hkv; a.head_dim = hd;
+      a.kv_entries = ctx->E; a.n_heads = q_cols / hd; a.n_kv_heads = ctx->Hkv; a.head_dim = hd;
       a.row_seq = d_seq; a.row_pos = d_pos; a.row_entry = d_entry; a.rope = ctx->rope;
       HIPCHK(prefill_gemm(EPI_QKV, a));
     }
+    if (l == last_layer) break;
     if (mfma_prefill) {
       PrefillAttnArgs a{};
       a.q = q; a.ldq = H * hd;
@@ -1177,17 +1187,31 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
       HIPCHK(prefill_gemm(EPI_SWIGLU, a));
     }
     {
-      const bool last = l == ctx->L - 1;
       GemmArgs a{};
       a.wp = ctx->p_down[l]; a.nsteps_w = ctx->ns_F; a.N = d; a.K = ctx->F; a.x = act; a.ldx = ctx->F; a.M = (int)M;
-      a.h = h; a.ld_h = d; a.alpha = alpha;
-      a.g_next = last ? nullptr : (const float *)LW(ctx, l + 1, DEX_P_ATTN_NORM);
-      a.xb = last ? nullptr : xb; a.part_out = part; a.n_part_out = ctx->n_part;
+      a.h = h; a.ld_h = d; a.alpha = alpha; a.g_next = (const float *)LW(ctx, l + 1, DEX_P_ATTN_NORM);
+      a.xb = xb; a.part_out = part; a.n_part_out = ctx->n_part;
       HIPCHK(prefill_gemm(EPI_RESID, a));
     }
   }
+  {
+    PrepArgs p{};
+    p.M = B; p.d = d; p.n_part = ctx->n_part; p.embed_rows = 0; p.row_src = d_exsrc; p.bnd_h = h; p.bnd_part = part;
+    p.g = (const float *)LW(ctx, last_layer, DEX_P_ATTN_NORM); p.h = ctx->h_w; p.part = ctx->part_w; p.xb = ctx->xb_w;
+    HIPCHK(launch_prep(ctx->dtype, p, ctx->stream));
+    StageTables t{};
+    t.seq = d_exseq; t.pos = d_expos; t.entry = d_expos; t.nc = d_exnc; t.chain_off = d_exzero; t.chain = d_zero;
+    t.g_row0 = d_exseq; t.g_nrows = d_exone; t.g_seq = d_exseq; t.g_nc = d_exnc;
+    t.n_groups = B; t.n_splits = jmax;
+    const bool timing = ctx->timing;
+    ctx->timing = false;                             // the kernel times are those of rounds
+    const dex_status ls = run_layers(ctx, ctx->stream, last_layer, last_layer, B, t, ctx->h_w, ctx->part_w, ctx->xb_w,
+                                     ctx->q_w, ctx->att_w, ctx->act_w, ctx->attn_part, ctx->jmax, false, nullptr);
+    ctx->timing = timing;
+    if (ls != DEX_OK) { cleanup(); return ls; }
+  }
   // y_0: final-depth exit head at the last prompt position of every sequence
-  dex_status es2 = run_exit(ctx, B, d_exsrc, h, part, d_exzero, d_exzero, nullptr, nullptr, d_exseq, d_expos, nullptr,
+  dex_status es2 = run_exit(ctx, B, d_exseq, ctx->h_w, ctx->part_w, d_exzero, d_exzero, nullptr, nullptr, d_exseq, d_expos, nullptr,
                             nullptr);
   if (es2 != DEX_OK) { cleanup(); return fail(ctx, es2); }
   HIPCHK(hipMemcpyAsync(ctx->res_host, ctx->u_dev, B * 4, hipMemcpyDeviceToHost, ctx->stream));
