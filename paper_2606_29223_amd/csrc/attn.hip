@@ -332,7 +332,10 @@ __global__ __launch_bounds__(64 * CMB_WAVES) void combine_kernel(CombineArgs a) 
   }
   __syncthreads();
   if (s != 0 || !dok) return;
-  T *out = (T *)a.out + (size_t)r * a.ld_out + h * HD + d0;
+  // a lane's dimensions share 16 bytes in every layout
+  const int pk = a.row_pk != nullptr ? a.row_pk[r] : a.row0 + r, rm = a.row_pk != nullptr ? pk < 0 : a.rm;
+  T *out = (T *)a.out + (a.out_steps > 0 ? act_off<T>(a.row_pk != nullptr && rm ? ~pk : pk, h * HD + d0, a.out_steps, rm)
+                                         : (size_t)r * a.ld_out + h * HD + d0);
 #pragma unroll
   for (int q = 0; q < DPL; ++q) {
     float v = red[0][dl + q];
@@ -673,7 +676,7 @@ void prefill_attn_kernel(PrefillAttnArgs a, int QW, int n_pairs) {
     const float inv = 1.f / l;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
-      *(uint2 *)((uint16_t *)a.out + prefill_out_off(a, row_base + query, h * HD + dt * 16 + grp * 4)) =
+      *(uint2 *)((uint16_t *)a.out + pk_off<bf16>((int)row_base + query, h * HD + dt * 16 + grp * 4, a.out_steps)) =
           make_uint2(pf_pack_bf16(o[mt][dt][0] * inv, o[mt][dt][1] * inv),
                      pf_pack_bf16(o[mt][dt][2] * inv, o[mt][dt][3] * inv));
   }
@@ -694,7 +697,7 @@ static hipError_t launch_prefill_t(const PrefillAttnArgs &a, hipStream_t s) {
 // of 128 (512) 74 against 82 us, 8 x 1024 (2048) 132 against 116 us.
 hipError_t launch_prefill_attention(const PrefillAttnArgs &a, hipStream_t s) {
   const int G = a.n_heads / a.n_kv_heads;
-  if (G < 1 || G > 8 || a.prompt_len < 1 || a.batch < 1 || a.ld_out % 4 != 0) return hipErrorInvalidValue;
+  if (G < 1 || G > 8 || a.prompt_len < 1 || a.batch < 1 || a.out_steps < 1) return hipErrorInvalidValue;
   const int span = 32 * (G >= 4 ? 1 : 4 / G);
   const bool two = (long long)((a.prompt_len + span - 1) / span) * a.n_kv_heads * a.batch >= 1024;
   switch (a.head_dim) {

@@ -20,11 +20,29 @@ __device__ __forceinline__ int qkv_col(int tile, int r16, int hd) {
 typedef uint16_t bf16;
 
 // Element offset of (row m, column k) in the packed block layout of `steps`
-// k-steps per 16-row block (bf16): block (m / 16, k / 32) is 1 KB, one
-// matrix-core fragment in lane order -- 16 bytes of row m % 16, k group
-// (k % 32) / 8 at lane 16 (k % 32) / 8 + m % 16.
-__device__ __forceinline__ size_t pk_off(int m, int k, int steps) {
-  return ((size_t)(m >> 4) * steps + (k >> 5)) * 512 + ((k & 31) >> 3) * 128 + (m & 15) * 8 + (k & 7);
+// k-steps per 16-row block: block (m / 16, k-step) is 1 KB, one matrix-core
+// fragment in lane order -- with EPB elements in 16 bytes and 4 EPB columns a
+// k-step, 16 bytes of row m % 16, column group (k % 4 EPB) / EPB at lane
+// 16 group + m % 16.  Weights and every activation that a GEMM reads are laid
+// out so: a fragment is then 1 KB of consecutive bytes, where 16 row-major
+// rows are sixteen 64-byte pieces that cost the vector L1 an access per lane
+// (64 against 18 per instruction, counted at 64 rows).
+template <typename T>
+__host__ __device__ __forceinline__ size_t pk_off(int m, int k, int steps) {
+  constexpr int EPB = 16 / (int)sizeof(T), KSTEP = 4 * EPB;
+  return ((size_t)(m >> 4) * steps + k / KSTEP) * (16 * KSTEP) + (k % KSTEP) / EPB * (16 * EPB) + (m & 15) * EPB +
+         k % EPB;
+}
+
+// The same element in an activation buffer of either layout: a few rows (rm)
+// lie row-major in the same blocks' bytes, rows of `steps` k-steps.  One or
+// two rows of a fragment are a sixteenth or an eighth of its lanes, and in
+// lane order 64 bytes of a row lie 256 bytes apart (one row: QKV 11.2 against
+// 11.7 us, down 19.7 against 19.9; equal at four, 22.1 against 20.1 at eight).
+template <typename T>
+__host__ __device__ __forceinline__ size_t act_off(int m, int k, int steps, int rm) {
+  constexpr int KSTEP = 64 / (int)sizeof(T);
+  return rm ? (size_t)m * steps * KSTEP + k : pk_off<T>(m, k, steps);
 }
 
 // Step of an LDS ring filled by direct global -> LDS transfers
@@ -84,8 +102,9 @@ struct GemmArgs {
   int nsteps_w;
   int N;          // output columns (SWIGLU: d_ffn)
   int K;
-  const void *x;  // activations [M][ldx]
-  int ldx;
+  const void *x;  // activations [M][K], packed (pk_off, nsteps_w k-steps)
+  int row0;       // row 0's row in x, xb and act
+  int rm;         // x, xb and act hold their rows row-major (act_off)
   int M;
   // RMSNorm scale from sum-of-squares partials (nullable): per row
   // 1/sqrt(sum(part[m][0..n_part)) * inv_d + eps).
@@ -109,18 +128,15 @@ struct GemmArgs {
   int ld_h;
   float alpha;
   const float *g_next;        // gain of the next RMSNorm (nullable)
-  void *xb;                   // next-norm input g*h (T) [M][ld_h] (nullable)
+  void *xb;                   // next-norm input g*h (T), packed with pk_steps (nullable)
   float *part_out;            // [M][n_part_out]
   int n_part_out;
   const int *row_bnd;         // nullable: write h/partials to boundary storage instead
   float *bnd_h, *bnd_part;
   const float *bias;          // RESID (nullable): h += alpha * (y + bias); BIAS_SILU: SiLU(y + bias)
-  // SWIGLU
-  void *act;                  // [M][ld_act] (T)
-  int ld_act;
-  // Prompt GEMMs (launch_gemm_tiled): x, xb and act are in the packed block
-  // layout (pk_off): x with nsteps_w k-steps, the output with pk_steps
-  int pk_steps;
+  // SWIGLU / BIAS_SILU
+  void *act;                  // [M][N] (T), packed with pk_steps
+  int pk_steps;               // k-steps of the packed output (xb or act)
   // LOGITS
   const int *mask_tok;        // [M][mask_stride]
   const int *mask_n;          // [M]
@@ -163,8 +179,11 @@ struct CombineArgs {
   const float *stat;
   const int *row_pos;
   int jmax, n_heads, head_dim;
-  void *out;                  // [R][H*hd] (T)
-  int ld_out;
+  void *out;                  // [R][H*hd] (T): an activation buffer of out_steps k-steps,
+  int ld_out;                 // or rows ld_out apart where out_steps is 0
+  int out_steps;
+  int row0, rm;               // row r's row and layout there, or from row_pk[r] where set:
+  const int *row_pk;          // the row, or ~row for a row-major one
 };
 
 // Grouped launches.  The stages of a round are independent and, taken in
@@ -186,6 +205,7 @@ struct GemmSeg {
   const int *row_bnd;         // RESID: boundary rows of the segment (nullable)
   float alpha;                // RESID: the layer's residual scale
   int r0, M;                  // rows [r0, r0 + M) of the launch's buffers
+  int p0, rm;                 // row0 and rm of its activations (see GemmArgs)
 };
 struct GemmSegs {
   int n;
@@ -200,7 +220,8 @@ __host__ __device__ inline void gemm_seg_view(GemmArgs &a, const GemmSeg &s) {
   const size_t r = (size_t)s.r0;
   a.wp = s.wp;
   a.M = s.M;
-  a.x = (const T *)a.x + r * a.ldx;
+  a.row0 = s.p0;
+  a.rm = s.rm;
   if (a.part != nullptr) a.part += r * a.n_part;
   if constexpr (EPI == EPI_QKV) {
     a.out += r * a.ld_out;
@@ -213,11 +234,9 @@ __host__ __device__ inline void gemm_seg_view(GemmArgs &a, const GemmSeg &s) {
     a.h += r * a.ld_h;
     a.alpha = s.alpha;
     a.g_next = s.g_next;
-    a.xb = s.g_next != nullptr ? (void *)((T *)a.xb + r * a.ld_h) : nullptr;
+    if (s.g_next == nullptr) a.xb = nullptr;
     a.part_out += r * a.n_part_out;
     a.row_bnd = s.row_bnd;
-  } else {
-    a.act = (T *)a.act + r * a.ld_act;
   }
 }
 
@@ -242,16 +261,10 @@ struct PrefillAttnArgs {
   const void *kc, *vc;        // this layer's cache base
   int kv_entries, n_kv_heads, n_heads, head_dim, batch, prompt_len;
   float scale;
-  void *out;                  // [batch * prompt_len][ld_out] (bf16), or
-  int ld_out;
-  int out_steps;              // > 0: in the packed block layout with that many k-steps
+  void *out;                  // [batch * prompt_len] rows (bf16), packed
+  int out_steps;              // with this many k-steps
 };
 hipError_t launch_prefill_attention(const PrefillAttnArgs &a, hipStream_t s);
-
-// Element offset of (row, column) of a prompt attention's output.
-__device__ __forceinline__ size_t prefill_out_off(const PrefillAttnArgs &a, size_t row, int col) {
-  return a.out_steps > 0 ? pk_off((int)row, col, a.out_steps) : row * a.ld_out + col;
-}
 
 // Weight packing.  mode 0: rows in order; 1: QKV, the three segments w0/w1/w2
 // concatenated with each tile holding RoPE partner dimensions (i, i + hd/2)
@@ -269,9 +282,8 @@ hipError_t launch_pack(int dtype, const PackArgs &a, hipStream_t s);
 // Launchers (return the HIP status of the launch).
 hipError_t launch_gemm(int dtype, int epi, const GemmArgs &a, int m_blocks, hipStream_t s);
 // Prompt-prefill GEMM (bf16, M-tiled) with the QKV / RESID / SWIGLU / PLAIN
-// epilogues.  x is in the packed block layout (zeros in the columns past K up
-// to the k-step), and so are the xb and act it writes; N a multiple of 16
-// except for SWIGLU, no boundary rows (gemm_tiled_supported);
+// epilogues.  x ends in zeros past K up to the k-step; N a multiple of 16
+// except for SWIGLU, no boundary rows, row0 0 (gemm_tiled_supported);
 // launch_gemm_tiled returns hipErrorInvalidValue otherwise.  A normed GEMM
 // takes its row scales from row_rsc.
 bool gemm_tiled_supported(int epi, const GemmArgs &a);
@@ -303,8 +315,10 @@ struct PrepArgs {
   int seg_end[MAX_SEGS];
   const float *seg_g[MAX_SEGS];
   float *h, *part;            // [M][d], [M][n_part]
-  void *xb;                   // [M][d] (T)
-  int xb_steps;               // > 0: xb in the packed block layout (bf16) with that many k-steps
+  void *xb;                   // [M][d] (T), an activation buffer of xb_steps k-steps
+  int xb_steps;
+  int row0, rm;               // row m's row and layout there, or row_pk[m] where set (as CombineArgs)
+  const int *row_pk;
   const int *row_out;         // nullable: write h/part to row_out[m] instead of m
 };
 hipError_t launch_prep(int dtype, const PrepArgs &a, hipStream_t s);

@@ -374,11 +374,17 @@ struct StageTables {
 
 double wbytes(const dex_ctx *ctx, double elems) { return elems * ctx->es; }
 
+// Up to this many rows of a stage (of the exit head) keep their GEMM inputs
+// row-major (act_off).
+constexpr int kRowMajorRows = 2;
+
+// p0: the first row's row in xb, att and act
 dex_status run_layers(dex_ctx *ctx, hipStream_t st, int first_layer, int last_layer, int M, const StageTables &t,
-                      float *h, float *part, void *xb, float *q, void *att, void *act, float *apart,
+                      float *h, float *part, void *xb, float *q, void *att, void *act, int p0, float *apart,
                       int jmax, bool to_boundary, const int *bnd_rows) {
   const int d = ctx->d, H = ctx->H, Hkv = ctx->Hkv, hd = ctx->hd, F = ctx->F;
   const size_t layer_kv = (size_t)ctx->B * Hkv * ctx->E * hd * ctx->es;
+  const int rm = M <= kRowMajorRows;
   for (int l = first_layer; l <= last_layer; ++l) {
     const float alpha = ctx->rscale * (float)(l + 1) / (float)ctx->L;
     // QKV
@@ -386,7 +392,7 @@ dex_status run_layers(dex_ctx *ctx, hipStream_t st, int first_layer, int last_la
       GemmArgs a{};
       a.wp = ctx->p_qkv[l]; a.nsteps_w = ctx->ns_d;
       a.N = (H + 2 * Hkv) * hd; a.K = d;
-      a.x = xb; a.ldx = d; a.M = M;
+      a.x = xb; a.row0 = p0; a.rm = rm; a.M = M;
       a.part = part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d; a.eps = ctx->eps;
       a.out = q; a.ld_out = H * hd;
       a.kc = (char *)ctx->kc + l * layer_kv; a.vc = (char *)ctx->vc + l * layer_kv;
@@ -413,7 +419,7 @@ dex_status run_layers(dex_ctx *ctx, hipStream_t st, int first_layer, int last_la
       CombineArgs c{};
       c.part = apart; c.stat = split_stats(apart, M, H, jmax, hd);
       c.row_pos = t.pos; c.jmax = jmax; c.n_heads = H; c.head_dim = hd;
-      c.out = att; c.ld_out = H * hd;
+      c.out = att; c.out_steps = ctx->ns_hhd; c.row0 = p0; c.rm = rm;
       TimedLaunch tl(ctx, 2, 0.0);
       HIPCHK(launch_combine(ctx->dtype, c, M, st));
     }
@@ -421,7 +427,7 @@ dex_status run_layers(dex_ctx *ctx, hipStream_t st, int first_layer, int last_la
     {
       GemmArgs a{};
       a.wp = ctx->p_o[l]; a.nsteps_w = ctx->ns_hhd; a.N = d; a.K = H * hd;
-      a.x = att; a.ldx = H * hd; a.M = M;
+      a.x = att; a.row0 = p0; a.rm = rm; a.M = M; a.pk_steps = ctx->ns_d;
       a.h = h; a.ld_h = d; a.alpha = alpha;
       a.g_next = (const float *)LW(ctx, l, DEX_P_FFN_NORM); a.xb = xb;
       a.part_out = part; a.n_part_out = ctx->n_part;
@@ -433,9 +439,9 @@ dex_status run_layers(dex_ctx *ctx, hipStream_t st, int first_layer, int last_la
       GemmArgs a{};
       a.wp = ctx->p_gu[l]; a.nsteps_w = ctx->ns_d;
       a.N = F; a.K = d;
-      a.x = xb; a.ldx = d; a.M = M;
+      a.x = xb; a.row0 = p0; a.rm = rm; a.M = M;
       a.part = part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d; a.eps = ctx->eps;
-      a.act = act; a.ld_act = F;
+      a.act = act; a.pk_steps = ctx->ns_F;
       TimedLaunch tl(ctx, 4, wbytes(ctx, 2.0 * F * d + (double)M * d + (double)M * F));
       HIPCHK(launch_gemm(ctx->dtype, EPI_SWIGLU, a, 1, st));
     }
@@ -444,7 +450,7 @@ dex_status run_layers(dex_ctx *ctx, hipStream_t st, int first_layer, int last_la
       const bool last = (l == last_layer);
       GemmArgs a{};
       a.wp = ctx->p_down[l]; a.nsteps_w = ctx->ns_F; a.N = d; a.K = F;
-      a.x = act; a.ldx = F; a.M = M;
+      a.x = act; a.row0 = p0; a.rm = rm; a.M = M; a.pk_steps = ctx->ns_d;
       a.h = h; a.ld_h = d; a.alpha = alpha;
       a.g_next = last ? nullptr : (const float *)LW(ctx, l + 1, DEX_P_ATTN_NORM);
       a.xb = last ? nullptr : xb;
@@ -461,14 +467,14 @@ dex_status run_layers(dex_ctx *ctx, hipStream_t st, int first_layer, int last_la
 
 // Rows [r0, r0 + M) of the exit buffers from their source states, with the
 // next norm's input g * h.
-dex_status exit_prep(dex_ctx *ctx, int r0, int M, const int *row_src, const float *src_h, const float *src_part,
+dex_status exit_prep(dex_ctx *ctx, int rm, int r0, int M, const int *row_src, const float *src_h, const float *src_part,
                      const float *g) {
   if (M <= 0) return DEX_OK;
   PrepArgs p{};
   p.M = M; p.d = ctx->d; p.n_part = ctx->n_part; p.embed_rows = 0;
   p.row_src = row_src + r0; p.bnd_h = src_h; p.bnd_part = src_part; p.g = g;
   p.h = ctx->ex_h + (size_t)r0 * ctx->d; p.part = ctx->ex_part + (size_t)r0 * ctx->n_part;
-  p.xb = (char *)ctx->ex_xb + (size_t)r0 * ctx->d * ctx->es;
+  p.xb = ctx->ex_xb; p.xb_steps = ctx->ns_d; p.row0 = r0; p.rm = rm;
   TimedLaunch tl(ctx, 7, 0.0);
   HIPCHK(launch_prep(ctx->dtype, p, ctx->stream));
   return DEX_OK;
@@ -477,24 +483,24 @@ dex_status exit_prep(dex_ctx *ctx, int r0, int M, const int *row_src, const floa
 // Inducing adapter of non-final depth k on exit rows [r0, r0 + M), whose
 // states and g_k * h are in the exit buffers: h <- h + alpha (W2 silu(W1
 // RMSNorm(h; g_k) + b1) + b2), then the final norm's input and partials.
-dex_status exit_adapter(dex_ctx *ctx, int k, int r0, int M) {
+dex_status exit_adapter(dex_ctx *ctx, int rm, int k, int r0, int M) {
   if (M <= 0) return DEX_OK;
   const int d = ctx->d, m = ctx->ad_m;
-  void *xb = (char *)ctx->ex_xb + (size_t)r0 * d * ctx->es;
+  void *xb = ctx->ex_xb;
   float *part = ctx->ex_part + (size_t)r0 * ctx->n_part;
-  void *act = (char *)ctx->ad_act + (size_t)r0 * m * ctx->es;
+  void *act = ctx->ad_act;
   {
     GemmArgs a{};
     a.wp = ctx->p_ad1[k]; a.nsteps_w = ctx->ns_d; a.N = m; a.K = d;
-    a.x = xb; a.ldx = d; a.M = M; a.part = part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d; a.eps = ctx->eps;
-    a.act = act; a.ld_act = m; a.bias = ctx->ad_b1[k];
+    a.x = xb; a.row0 = r0; a.rm = rm; a.M = M; a.part = part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d; a.eps = ctx->eps;
+    a.act = act; a.pk_steps = ctx->ns_m; a.bias = ctx->ad_b1[k];
     TimedLaunch tl(ctx, 7, 0.0);
     HIPCHK(launch_gemm(ctx->dtype, EPI_BIAS_SILU, a, 1, ctx->stream));
   }
   {
     GemmArgs a{};
     a.wp = ctx->p_ad2[k]; a.nsteps_w = ctx->ns_m; a.N = d; a.K = m;
-    a.x = act; a.ldx = m; a.M = M;
+    a.x = act; a.row0 = r0; a.rm = rm; a.M = M; a.pk_steps = ctx->ns_d;
     a.h = ctx->ex_h + (size_t)r0 * d; a.ld_h = d; a.alpha = ctx->ad_alpha[k]; a.bias = ctx->ad_b2[k];
     a.g_next = ctx->final_norm; a.xb = xb; a.part_out = part; a.n_part_out = ctx->n_part;
     TimedLaunch tl(ctx, 7, 0.0);
@@ -510,25 +516,26 @@ dex_status run_exit(dex_ctx *ctx, int M, const int *row_src, const float *src_h,
                     const int *mask_n, const int *mask_tok, const int *cand_idx, int *cand, const int *row_seq,
                     const int *row_pos, const int *stage_r0, const int *row_commit) {
   const hipStream_t st = ctx->stream;
+  const int rm = M <= kRowMajorRows;
   if (ctx->ad_m > 0 && stage_r0 != nullptr) {
     const int N = ctx->N;
     for (int k = 0; k + 1 < N; ++k) {
       const int b0 = stage_r0[k], nb = stage_r0[k + 1] - b0;
-      dex_status s1 = exit_prep(ctx, b0, nb, row_src, src_h, src_part, ctx->ad_norm[k]);
-      if (s1 == DEX_OK) s1 = exit_adapter(ctx, k, b0, nb);
+      dex_status s1 = exit_prep(ctx, rm, b0, nb, row_src, src_h, src_part, ctx->ad_norm[k]);
+      if (s1 == DEX_OK) s1 = exit_adapter(ctx, rm, k, b0, nb);
       if (s1 != DEX_OK) return s1;
     }
-    dex_status s2 = exit_prep(ctx, stage_r0[N - 1], M - stage_r0[N - 1], row_src, src_h, src_part, ctx->final_norm);
+    dex_status s2 = exit_prep(ctx, rm, stage_r0[N - 1], M - stage_r0[N - 1], row_src, src_h, src_part, ctx->final_norm);
     if (s2 != DEX_OK) return s2;
   } else {
-    dex_status s2 = exit_prep(ctx, 0, M, row_src, src_h, src_part, ctx->final_norm);
+    dex_status s2 = exit_prep(ctx, rm, 0, M, row_src, src_h, src_part, ctx->final_norm);
     if (s2 != DEX_OK) return s2;
   }
   const int n_tiles = (ctx->V + 15) / 16;
   {
     GemmArgs a{};
     a.wp = ctx->p_lm; a.nsteps_w = ctx->ns_d; a.N = ctx->V; a.K = ctx->d;
-    a.x = ctx->ex_xb; a.ldx = ctx->d; a.M = M;
+    a.x = ctx->ex_xb; a.rm = rm; a.M = M;
     a.part = ctx->ex_part; a.n_part = ctx->n_part; a.inv_d = 1.0f / ctx->d; a.eps = ctx->eps;
     a.mask_n = mask_n; a.mask_tok = mask_tok; a.mask_stride = ctx->N;
     a.logits_tap = ctx->logits_tap; a.amax = ctx->amax; a.n_tiles = n_tiles;
@@ -833,6 +840,11 @@ dex_status dex_create(const dex_model *m, const dex_config *c, dex_ctx **out) {
   ctx->E = ctx->max_ctx + 2 * ctx->S;
   ctx->n_part = ctx->d / 16;
   ctx->jmax = (ctx->max_ctx + ATT_SPLIT - 1) / ATT_SPLIT;
+  const int kstep = ctx->dtype == DEX_BF16 ? 32 : 16;
+  ctx->ns_d = (ctx->d + kstep - 1) / kstep;
+  ctx->ns_hhd = (ctx->H * ctx->hd + kstep - 1) / kstep;
+  ctx->ns_F = (ctx->F + kstep - 1) / kstep;
+  ctx->ns_m = (c->adapter_dim + kstep - 1) / kstep;
 
   dex_status st = DEX_OK;
   auto A = [&](void **p, size_t bytes) {
@@ -849,15 +861,18 @@ dex_status dex_create(const dex_model *m, const dex_config *c, dex_ctx **out) {
   A((void **)&ctx->cand, slots_total * N * 4);
   A((void **)&ctx->h_w, R * d * 4);
   A((void **)&ctx->part_w, R * ctx->n_part * 4);
-  A(&ctx->xb_w, R * d * es);
+  // packed activations: a round's stages start on 16-row blocks of their own
+  // (blocks are shared cache lines, and stages run on different streams)
+  const size_t blocks = R / 16 + N, blk = 1024;
+  A(&ctx->xb_w, blocks * ctx->ns_d * blk);
   A((void **)&ctx->q_w, R * ctx->H * ctx->hd * 4);
-  A(&ctx->att_w, R * ctx->H * ctx->hd * es);
-  A(&ctx->act_w, R * ctx->F * es);
+  A(&ctx->att_w, blocks * ctx->ns_hhd * blk);
+  A(&ctx->act_w, blocks * ctx->ns_F * blk);
   A((void **)&ctx->attn_part, R * ctx->H * ctx->jmax * (ctx->hd + 2) * 4);
   A((void **)&ctx->ex_h, R * d * 4);
   A((void **)&ctx->ex_part, R * ctx->n_part * 4);
-  A(&ctx->ex_xb, R * d * es);
-  if (c->adapter_dim > 0) A(&ctx->ad_act, R * (size_t)c->adapter_dim * es);
+  A(&ctx->ex_xb, blocks * ctx->ns_d * blk);
+  if (c->adapter_dim > 0) A(&ctx->ad_act, blocks * ctx->ns_m * blk);
   A((void **)&ctx->amax, R * ((ctx->V + 15) / 16) * sizeof(float2));
   A((void **)&ctx->u_dev, (R + 2 * (size_t)ctx->B) * 4 + 256);
   A((void **)&ctx->job_dev, (size_t)(ctx->B * (ctx->S + 1)) * 6 * 4 + 256);
@@ -897,10 +912,6 @@ dex_status dex_create(const dex_model *m, const dex_config *c, dex_ctx **out) {
   }
   // packed weights: every wave load of the skinny GEMMs reads 1 KB contiguously
   {
-    const int kstep = ctx->dtype == DEX_BF16 ? 32 : 16;
-    ctx->ns_d = (ctx->d + kstep - 1) / kstep;
-    ctx->ns_hhd = (ctx->H * ctx->hd + kstep - 1) / kstep;
-    ctx->ns_F = (ctx->F + kstep - 1) / kstep;
     const int H = ctx->H, Hkv = ctx->Hkv, hd = ctx->hd, dd = ctx->d, F = ctx->F;
     auto pack = [&](void **dst, const void *w0, const void *w1, const void *w2, int n0, int n1, int n2, int N,
                     int K, int mode) -> dex_status {
@@ -928,7 +939,6 @@ dex_status dex_create(const dex_model *m, const dex_config *c, dex_ctx **out) {
     if (ps == DEX_OK && c->adapter_dim > 0) {
       const int am = c->adapter_dim;
       ctx->ad_m = am;
-      ctx->ns_m = (am + kstep - 1) / kstep;
       ctx->p_ad1.assign(N - 1, nullptr); ctx->p_ad2.assign(N - 1, nullptr);
       ctx->ad_norm.assign(N - 1, nullptr); ctx->ad_b1.assign(N - 1, nullptr); ctx->ad_b2.assign(N - 1, nullptr);
       ctx->ad_alpha.assign(N - 1, 0.f);
@@ -1010,12 +1020,9 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   const int G = H / ctx->Hkv;
   // matrix-core prompt attention for bf16 caches; the split kernel otherwise
   const bool mfma_prefill = ctx->dtype == DEX_BF16 && (hd == 64 || hd == 128) && G <= 8;
-  // many prompt rows: the M-tiled GEMMs (bf16) on packed activations; the
-  // decode GEMMs on row-major ones otherwise
+  // many prompt rows: the M-tiled GEMMs (bf16); the decode GEMMs otherwise
   const bool tiled = ctx->dtype == DEX_BF16 && M > 64;
-  const bool pack_att = tiled && !mfma_prefill;   // the split kernels write row-major
-  const size_t Mp = tiled ? (M + 15) / 16 * 16 : M;
-  const size_t xb_cols = tiled ? (size_t)ctx->ns_d * 32 : d, act_cols = tiled ? (size_t)ctx->ns_F * 32 : ctx->F;
+  const size_t blocks = (M + 15) / 16;       // of packed rows
   const int grp_rows = std::max(1, ATT_MAX_PAIRS / G);
   const int jmax = (P + ATT_SPLIT - 1) / ATT_SPLIT;
   // attention row chunk bounded so its split partials stay below ~512 MiB
@@ -1026,7 +1033,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   if (chunk == 0) chunk = grp_rows;
 
   float *h = nullptr, *part = nullptr, *q = nullptr, *apart = nullptr, *rsc = nullptr;
-  void *xb = nullptr, *att = nullptr, *att_rows = nullptr, *act = nullptr;
+  void *xb = nullptr, *att = nullptr, *act = nullptr;
   int *tab = nullptr;
   dex_status st = DEX_OK;
   auto A = [&](void **p, size_t bytes) {
@@ -1034,11 +1041,10 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   };
   A((void **)&h, M * d * 4);
   A((void **)&part, M * ctx->n_part * 4);
-  A(&xb, Mp * xb_cols * es);
+  A(&xb, blocks * ctx->ns_d * 1024);
   A((void **)&q, M * H * hd * 4);
-  A(&att, Mp * H * hd * es);
-  if (pack_att) A(&att_rows, M * H * hd * es);
-  A(&act, Mp * act_cols * es);
+  A(&att, blocks * ctx->ns_hhd * 1024);
+  A(&act, blocks * ctx->ns_F * 1024);
   A((void **)&rsc, M * 4);
   if (!mfma_prefill) A((void **)&apart, chunk * per_row);
   const size_t n_groups_total = (size_t)B * ((P + grp_rows - 1) / grp_rows);
@@ -1046,7 +1052,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   A((void **)&tab, tab_ints * 4);
   auto cleanup = [&]() {
     dfree(ctx, h); dfree(ctx, part); dfree(ctx, xb); dfree(ctx, q); dfree(ctx, att); dfree(ctx, act);
-    dfree(ctx, apart); dfree(ctx, tab); dfree(ctx, rsc); dfree(ctx, att_rows);
+    dfree(ctx, apart); dfree(ctx, tab); dfree(ctx, rsc);
   };
   if (st != DEX_OK) { cleanup(); return st; }   // nothing changed yet: not poisoned
 
@@ -1097,26 +1103,26 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   const int *d_exsrc = d_grel + n_groups_total, *d_exzero = d_exsrc + B;
   const int *d_exseq = d_exzero + 2 * B, *d_expos = d_exseq + B, *d_exone = d_expos + B, *d_exnc = d_exone + B;
 
-  // a packed k-step that the columns do not fill ends in zeros
-  if (xb_cols > (size_t)d) HIPCHK(hipMemsetAsync(xb, 0, Mp * xb_cols * es, ctx->stream));
-  if (act_cols > (size_t)ctx->F) HIPCHK(hipMemsetAsync(act, 0, Mp * act_cols * es, ctx->stream));
+  // for the tiled GEMMs a packed k-step that the columns do not fill ends in zeros
+  if (tiled && d % 32 != 0) HIPCHK(hipMemsetAsync(xb, 0, blocks * ctx->ns_d * 1024, ctx->stream));
+  if (tiled && ctx->F % 32 != 0) HIPCHK(hipMemsetAsync(act, 0, blocks * ctx->ns_F * 1024, ctx->stream));
   {
     PrepArgs p{};
     p.M = (int)M; p.d = d; p.n_part = ctx->n_part; p.embed_rows = (int)M; p.row_tok = d_tok; p.embed = ctx->embed;
     p.g = (const float *)LW(ctx, 0, DEX_P_ATTN_NORM); p.h = h; p.part = part; p.xb = xb;
-    p.xb_steps = tiled ? ctx->ns_d : 0;
+    p.xb_steps = ctx->ns_d;
     HIPCHK(launch_prep(ctx->dtype, p, ctx->stream));
   }
   const size_t layer_kv = (size_t)B * ctx->Hkv * ctx->E * hd * es;
   // a normed tiled GEMM first gets its row scales
   auto prefill_gemm = [&](int epi, GemmArgs a) -> hipError_t {
+    a.pk_steps = epi == EPI_SWIGLU ? ctx->ns_F : ctx->ns_d;
     if (!tiled) return launch_gemm(ctx->dtype, epi, a, 1, ctx->stream);
     if (a.part != nullptr) {
       a.row_rsc = rsc;
       const hipError_t e = launch_row_scale(a.part, a.n_part, a.M, a.inv_d, a.eps, rsc, ctx->stream);
       if (e != hipSuccess) return e;
     }
-    a.pk_steps = epi == EPI_SWIGLU ? ctx->ns_F : ctx->ns_d;
     return launch_gemm_tiled(epi, a, ctx->stream);
   };
   // Nothing reads the last layer's output but the exit head, at the last
@@ -1132,7 +1138,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
       GemmArgs a{};
       a.wp = (const char *)ctx->p_qkv[l] + (l == last_layer ? (size_t)H * hd / 16 * ctx->ns_d * 1024 : 0);
       a.nsteps_w = ctx->ns_d;
-      a.N = q_cols + 2 * ctx->Hkv * hd; a.K = d; a.x = xb; a.ldx = d; a.M = (int)M;
+      a.N = q_cols + 2 * ctx->Hkv * hd; a.K = d; a.x = xb; a.M = (int)M;
       a.part = part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d; a.eps = ctx->eps;
       a.out = q; a.ld_out = H * hd;
       a.kc = (char *)ctx->kc + l * layer_kv; a.vc = (char *)ctx->vc + l * layer_kv;
@@ -1146,8 +1152,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
       a.q = q; a.ldq = H * hd;
       a.kc = (char *)ctx->kc + l * layer_kv; a.vc = (char *)ctx->vc + l * layer_kv;
       a.kv_entries = ctx->E; a.n_kv_heads = ctx->Hkv; a.n_heads = H; a.head_dim = hd; a.batch = B;
-      a.prompt_len = P; a.scale = 1.0f / std::sqrt((float)hd); a.out = att; a.ld_out = H * hd;
-      a.out_steps = tiled ? ctx->ns_hhd : 0;
+      a.prompt_len = P; a.scale = 1.0f / std::sqrt((float)hd); a.out = att; a.out_steps = ctx->ns_hhd;
       HIPCHK(launch_prefill_attention(a, ctx->stream));
     } else for (const auto &ch : chunks) {
       const int g_first = ch[0], g_cnt = ch[1], c0 = ch[2], cn = ch[3];
@@ -1164,17 +1169,12 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
       CombineArgs cb{};
       cb.part = apart; cb.stat = split_stats(apart, cn, H, jmax, hd);
       cb.row_pos = d_pos + c0; cb.jmax = jmax; cb.n_heads = H; cb.head_dim = hd;
-      cb.out = (char *)(pack_att ? att_rows : att) + (size_t)c0 * H * hd * es; cb.ld_out = H * hd;
+      cb.out = att; cb.out_steps = ctx->ns_hhd; cb.row0 = c0;
       HIPCHK(launch_combine(ctx->dtype, cb, cn, ctx->stream));
-    }
-    if (pack_att) {                          // rows as the "weight rows" of a plain pack
-      PackArgs pa{};
-      pa.w0 = att_rows; pa.n0 = pa.N = (int)M; pa.K = H * hd; pa.mode = 0; pa.head_dim = hd; pa.out = att;
-      HIPCHK(launch_pack(ctx->dtype, pa, ctx->stream));
     }
     {
       GemmArgs a{};
-      a.wp = ctx->p_o[l]; a.nsteps_w = ctx->ns_hhd; a.N = d; a.K = H * hd; a.x = att; a.ldx = H * hd; a.M = (int)M;
+      a.wp = ctx->p_o[l]; a.nsteps_w = ctx->ns_hhd; a.N = d; a.K = H * hd; a.x = att; a.M = (int)M;
       a.h = h; a.ld_h = d; a.alpha = alpha; a.g_next = (const float *)LW(ctx, l, DEX_P_FFN_NORM); a.xb = xb;
       a.part_out = part; a.n_part_out = ctx->n_part;
       HIPCHK(prefill_gemm(EPI_RESID, a));
@@ -1182,13 +1182,13 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
     {
       GemmArgs a{};
       a.wp = ctx->p_gu[l]; a.nsteps_w = ctx->ns_d; a.N = ctx->F; a.K = d;
-      a.x = xb; a.ldx = d; a.M = (int)M; a.part = part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d;
-      a.eps = ctx->eps; a.act = act; a.ld_act = ctx->F;
+      a.x = xb; a.M = (int)M; a.part = part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d;
+      a.eps = ctx->eps; a.act = act;
       HIPCHK(prefill_gemm(EPI_SWIGLU, a));
     }
     {
       GemmArgs a{};
-      a.wp = ctx->p_down[l]; a.nsteps_w = ctx->ns_F; a.N = d; a.K = ctx->F; a.x = act; a.ldx = ctx->F; a.M = (int)M;
+      a.wp = ctx->p_down[l]; a.nsteps_w = ctx->ns_F; a.N = d; a.K = ctx->F; a.x = act; a.M = (int)M;
       a.h = h; a.ld_h = d; a.alpha = alpha; a.g_next = (const float *)LW(ctx, l + 1, DEX_P_ATTN_NORM);
       a.xb = xb; a.part_out = part; a.n_part_out = ctx->n_part;
       HIPCHK(prefill_gemm(EPI_RESID, a));
@@ -1198,6 +1198,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
     PrepArgs p{};
     p.M = B; p.d = d; p.n_part = ctx->n_part; p.embed_rows = 0; p.row_src = d_exsrc; p.bnd_h = h; p.bnd_part = part;
     p.g = (const float *)LW(ctx, last_layer, DEX_P_ATTN_NORM); p.h = ctx->h_w; p.part = ctx->part_w; p.xb = ctx->xb_w;
+    p.xb_steps = ctx->ns_d; p.rm = B <= kRowMajorRows;
     HIPCHK(launch_prep(ctx->dtype, p, ctx->stream));
     StageTables t{};
     t.seq = d_exseq; t.pos = d_expos; t.entry = d_expos; t.nc = d_exnc; t.chain_off = d_exzero; t.chain = d_zero;
@@ -1206,7 +1207,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
     const bool timing = ctx->timing;
     ctx->timing = false;                             // the kernel times are those of rounds
     const dex_status ls = run_layers(ctx, ctx->stream, last_layer, last_layer, B, t, ctx->h_w, ctx->part_w, ctx->xb_w,
-                                     ctx->q_w, ctx->att_w, ctx->act_w, ctx->attn_part, ctx->jmax, false, nullptr);
+                                     ctx->q_w, ctx->att_w, ctx->act_w, 0, ctx->attn_part, ctx->jmax, false, nullptr);
     ctx->timing = timing;
     if (ls != DEX_OK) { cleanup(); return ls; }
   }
@@ -1293,7 +1294,8 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
   int *t_gn = t_g0 + R, *t_gs = t_gn + R;
   int *t_gnc = t_gs + R;                   // committed prefix length of each group's rows
   int *t_rcommit = t_gnc + R;              // [R] commit slot of a row completing its anchor, else -1
-  std::vector<int> stage_r0(N + 1, 0), stage_g0(N + 1, 0);
+  int *t_pk = t_rcommit + R;               // [R] activation row (row_pk): every stage starts on a 16-row block
+  std::vector<int> stage_r0(N + 1, 0), stage_g0(N + 1, 0), stage_p0(N, 0);
   int chain_used = 0, ngroups = 0;
   const int G = ctx->H / ctx->Hkv;
   const int grp_rows = std::max(1, ATT_MAX_PAIRS / G);
@@ -1322,6 +1324,12 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
     stage_r0[rw.stage + 1] = r + 1;
   }
   for (int k = 1; k <= N; ++k) stage_r0[k] = std::max(stage_r0[k], stage_r0[k - 1]);
+  for (int k = 0, p0 = 0; k < N; ++k) {
+    stage_p0[k] = p0;
+    const int n = stage_r0[k + 1] - stage_r0[k];
+    for (int i = 0; i < n; ++i) t_pk[stage_r0[k] + i] = n <= kRowMajorRows ? ~(p0 + i) : p0 + i;
+    p0 += (n + 15) / 16 * 16;
+  }
   // attention row groups per stage: consecutive rows of one sequence
   for (int k = 0; k < N; ++k) {
     stage_g0[k] = ngroups;
@@ -1349,7 +1357,7 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
       commit_seqs.push_back(si);
     }
   }
-  const size_t tab_ints = (size_t)(t_rcommit - T) + R;
+  const size_t tab_ints = (size_t)(t_pk - T) + R;
   if (tab_ints > ctx->tab_cap) return fail_mid_round(ctx, "row table overflow", DEX_E_CAPACITY);
   hipEvent_t *rt = ctx->round_timing ? ctx->rt_ev[ctx->rt_cur] : nullptr;
   if (rt) {
@@ -1426,7 +1434,7 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
       p.row_tok = t.tok; p.row_src = t.bnd; p.embed = ctx->embed; p.bnd_h = ctx->bnd_h; p.bnd_part = ctx->bnd_part;
       p.g = (const float *)LW(ctx, ls.front(), DEX_P_ATTN_NORM);
       p.h = ctx->h_w + (size_t)r0 * ctx->d; p.part = ctx->part_w + (size_t)r0 * ctx->n_part;
-      p.xb = (char *)ctx->xb_w + (size_t)r0 * ctx->d * ctx->es;
+      p.xb = ctx->xb_w; p.xb_steps = ctx->ns_d; p.row0 = stage_p0[k]; p.rm = M <= kRowMajorRows;
       TimedLaunch tl(ctx, 7, 0.0);
       HIPCHK(launch_prep(ctx->dtype, p, lst));
     }
@@ -1441,10 +1449,7 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
     if (ps != DEX_OK) return ps;
     return run_layers(ctx, lst, ls.front(), ls.back(), M, t, ctx->h_w + (size_t)r0 * ctx->d,
                       ctx->part_w + (size_t)r0 * ctx->n_part,
-                      (char *)ctx->xb_w + (size_t)r0 * ctx->d * ctx->es,
-                      ctx->q_w + (size_t)r0 * ctx->H * ctx->hd,
-                      (char *)ctx->att_w + (size_t)r0 * ctx->H * ctx->hd * ctx->es,
-                      (char *)ctx->act_w + (size_t)r0 * ctx->F * ctx->es,
+                      ctx->xb_w, ctx->q_w + (size_t)r0 * ctx->H * ctx->hd, ctx->att_w, ctx->act_w, stage_p0[k],
                       ctx->attn_part + (size_t)r0 * ctx->H * ctx->jmax * (ctx->hd + 2), ctx->jmax,
                       true, t.bnd);
   };
@@ -1484,7 +1489,7 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
       }
       p.g = p.seg_g[0];
       p.h = ctx->h_w + (size_t)ra * ctx->d; p.part = ctx->part_w + (size_t)ra * ctx->n_part;
-      p.xb = (char *)ctx->xb_w + (size_t)ra * ctx->d * ctx->es;
+      p.xb = ctx->xb_w; p.xb_steps = ctx->ns_d; p.row_pk = dptr(t_pk) + ra;
       TimedLaunch tl(ctx, 7, 0.0);
       HIPCHK(launch_prep(ctx->dtype, p, st));
     }
@@ -1507,12 +1512,14 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
       auto seg_rows = [&](GemmSeg &g, int i) {
         g.r0 = stage_r0[on[i]];
         g.M = stage_r0[on[i] + 1] - g.r0;
+        g.p0 = stage_p0[on[i]];
+        g.rm = g.M <= kRowMajorRows;
       };
       // QKV
       {
         GemmArgs a{};
         a.nsteps_w = ctx->ns_d; a.N = (H + 2 * Hkv) * hd; a.K = d;
-        a.x = ctx->xb_w; a.ldx = d;
+        a.x = ctx->xb_w;
         a.part = ctx->part_w; a.n_part = ctx->n_part; a.inv_d = 1.0f / d; a.eps = ctx->eps;
         a.out = ctx->q_w; a.ld_out = H * hd;
         a.kv_entries = ctx->E; a.n_heads = H; a.n_kv_heads = Hkv; a.head_dim = hd;
@@ -1566,7 +1573,7 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
         c.part = (char *)ctx->attn_part + ra * rec_row;
         c.stat = stat_all + (size_t)ra * H * jmax * 2;
         c.row_pos = dptr(t_pos) + ra; c.jmax = jmax; c.n_heads = H; c.head_dim = hd;
-        c.out = (char *)ctx->att_w + (size_t)ra * H * hd * ctx->es; c.ld_out = H * hd;
+        c.out = ctx->att_w; c.out_steps = ctx->ns_hhd; c.row_pk = dptr(t_pk) + ra;
         TimedLaunch tl(ctx, 2, 0.0);
         HIPCHK(launch_combine(ctx->dtype, c, rb - ra, st));
         i = e;
@@ -1575,8 +1582,8 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
       {
         GemmArgs a{};
         a.nsteps_w = ctx->ns_hhd; a.N = d; a.K = H * hd;
-        a.x = ctx->att_w; a.ldx = H * hd;
-        a.h = ctx->h_w; a.ld_h = d; a.xb = ctx->xb_w;
+        a.x = ctx->att_w;
+        a.h = ctx->h_w; a.ld_h = d; a.xb = ctx->xb_w; a.pk_steps = ctx->ns_d;
         a.part_out = ctx->part_w; a.n_part_out = ctx->n_part;
         double bytes = 0.0;
         for (int i = 0; i < n; ++i) {
@@ -1596,9 +1603,9 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
       {
         GemmArgs a{};
         a.nsteps_w = ctx->ns_d; a.N = F; a.K = d;
-        a.x = ctx->xb_w; a.ldx = d;
+        a.x = ctx->xb_w;
         a.part = ctx->part_w; a.n_part = ctx->n_part; a.inv_d = 1.0f / d; a.eps = ctx->eps;
-        a.act = ctx->act_w; a.ld_act = F;
+        a.act = ctx->act_w; a.pk_steps = ctx->ns_F;
         double bytes = 0.0;
         for (int i = 0; i < n; ++i) {
           GemmSeg &g = gs[i];
@@ -1614,8 +1621,8 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
       {
         GemmArgs a{};
         a.nsteps_w = ctx->ns_F; a.N = d; a.K = F;
-        a.x = ctx->act_w; a.ldx = F;
-        a.h = ctx->h_w; a.ld_h = d; a.xb = ctx->xb_w;
+        a.x = ctx->act_w;
+        a.h = ctx->h_w; a.ld_h = d; a.xb = ctx->xb_w; a.pk_steps = ctx->ns_d;
         a.part_out = ctx->part_w; a.n_part_out = ctx->n_part;
         a.bnd_h = ctx->bnd_h; a.bnd_part = ctx->bnd_part;
         double bytes = 0.0;
@@ -1961,23 +1968,24 @@ dex_status dex_debug_time_kernel(dex_ctx *ctx, int32_t cls, int32_t M, int32_t r
     const int l = rep % ctx->L;
     GemmArgs a{};
     a.M = M;
+    a.rm = M <= kRowMajorRows;
     int epi = EPI_RESID;
     if (cls == 3) {
-      a.wp = ctx->p_o[l]; a.nsteps_w = ctx->ns_hhd; a.N = d; a.K = H * hd; a.x = ctx->att_w; a.ldx = H * hd;
+      a.wp = ctx->p_o[l]; a.nsteps_w = ctx->ns_hhd; a.N = d; a.K = H * hd; a.x = ctx->att_w; a.pk_steps = ctx->ns_d;
       a.h = ctx->h_w; a.ld_h = d; a.alpha = 0.f; a.part_out = ctx->part_w; a.n_part_out = ctx->n_part;
       bytes = (double)ctx->es * ((double)d * H * hd + (double)M * H * hd + (double)M * d) + 8.0 * M * d;
     } else if (cls == 4) {
-      a.wp = ctx->p_gu[l]; a.nsteps_w = ctx->ns_d; a.N = F; a.K = d; a.x = ctx->xb_w; a.ldx = d;
+      a.wp = ctx->p_gu[l]; a.nsteps_w = ctx->ns_d; a.N = F; a.K = d; a.x = ctx->xb_w;
       a.part = ctx->part_w; a.n_part = ctx->n_part; a.inv_d = 1.0f / d; a.eps = ctx->eps;
-      a.act = ctx->act_w; a.ld_act = F;
+      a.act = ctx->act_w; a.pk_steps = ctx->ns_F;
       epi = EPI_SWIGLU;
       bytes = (double)ctx->es * (2.0 * F * d + (double)M * d + (double)M * F);
     } else if (cls == 5) {
-      a.wp = ctx->p_down[l]; a.nsteps_w = ctx->ns_F; a.N = d; a.K = F; a.x = ctx->act_w; a.ldx = F;
+      a.wp = ctx->p_down[l]; a.nsteps_w = ctx->ns_F; a.N = d; a.K = F; a.x = ctx->act_w; a.pk_steps = ctx->ns_d;
       a.h = ctx->h_w; a.ld_h = d; a.alpha = 0.f; a.part_out = ctx->part_w; a.n_part_out = ctx->n_part;
       bytes = (double)ctx->es * ((double)d * F + (double)M * F + (double)M * d) + 8.0 * M * d;
     } else {
-      a.wp = ctx->p_lm; a.nsteps_w = ctx->ns_d; a.N = ctx->V; a.K = d; a.x = ctx->ex_xb; a.ldx = d;
+      a.wp = ctx->p_lm; a.nsteps_w = ctx->ns_d; a.N = ctx->V; a.K = d; a.x = ctx->ex_xb;
       a.part = ctx->ex_part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d; a.eps = ctx->eps;
       a.mask_n = ctx->tab_dev; a.mask_tok = ctx->tab_dev; a.mask_stride = 0;
       a.amax = ctx->amax; a.n_tiles = (ctx->V + 15) / 16;
@@ -2006,20 +2014,20 @@ dex_status dex_debug_gemm(int32_t dtype, const void *W, int32_t N, int32_t K, co
   if (dtype != DEX_F32 && dtype != DEX_BF16) return DEX_E_INVAL;
   if (M > 64 && (dtype != DEX_BF16 || N % 16)) return DEX_E_INVAL;
   if (K % (dtype == DEX_BF16 ? 8 : 4)) return DEX_E_INVAL;
-  // the M-tiled kernel takes x in the packed layout too
-  const size_t wbytes_packed = packed_bytes(dtype, N, K, 0), xbytes = M > 64 ? packed_bytes(dtype, M, K, 0) : 0;
+  // the kernels take x in the packed layout too
+  const size_t wbytes_packed = packed_bytes(dtype, N, K, 0), xbytes = packed_bytes(dtype, M, K, 0);
   void *wp = nullptr;
   if (hipMalloc(&wp, wbytes_packed + xbytes) != hipSuccess) return DEX_E_NOMEM;
   PackArgs pa{};
   pa.w0 = W; pa.n0 = N; pa.N = N; pa.K = K; pa.mode = 0; pa.head_dim = 16; pa.out = wp;
   hipError_t e = launch_pack(dtype, pa, (hipStream_t)stream);
-  if (e == hipSuccess && M > 64) {
+  if (e == hipSuccess) {
     pa.w0 = x; pa.n0 = pa.N = M; pa.out = (char *)wp + wbytes_packed;
     e = launch_pack(dtype, pa, (hipStream_t)stream);
   }
   GemmArgs a{};
   a.wp = wp; a.nsteps_w = (K + (dtype == DEX_BF16 ? 32 : 16) - 1) / (dtype == DEX_BF16 ? 32 : 16);
-  a.N = N; a.K = K; a.x = M > 64 ? (const char *)wp + wbytes_packed : x; a.ldx = K; a.M = M; a.out = y; a.ld_out = N;
+  a.N = N; a.K = K; a.x = (const char *)wp + wbytes_packed; a.M = M; a.out = y; a.ld_out = N;
   if (e == hipSuccess)
     e = M > 64 ? launch_gemm_tiled(EPI_PLAIN, a, (hipStream_t)stream) : launch_gemm(dtype, EPI_PLAIN, a, 1, (hipStream_t)stream);
   if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);

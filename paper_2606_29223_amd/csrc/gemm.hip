@@ -6,7 +6,7 @@
 // a weight stream: one workgroup owns a 16-column tile of W (two tiles for
 // the gate/up pair), its eight waves split K by interleaved 16-byte steps,
 // and each wave issues 128-bit loads of W (A operand, 16 rows x 64 bytes per
-// instruction) and of x (B operand, from L2) into v_mfma_f32_16x16x32_bf16
+// instruction) and of x (B operand, from L2, in the same packed layout) into v_mfma_f32_16x16x32_bf16
 // (bf16) or v_mfma_f32_16x16x4_f32 (fp32) tiles.  Rows beyond M are zero.
 // The split-K partials meet in LDS and are summed in wave order, so a row's
 // result depends only on its own input: the same bits for any M, any
@@ -61,14 +61,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a) {
     wok[tw] = tile0 + tw < n_tiles;
     wbase[tw] = (const char *)a.wp + (size_t)(wok[tw] ? tile0 + tw : 0) * a.nsteps_w * NT * 1024 + lane * 16;
   }
-  // ---- this lane's activation rows (one per M block)
-  const T *xrow[MB];
+  // ---- this lane's activation rows (one per M block): packed like the
+  // weights, a few rows row-major
+  const int xstep = a.rm ? 64 : 1024;          // bytes from k-step to k-step
+  const char *xrow[MB];
   bool xok[MB];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
     const int m = m0 + mb * 16 + r16;
     xok[mb] = m < a.M;
-    xrow[mb] = (const T *)a.x + (size_t)(xok[mb] ? m : 0) * a.ldx;
+    xrow[mb] = (const char *)((const T *)a.x + act_off<T>(a.row0 + (xok[mb] ? m : 0), grp * EPB, a.nsteps_w, a.rm));
   }
 
   f32x4_t acc[NA][MB];
@@ -92,7 +94,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a) {
         for (int t = 0; t < NT; ++t)
           w[u][tw * NT + t].v = load16(wbase[tw] + ((size_t)s * NT + t) * 1024, s < nsteps && wok[tw]);
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) x[u][mb].v = load16_cached(xrow[mb] + k, kin && xok[mb]);
+      for (int mb = 0; mb < MB; ++mb) x[u][mb].v = load16_cached(xrow[mb] + (size_t)s * xstep, kin && xok[mb]);
     }
   };
   auto compute_chunk = [&](const F (&w)[U][NA], const F (&x)[U][MB]) {
@@ -194,7 +196,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a) {
       const float r = (a.part != nullptr) ? rs[ml] : 1.f;
       const float gt = vt[0][nl][ml] * r, up = vt[NT - 1][nl][ml] * r;
       const float sg = gt / (1.0f + expf(-gt));
-      ((T *)a.act)[(size_t)m * a.ld_act + n] = to_t<T>(sg * up);
+      ((T *)a.act)[act_off<T>(a.row0 + m, n, a.pk_steps, a.rm)] = to_t<T>(sg * up);
     }
   } else if constexpr (EPI == EPI_BIAS_SILU) {
     for (int e = threadIdx.x; e < 16 * Mloc; e += GEMM_THREADS) {
@@ -203,7 +205,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a) {
       if (n >= a.N) continue;
       const float r = (a.part != nullptr) ? rs[ml] : 1.f;
       const float u = vt[0][nl][ml] * r + a.bias[n];
-      ((T *)a.act)[(size_t)m * a.ld_act + n] = to_t<T>(u / (1.0f + expf(-u)));
+      ((T *)a.act)[act_off<T>(a.row0 + m, n, a.pk_steps, a.rm)] = to_t<T>(u / (1.0f + expf(-u)));
     }
   } else if constexpr (EPI == EPI_LOGITS) {
     __shared__ float z[16][16 * MB];
@@ -323,86 +325,80 @@ static void go(const GemmArgs &a, const GemmSegs *g, dim3 grid, hipStream_t s) {
   hipLaunchKernelGGL((gemm_kernel<T, EPI, MB, U, NTW>), grid, dim3(GEMM_THREADS), 0, s, a);
 }
 
-// Weight tiles per workgroup of a projection with 256 (O, down) or 384 (QKV)
-// tiles at up to 32 rows over nseg segments: every activation load feeds
-// NTW tiles, which pays from 5 rows on once the grid still fills the chip;
-// at 1-4 rows a grouped launch keeps one tile with a shallower prefetch
-// (measured per class, row count and segment count on the 32-layer d4096
-// model, lone QKV launches at 1-4 rows inside the decode step; 0: the
-// general table).
-static int proj_tiles_per_wg(int n_tiles, int M, int nseg) {
-  if (M > 32 || n_tiles < 256 || n_tiles > 384) return 0;
-  const bool qkv = n_tiles > 256;
-  if (nseg == 1) return qkv && M > 4 ? 2 : 0;
-  if (M <= 4) return 1;
-  if (nseg == 2) return qkv ? 4 : 2;
-  if (nseg <= 4) return qkv ? 2 : (nseg == 4 && M <= 8 ? 2 : 4);
-  return 4;
-}
-
 // The configuration for M rows (a grouped launch of nseg segments: its
-// largest segment's).
+// largest segment's): row blocks of 16 per workgroup, prefetch depth, weight
+// tiles per workgroup.  Every activation load feeds the workgroup's tiles,
+// so more rows call for more tiles, as long as the grid still covers the 256
+// compute units in whole rounds.  Measured per class, row count and segment
+// count on the 4096-wide, 14336-FFN shapes (back-to-back launches over
+// distinct weights; us): gate/up 1 / 8 / 16 / 32 / 64 rows 37.6 / 38.2 / 40.4
+// / 42.8 / 61.8, down 19.6 / 19.7 / 22.1 / 28.5 / 36.8, O 7.8 / 7.9 / 8.6 /
+// 10.5 / 12.9, QKV 11.5 / 12.2 / 13.4 / 16.7 / 21.8, LM head 40.0 / 40.9 /
+// 47.1 / 52.1 / 70.7 (with row-major activations at 64 rows 72.6, 48.7, 15.2,
+// 36.7 and 80.4).
 template <typename T, int EPI>
 static hipError_t launch_t(const GemmArgs &a, const GemmSegs *g, int M, int nseg, hipStream_t s) {
   const int n_tiles = (a.N + 15) / 16;
+  auto tiles = [&](int ntw) { return (unsigned)((n_tiles + ntw - 1) / ntw); };
+  const unsigned b32 = (unsigned)((M + 31) / 32), b64 = (unsigned)((M + 63) / 64);
   if constexpr (EPI == EPI_QKV || EPI == EPI_RESID) {
-    const int ntw = proj_tiles_per_wg(n_tiles, M, nseg);
-    if (ntw == 1) {
-      go<T, EPI, 1, 2, 1>(a, g, dim3(n_tiles, 1), s);
-      return hipGetLastError();
-    }
-    if (ntw > 0 && M <= 16) {
-      if (ntw == 4) go<T, EPI, 1, 2, 4>(a, g, dim3((n_tiles + 3) / 4, 1), s);
-      else if (nseg == 1) go<T, EPI, 1, 8, 2>(a, g, dim3((n_tiles + 1) / 2, 1), s);
-      else go<T, EPI, 1, 4, 2>(a, g, dim3((n_tiles + 1) / 2, 1), s);
-      return hipGetLastError();
-    }
-    if (ntw > 0) {
-      if (ntw == 4) go<T, EPI, 2, 2, 4>(a, g, dim3((n_tiles + 3) / 4, 1), s);
-      else if (EPI == EPI_QKV && nseg > 1) go<T, EPI, 2, 2, 2>(a, g, dim3((n_tiles + 1) / 2, 1), s);
-      else go<T, EPI, 2, 4, 2>(a, g, dim3((n_tiles + 1) / 2, 1), s);
+    // the projections of a 4096-wide layer (256 tiles: O, down; 384: QKV):
+    // alone, one tile per workgroup occupies the chip; grouped over segments
+    // or row blocks the grid has room for several
+    if (n_tiles >= 256 && n_tiles <= 512) {
+      constexpr bool qkv = EPI == EPI_QKV;
+      if (M <= 16) {
+        if (qkv && nseg > 1) go<T, EPI, 1, 2, 1>(a, g, dim3(tiles(1)), s);
+        else if (qkv && M <= 8) go<T, EPI, 1, 4, 1>(a, g, dim3(tiles(1)), s);
+        else if (!qkv && nseg == 1) go<T, EPI, 1, 8, 1>(a, g, dim3(tiles(1)), s);
+        else if (!qkv && M <= 8) go<T, EPI, 1, 4, 1>(a, g, dim3(tiles(1)), s);
+        else if (qkv || nseg == 2 || nseg == 4) go<T, EPI, 1, 4, 2>(a, g, dim3(tiles(2)), s);
+        else go<T, EPI, 1, 2, 4>(a, g, dim3(tiles(4)), s);
+      } else if (M <= 32) {
+        if (!qkv && nseg == 1) go<T, EPI, 2, 8, 1>(a, g, dim3(tiles(1)), s);
+        else if (qkv ? nseg == 1 : nseg == 2) go<T, EPI, 2, 4, 2>(a, g, dim3(tiles(2)), s);
+        else if (qkv && (nseg == 3 || nseg == 4)) go<T, EPI, 2, 2, 2>(a, g, dim3(tiles(2)), s);
+        else go<T, EPI, 2, 2, 4>(a, g, dim3(tiles(4)), s);
+      } else if (nseg == 1 && M <= 64) {
+        if (qkv) go<T, EPI, 2, 4, 4>(a, g, dim3(tiles(4), b32), s);
+        else go<T, EPI, 2, 4, 2>(a, g, dim3(tiles(2), b32), s);
+      } else if (!qkv && nseg * (int)b64 == 2) {
+        go<T, EPI, 4, 2, 2>(a, g, dim3(tiles(2), b64), s);
+      } else {
+        go<T, EPI, 4, 2, 4>(a, g, dim3(tiles(4), b64), s);
+      }
       return hipGetLastError();
     }
   }
   if (M <= 16) {
     // deeper prefetch when a workgroup per CU streams a long tile, shallower
-    // when many workgroups share each CU (measured on the 4096-wide layers);
-    // from 5 rows on, the wide matrices (gate/up, LM head) take two tiles per
-    // workgroup so that each activation load feeds two weight tiles
-    if (M > 4 && n_tiles > 512)
-      go<T, EPI, 1, 2, 2>(a, g, dim3((n_tiles + 1) / 2, 1), s);
-    else if (n_tiles <= 256) go<T, EPI, 1, 8, 1>(a, g, dim3(n_tiles, 1), s);
-    else if (n_tiles <= 1024) go<T, EPI, 1, 4, 1>(a, g, dim3(n_tiles, 1), s);
-    else go<T, EPI, 1, 2, 1>(a, g, dim3(n_tiles, 1), s);
-  } else {
-    // more rows: the wide matrices take several weight tiles per workgroup
-    // so that each activation load feeds them all -- four for the 2000-tile
-    // LM head and for gate/up up to 32 rows, two for gate/up beyond; the
-    // 256-tile projections take two tiles per workgroup and split the rows
-    // over a second grid row from 25 rows on (the same 256 workgroups, each
-    // activation load feeding two tiles); the 384-tile QKV keeps one tile
-    // per workgroup (measured per class at 17-64 rows); with 64-row blocks
-    // the reduction buffer takes most of the LDS
-    if (M <= 32) {
-      if constexpr (EPI == EPI_LOGITS || EPI == EPI_SWIGLU)
-        go<T, EPI, 2, 2, 4>(a, g, dim3((n_tiles + 3) / 4, 1), s);
-      else if (n_tiles <= 256 && M > 24)
-        go<T, EPI, 1, 8, 2>(a, g, dim3((n_tiles + 1) / 2, 2), s);
-      else if (n_tiles <= 256)
-        go<T, EPI, 2, 8, 1>(a, g, dim3(n_tiles, 1), s);
-      else
-        go<T, EPI, 2, 4, 1>(a, g, dim3(n_tiles, 1), s);
-    } else if (n_tiles <= 256 && EPI != EPI_LOGITS && EPI != EPI_SWIGLU) {
-      go<T, EPI, 2, 4, 2>(a, g, dim3((n_tiles + 1) / 2, (M + 31) / 32), s);
+    // when many workgroups share each CU; above 8 rows a lone wide launch
+    // takes two tiles per workgroup
+    if (M > 8 && nseg == 1 && n_tiles > 512) go<T, EPI, 1, 2, 2>(a, g, dim3(tiles(2)), s);
+    else if (n_tiles <= 256) go<T, EPI, 1, 8, 1>(a, g, dim3(tiles(1)), s);
+    else if (n_tiles <= 1024) go<T, EPI, 1, 4, 1>(a, g, dim3(tiles(1)), s);
+    else go<T, EPI, 1, 2, 1>(a, g, dim3(tiles(1)), s);
+  } else if constexpr (EPI == EPI_LOGITS || EPI == EPI_SWIGLU) {
+    // gate/up four tiles up to 32 rows, two beyond; the 2000-tile LM head
+    // eight, then four (with 64-row blocks the reduction buffer takes most
+    // of the LDS)
+    if (M <= 32 && EPI == EPI_LOGITS && n_tiles > 1024) {
+      if constexpr (EPI == EPI_LOGITS) go<T, EPI, 2, 2, 8>(a, g, dim3(tiles(8)), s);
+    } else if (M <= 32) {
+      go<T, EPI, 2, 2, 4>(a, g, dim3(tiles(4)), s);
+    } else if constexpr (EPI == EPI_LOGITS) {
+      go<T, EPI, 4, 2, 4>(a, g, dim3(tiles(4), b64), s);
     } else {
-      const unsigned mb = (unsigned)((M + 63) / 64);
-      if constexpr (EPI == EPI_LOGITS)
-        go<T, EPI, 4, 2, 4>(a, g, dim3((n_tiles + 3) / 4, mb), s);
-      else if constexpr (EPI == EPI_SWIGLU)
-        go<T, EPI, 4, 2, 2>(a, g, dim3((n_tiles + 1) / 2, mb), s);
-      else
-        go<T, EPI, 4, 4, 1>(a, g, dim3(n_tiles, mb), s);
+      go<T, EPI, 4, 2, 2>(a, g, dim3(tiles(2), b64), s);
     }
+  } else if (M <= 32) {
+    if (n_tiles <= 256 && M > 24) go<T, EPI, 1, 8, 2>(a, g, dim3(tiles(2), 2), s);
+    else if (n_tiles <= 256) go<T, EPI, 2, 8, 1>(a, g, dim3(tiles(1)), s);
+    else go<T, EPI, 2, 4, 1>(a, g, dim3(tiles(1)), s);
+  } else if (n_tiles <= 256) {
+    go<T, EPI, 2, 4, 2>(a, g, dim3(tiles(2), b32), s);
+  } else {
+    go<T, EPI, 4, 4, 1>(a, g, dim3(tiles(1), b64), s);
   }
   return hipGetLastError();
 }

@@ -100,7 +100,7 @@ __device__ __forceinline__ void epi_resid(const GemmArgs &a, int tile, int m0, i
     const float br = (a.bias != nullptr) ? a.alpha * (vt[nl][ml] + a.bias[n]) : a.alpha * vt[nl][ml];
     const float hn = hin[n] + br;
     hout[n] = hn;
-    if (a.xb != nullptr) ((T *)a.xb)[(size_t)m * a.ld_h + n] = to_t<T>(a.g_next[n] * hn);
+    if (a.xb != nullptr) ((T *)a.xb)[act_off<T>(a.row0 + m, n, a.pk_steps, a.rm)] = to_t<T>(a.g_next[n] * hn);
     sq[nl][ml] = hn * hn;
   }
   __syncthreads();

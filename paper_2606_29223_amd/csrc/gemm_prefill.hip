@@ -104,7 +104,7 @@ __device__ __forceinline__ void tb_epilogue(const GemmArgs &a, int tile, int m, 
       *(float4 *)hp = make_float4(hn[0], hn[1], hn[2], hn[3]);
       if (a.xb != nullptr) {
         const float *gn = a.g_next + n0;
-        *(uint2 *)((uint16_t *)a.xb + pk_off(m, n0, a.pk_steps)) =
+        *(uint2 *)((uint16_t *)a.xb + pk_off<bf16>(m, n0, a.pk_steps)) =
             tb_pack4(gn[0] * hn[0], gn[1] * hn[1], gn[2] * hn[2], gn[3] * hn[3]);
       }
     }
@@ -122,7 +122,7 @@ __device__ __forceinline__ void tb_epilogue(const GemmArgs &a, int tile, int m, 
         const float gt = acc[0][i] * rsc, up = acc[NT - 1][i] * rsc;
         o[i] = gt / (1.0f + expf(-gt)) * up;
       }
-      *(uint2 *)((uint16_t *)a.act + pk_off(m, tile * 16 + grp * 4, a.pk_steps)) = tb_pack4(o[0], o[1], o[2], o[3]);
+      *(uint2 *)((uint16_t *)a.act + pk_off<bf16>(m, tile * 16 + grp * 4, a.pk_steps)) = tb_pack4(o[0], o[1], o[2], o[3]);
     }
   }
 }
@@ -392,7 +392,7 @@ void gemm_ring_kernel(GemmArgs a, int n_blk_n, int n_wg, int group) {
 }  // namespace
 
 bool gemm_tiled_supported(int epi, const GemmArgs &a) {
-  if (a.M < 1 || a.N < 1 || a.nsteps_w < 1 || a.row_bnd != nullptr) return false;
+  if (a.M < 1 || a.N < 1 || a.nsteps_w < 1 || a.row_bnd != nullptr || a.row0 != 0 || a.rm) return false;
   if (a.part != nullptr && a.row_rsc == nullptr) return false;   // the row scales come precomputed
   if ((a.M + 127) / 128 > 65535) return false;
   switch (epi) {

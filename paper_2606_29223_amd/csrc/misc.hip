@@ -75,9 +75,9 @@ __global__ __launch_bounds__(PREP_THREADS) void prep_kernel(PrepArgs a) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) h[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
   if (a.xb != nullptr) {
-    const bool packed = sizeof(T) == 2 && a.xb_steps > 0;
-    uint4 *xb = (uint4 *)((T *)a.xb + (packed ? pk_off(mo, c0, a.xb_steps) : (size_t)mo * a.d + c0));
-    const int qs = packed ? 16 : 1;            // a packed row's next 8 columns lie 16 lanes on
+    const int pk = a.row_pk != nullptr ? a.row_pk[m] : a.row0 + mo, rm = a.row_pk != nullptr ? pk < 0 : a.rm;
+    uint4 *xb = (uint4 *)((T *)a.xb + act_off<T>(a.row_pk != nullptr && rm ? ~pk : pk, c0, a.xb_steps, rm));
+    const int qs = rm ? 1 : 16;                // packed, a row's next 16 bytes lie 16 lanes on
 #pragma unroll
     for (int q = 0; q < 16 / EPV; ++q) {
       uint32_t w[4];
