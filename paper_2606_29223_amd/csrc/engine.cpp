@@ -167,6 +167,11 @@ struct dex_ctx {
   int *job_dev = nullptr;
   // pinned host staging
   int *tab_host = nullptr, *res_host = nullptr, *job_host = nullptr;
+  // prompt scratch and its pinned row tables, kept between prompts
+  void *pf_dev = nullptr;
+  size_t pf_bytes = 0;
+  int *pf_host = nullptr;
+  size_t pf_ints = 0;
   // state
   std::vector<Seq> seqs;
   bool prefilled = false;
@@ -231,6 +236,42 @@ void dfree(dex_ctx *ctx, void *p) {
   auto it = std::find(ctx->allocs.begin(), ctx->allocs.end(), p);
   if (it != ctx->allocs.end()) ctx->allocs.erase(it);
   (void)hipFree(p);
+}
+
+// Prompt scratch of at least `bytes` on the device and `ints` pinned on the
+// host.  A context keeps it from prompt to prompt (allocating and freeing cost
+// about 0.1 ms of a 0.8 ms prompt) up to kPrefillKeep bytes, and frees what
+// is larger when the call is done.
+constexpr int kPrefillRows = 8192;
+constexpr size_t kPrefillKeep = 1ull << 30;
+dex_status prefill_room(dex_ctx *ctx, size_t bytes, size_t ints) {
+  if (ctx->pf_bytes < bytes) {
+    dfree(ctx, ctx->pf_dev);
+    ctx->pf_dev = nullptr;
+    ctx->pf_bytes = 0;
+    const dex_status st = dalloc(ctx, &ctx->pf_dev, bytes);
+    if (st != DEX_OK) return st;
+    ctx->pf_bytes = bytes;
+  }
+  if (ctx->pf_ints < ints) {
+    if (ctx->pf_host) (void)hipHostFree(ctx->pf_host);
+    ctx->pf_host = nullptr;
+    ctx->pf_ints = 0;
+    const hipError_t e = hipHostMalloc((void **)&ctx->pf_host, ints * 4);
+    if (e != hipSuccess) {
+      ctx->pf_host = nullptr;
+      ctx->err = std::string("hipHostMalloc of the prompt tables failed: ") + hipGetErrorString(e);
+      return DEX_E_NOMEM;
+    }
+    ctx->pf_ints = ints;
+  }
+  return DEX_OK;
+}
+void prefill_trim(dex_ctx *ctx) {
+  if (ctx->pf_bytes <= kPrefillKeep) return;
+  dfree(ctx, ctx->pf_dev);
+  ctx->pf_dev = nullptr;
+  ctx->pf_bytes = 0;
 }
 
 const void *LW(const dex_ctx *ctx, int l, int p) { return ctx->lw[(size_t)l * DEX_P_COUNT + p]; }
@@ -760,6 +801,7 @@ void dex_destroy(dex_ctx *ctx) {
   if (ctx->tab_host) (void)hipHostFree(ctx->tab_host);
   if (ctx->res_host) (void)hipHostFree(ctx->res_host);
   if (ctx->job_host) (void)hipHostFree(ctx->job_host);
+  if (ctx->pf_host) (void)hipHostFree(ctx->pf_host);
   for (auto e : ctx->ev_pool) (void)hipEventDestroy(e);
   for (size_t i = 0; i < ctx->lane_st.size(); ++i) {
     if (!ctx->lane_st[i] || ctx->lane_st[i] == ctx->stream) continue;
@@ -1022,97 +1064,88 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   const bool mfma_prefill = ctx->dtype == DEX_BF16 && (hd == 64 || hd == 128) && G <= 8;
   // many prompt rows: the M-tiled GEMMs (bf16); the decode GEMMs otherwise
   const bool tiled = ctx->dtype == DEX_BF16 && M > 64;
-  const size_t blocks = (M + 15) / 16;       // of packed rows
-  const int grp_rows = std::max(1, ATT_MAX_PAIRS / G);
+  // Whole sequences at a time, about kPrefillRows rows through all layers: the
+  // activations of 8192 rows of a 4096-wide layer (0.6 GB) stay near the
+  // 256 MB memory-side cache and the scratch stays small enough to keep,
+  // while the GEMMs still run whole rounds of tiles.  Sequences share nothing,
+  // and no kernel's row depends on the others of its launch.
+  const int n_part_calls = (B + std::max(1, kPrefillRows / P) - 1) / std::max(1, kPrefillRows / P);
+  const int seqs_per = (B + n_part_calls - 1) / n_part_calls;
+  const size_t rows = (size_t)seqs_per * P, blocks = (rows + 15) / 16;   // of a part; its packed row blocks
   const int jmax = (P + ATT_SPLIT - 1) / ATT_SPLIT;
+  // The split kernel runs a group's rows one after another (a wave per group,
+  // kv head and split): at most 64 (row, head) pairs, fewer while that leaves
+  // under 2048 waves (4 x 256 rows, 4 heads: 16 rows a group instead of 64,
+  // 204 -> 30 us).
+  const int grp_rows = std::max(1, std::min<int>(ATT_MAX_PAIRS / G, (int)std::min<size_t>(rows * ctx->Hkv * jmax / 2048, 64)));
+  const int grp_seq = (P + grp_rows - 1) / grp_rows;                     // groups of a sequence
   // attention row chunk bounded so its split partials stay below ~512 MiB
   const size_t per_row = (size_t)H * jmax * (hd + 2) * 4;
   size_t chunk = std::max<size_t>(grp_rows, (512ull << 20) / per_row);
-  chunk = std::min(chunk, M);
+  chunk = std::min(chunk, rows);
   chunk = (chunk / grp_rows) * grp_rows;
   if (chunk == 0) chunk = grp_rows;
 
-  float *h = nullptr, *part = nullptr, *q = nullptr, *apart = nullptr, *rsc = nullptr;
-  void *xb = nullptr, *att = nullptr, *act = nullptr;
-  int *tab = nullptr;
-  dex_status st = DEX_OK;
-  auto A = [&](void **p, size_t bytes) {
-    if (st == DEX_OK) st = dalloc(ctx, p, bytes);
+  // scratch: one allocation, kept by the context for the next prompt
+  size_t slab = 0;
+  auto room = [&](size_t bytes) {
+    const size_t at = slab;
+    slab += (bytes + 255) / 256 * 256;
+    return at;
   };
-  A((void **)&h, M * d * 4);
-  A((void **)&part, M * ctx->n_part * 4);
-  A(&xb, blocks * ctx->ns_d * 1024);
-  A((void **)&q, M * H * hd * 4);
-  A(&att, blocks * ctx->ns_hhd * 1024);
-  A(&act, blocks * ctx->ns_F * 1024);
-  A((void **)&rsc, M * 4);
-  if (!mfma_prefill) A((void **)&apart, chunk * per_row);
-  const size_t n_groups_total = (size_t)B * ((P + grp_rows - 1) / grp_rows);
-  const size_t tab_ints = M * 8 + n_groups_total * 4 + 8 * B + 64;
-  A((void **)&tab, tab_ints * 4);
-  auto cleanup = [&]() {
-    dfree(ctx, h); dfree(ctx, part); dfree(ctx, xb); dfree(ctx, q); dfree(ctx, att); dfree(ctx, act);
-    dfree(ctx, apart); dfree(ctx, tab); dfree(ctx, rsc);
-  };
-  if (st != DEX_OK) { cleanup(); return st; }   // nothing changed yet: not poisoned
+  const size_t n_groups = mfma_prefill ? 0 : (size_t)B * grp_seq;
+  const size_t tab_ints = 3 * M + 7 * (size_t)B + (mfma_prefill ? 0 : 2 * M + 3 * n_groups) + 16;
+  const size_t o_tab = room(tab_ints * 4), o_h = room(rows * d * 4), o_part = room(rows * ctx->n_part * 4),
+               o_xb = room(blocks * ctx->ns_d * 1024), o_q = room(rows * H * hd * 4),
+               o_att = room(blocks * ctx->ns_hhd * 1024), o_act = room(blocks * ctx->ns_F * 1024),
+               o_rsc = room(rows * 4), o_apart = room(mfma_prefill ? 0 : chunk * per_row);
+  const dex_status rs = prefill_room(ctx, slab, tab_ints);
+  if (rs != DEX_OK) return rs;                  // nothing changed yet: not poisoned
+  char *base = (char *)ctx->pf_dev;
+  float *h = (float *)(base + o_h), *part = (float *)(base + o_part), *q = (float *)(base + o_q),
+        *rsc = (float *)(base + o_rsc), *apart = (float *)(base + o_apart);
+  void *xb = base + o_xb, *att = base + o_att, *act = base + o_act;
 
-  // row tables: rows ordered (seq, position)
-  std::vector<int> host(tab_ints, 0);
-  int *t_seq = host.data(), *t_pos = t_seq + M, *t_entry = t_pos + M, *t_tok = t_entry + M, *t_nc = t_tok + M,
-      *t_coff = t_nc + M, *t_bnd = t_coff + M, *t_zero = t_bnd + M;
-  int *g_row0 = t_zero + M, *g_nrows = g_row0 + n_groups_total, *g_seq = g_nrows + n_groups_total;
-  int *g_rel = g_seq + n_groups_total;
-  int *ex_src = g_rel + n_groups_total, *ex_zero = ex_src + B, *ex_cidx = ex_zero + B;
-  int *ex_seq = ex_cidx + B, *ex_pos = ex_seq + B, *ex_one = ex_pos + B, *ex_nc = ex_one + B;
-  for (int s = 0; s < B; ++s)
+  // row tables: rows ordered (seq, position); then per sequence the tables of
+  // its last row; then what only the split kernel reads
+  int *T = ctx->pf_host;
+  int *t_seq = T, *t_pos = t_seq + M, *t_tok = t_pos + M;
+  int *ex_src = t_tok + M, *ex_zero = ex_src + B, *ex_cidx = ex_zero + B, *ex_seq = ex_cidx + B, *ex_pos = ex_seq + B,
+      *ex_one = ex_pos + B, *ex_nc = ex_one + B;
+  int *t_nc = ex_nc + B, *t_zero = t_nc + (mfma_prefill ? 0 : M), *g_nrows = t_zero + (mfma_prefill ? 1 : M),
+      *g_seq = g_nrows + n_groups, *g_rel = g_seq + n_groups;
+  for (int s = 0; s < B; ++s) {
     for (int p = 0; p < P; ++p) {
       const size_t r = (size_t)s * P + p;
-      t_seq[r] = s; t_pos[r] = p; t_entry[r] = p; t_tok[r] = prompts[r]; t_nc[r] = p + 1;
-      t_coff[r] = 0; t_bnd[r] = 0; t_zero[r] = 0;
+      t_seq[r] = s; t_pos[r] = p; t_tok[r] = prompts[r];
     }
-  std::vector<int> gr0, gnr, gsq;
-  for (int s = 0; s < B; ++s)
-    for (int p = 0; p < P; p += grp_rows) {
-      gr0.push_back(s * P + p);
-      gnr.push_back(std::min(grp_rows, P - p));
-      gsq.push_back(s);
-    }
-  const int ng = (int)gr0.size();
-  std::copy(gr0.begin(), gr0.end(), g_row0);
-  std::copy(gnr.begin(), gnr.end(), g_nrows);
-  std::copy(gsq.begin(), gsq.end(), g_seq);
-  // attention chunks: runs of whole groups holding at most `chunk` rows
-  std::vector<std::array<int, 4>> chunks;   // first group, groups, first row, rows
-  for (int g = 0; g < ng;) {
-    const int c0 = gr0[g];
-    int e = g, rows_in = 0;
-    while (e < ng && (rows_in + gnr[e] <= (int)chunk || e == g)) { rows_in += gnr[e]; ++e; }
-    for (int i = g; i < e; ++i) g_rel[i] = gr0[i] - c0;
-    chunks.push_back({g, e - g, c0, rows_in});
-    g = e;
-  }
-  for (int s = 0; s < B; ++s) {
-    ex_src[s] = s * P + P - 1; ex_zero[s] = 0; ex_cidx[s] = 0; ex_seq[s] = s; ex_pos[s] = P - 1;
+    ex_src[s] = (s % seqs_per) * P + P - 1; ex_zero[s] = 0; ex_cidx[s] = 0; ex_seq[s] = s; ex_pos[s] = P - 1;
     ex_one[s] = 1; ex_nc[s] = P;
   }
-  HIPCHK(hipMemcpyAsync(tab, host.data(), tab_ints * 4, hipMemcpyHostToDevice, ctx->stream));
-  const int *d_seq = tab, *d_pos = tab + M, *d_entry = d_pos + M, *d_tok = d_entry + M, *d_nc = d_tok + M,
-            *d_coff = d_nc + M, *d_zero = d_coff + 2 * M;
-  const int *d_g0 = d_zero + M, *d_gn = d_g0 + n_groups_total, *d_gs = d_gn + n_groups_total;
-  const int *d_grel = d_gs + n_groups_total;
-  const int *d_exsrc = d_grel + n_groups_total, *d_exzero = d_exsrc + B;
-  const int *d_exseq = d_exzero + 2 * B, *d_expos = d_exseq + B, *d_exone = d_expos + B, *d_exnc = d_exone + B;
-
-  // for the tiled GEMMs a packed k-step that the columns do not fill ends in zeros
-  if (tiled && d % 32 != 0) HIPCHK(hipMemsetAsync(xb, 0, blocks * ctx->ns_d * 1024, ctx->stream));
-  if (tiled && ctx->F % 32 != 0) HIPCHK(hipMemsetAsync(act, 0, blocks * ctx->ns_F * 1024, ctx->stream));
-  {
-    PrepArgs p{};
-    p.M = (int)M; p.d = d; p.n_part = ctx->n_part; p.embed_rows = (int)M; p.row_tok = d_tok; p.embed = ctx->embed;
-    p.g = (const float *)LW(ctx, 0, DEX_P_ATTN_NORM); p.h = h; p.part = part; p.xb = xb;
-    p.xb_steps = ctx->ns_d;
-    HIPCHK(launch_prep(ctx->dtype, p, ctx->stream));
+  t_zero[0] = 0;
+  std::vector<std::array<int, 4>> chunks;       // of the split kernel: first group, groups, first row of the part, rows
+  std::vector<int> chunk0(n_part_calls + 1, 0); // each part's first chunk
+  if (!mfma_prefill) {
+    for (size_t r = 0; r < M; ++r) { t_nc[r] = t_pos[r] + 1; t_zero[r] = 0; }
+    for (int c = 0; c < n_part_calls; ++c) {
+      const int s0 = c * seqs_per, s1 = std::min(B, s0 + seqs_per);
+      chunk0[c] = (int)chunks.size();
+      for (int s = s0; s < s1; ++s)
+        for (int i = 0; i < grp_seq; ++i) {     // runs of whole groups holding at most `chunk` rows
+          const int gi = s * grp_seq + i, row = (s - s0) * P + i * grp_rows, n = std::min(grp_rows, P - i * grp_rows);
+          if ((int)chunks.size() == chunk0[c] || chunks.back()[3] + n > (int)chunk) chunks.push_back({gi, 0, row, 0});
+          auto &ch = chunks.back();
+          g_nrows[gi] = n; g_seq[gi] = s; g_rel[gi] = row - ch[2];
+          ++ch[1];
+          ch[3] += n;
+        }
+    }
+    chunk0[n_part_calls] = (int)chunks.size();
   }
+  int *tab = (int *)(base + o_tab);
+  auto dev = [&](const int *t) -> const int * { return tab + (t - T); };
+  HIPCHK(hipMemcpyAsync(tab, T, tab_ints * 4, hipMemcpyHostToDevice, ctx->stream));
+  const int *d_exseq = dev(ex_seq), *d_exzero = dev(ex_zero), *d_expos = dev(ex_pos);
   const size_t layer_kv = (size_t)B * ctx->Hkv * ctx->E * hd * es;
   // a normed tiled GEMM first gets its row scales
   auto prefill_gemm = [&](int epi, GemmArgs a) -> hipError_t {
@@ -1130,94 +1163,112 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   // eighth of the layer's work at 32 / 8 heads and d_ffn 3.5 d), and the last
   // ones run the layer as decode rows.
   const int last_layer = ctx->L - 1;
-  for (int l = 0; l < ctx->L; ++l) {
-    if (l == last_layer && P == 1) break;            // every row is a last row
-    const float alpha = ctx->rscale * (float)(l + 1) / (float)ctx->L;
+  for (int c = 0; c < n_part_calls; ++c) {
+    const int s0 = c * seqs_per, ns = std::min(B, s0 + seqs_per) - s0;
+    const size_t r0 = (size_t)s0 * P;
+    const int R = ns * P;
+    // for the tiled GEMMs a packed k-step that the columns do not fill ends in zeros
+    if (tiled && d % 32 != 0) HIPCHK(hipMemsetAsync(xb, 0, blocks * ctx->ns_d * 1024, ctx->stream));
+    if (tiled && ctx->F % 32 != 0) HIPCHK(hipMemsetAsync(act, 0, blocks * ctx->ns_F * 1024, ctx->stream));
     {
-      const int q_cols = l == last_layer ? 0 : H * hd;   // the packed tiles hold q, then k, then v
-      GemmArgs a{};
-      a.wp = (const char *)ctx->p_qkv[l] + (l == last_layer ? (size_t)H * hd / 16 * ctx->ns_d * 1024 : 0);
-      a.nsteps_w = ctx->ns_d;
-      a.N = q_cols + 2 * ctx->Hkv * hd; a.K = d; a.x = xb; a.M = (int)M;
-      a.part = part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d; a.eps = ctx->eps;
-      a.out = q; a.ld_out = H * hd;
-      a.kc = (char *)ctx->kc + l * layer_kv; a.vc = (char *)ctx->vc + l * layer_kv;
-      a.kv_entries = ctx->E; a.n_heads = q_cols / hd; a.n_kv_heads = ctx->Hkv; a.head_dim = hd;
-      a.row_seq = d_seq; a.row_pos = d_pos; a.row_entry = d_entry; a.rope = ctx->rope;
-      HIPCHK(prefill_gemm(EPI_QKV, a));
+      PrepArgs p{};
+      p.M = R; p.d = d; p.n_part = ctx->n_part; p.embed_rows = R; p.row_tok = dev(t_tok) + r0; p.embed = ctx->embed;
+      p.g = (const float *)LW(ctx, 0, DEX_P_ATTN_NORM); p.h = h; p.part = part; p.xb = xb; p.xb_steps = ctx->ns_d;
+      HIPCHK(launch_prep(ctx->dtype, p, ctx->stream));
     }
-    if (l == last_layer) break;
-    if (mfma_prefill) {
-      PrefillAttnArgs a{};
-      a.q = q; a.ldq = H * hd;
-      a.kc = (char *)ctx->kc + l * layer_kv; a.vc = (char *)ctx->vc + l * layer_kv;
-      a.kv_entries = ctx->E; a.n_kv_heads = ctx->Hkv; a.n_heads = H; a.head_dim = hd; a.batch = B;
-      a.prompt_len = P; a.scale = 1.0f / std::sqrt((float)hd); a.out = att; a.out_steps = ctx->ns_hhd;
-      HIPCHK(launch_prefill_attention(a, ctx->stream));
-    } else for (const auto &ch : chunks) {
-      const int g_first = ch[0], g_cnt = ch[1], c0 = ch[2], cn = ch[3];
-      AttnArgs a{};
-      a.q = q + (size_t)c0 * H * hd; a.ldq = H * hd;
-      a.kc = (char *)ctx->kc + l * layer_kv; a.vc = (char *)ctx->vc + l * layer_kv;
-      a.kv_entries = ctx->E; a.n_kv_heads = ctx->Hkv; a.n_heads = H; a.head_dim = hd; a.batch = B;
-      a.grp_row0 = d_grel + g_first; a.grp_nrows = d_gn + g_first; a.grp_seq = d_gs + g_first;
-      a.row_pos = d_pos + c0; a.row_nc = d_nc + c0; a.row_chain_off = d_coff + c0; a.chain = d_zero;
-      a.row_seq = d_seq + c0; a.n_rows = cn;
-      a.part = apart; a.stat = split_stats(apart, cn, H, jmax, hd);
-      a.jmax = jmax; a.n_splits = jmax; a.scale = 1.0f / std::sqrt((float)hd);
-      HIPCHK(launch_attention(ctx->dtype, a, g_cnt, ctx->stream));
-      CombineArgs cb{};
-      cb.part = apart; cb.stat = split_stats(apart, cn, H, jmax, hd);
-      cb.row_pos = d_pos + c0; cb.jmax = jmax; cb.n_heads = H; cb.head_dim = hd;
-      cb.out = att; cb.out_steps = ctx->ns_hhd; cb.row0 = c0;
-      HIPCHK(launch_combine(ctx->dtype, cb, cn, ctx->stream));
+    for (int l = 0; l < ctx->L; ++l) {
+      if (l == last_layer && P == 1) break;            // every row is a last row
+      const float alpha = ctx->rscale * (float)(l + 1) / (float)ctx->L;
+      char *kcl = (char *)ctx->kc + l * layer_kv, *vcl = (char *)ctx->vc + l * layer_kv;
+      {
+        const int q_cols = l == last_layer ? 0 : H * hd;   // the packed tiles hold q, then k, then v
+        GemmArgs a{};
+        a.wp = (const char *)ctx->p_qkv[l] + (l == last_layer ? (size_t)H * hd / 16 * ctx->ns_d * 1024 : 0);
+        a.nsteps_w = ctx->ns_d;
+        a.N = q_cols + 2 * ctx->Hkv * hd; a.K = d; a.x = xb; a.M = R;
+        a.part = part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d; a.eps = ctx->eps;
+        a.out = q; a.ld_out = H * hd;
+        a.kc = kcl; a.vc = vcl;
+        a.kv_entries = ctx->E; a.n_heads = q_cols / hd; a.n_kv_heads = ctx->Hkv; a.head_dim = hd;
+        a.row_seq = dev(t_seq) + r0; a.row_pos = a.row_entry = dev(t_pos) + r0; a.rope = ctx->rope;
+        HIPCHK(prefill_gemm(EPI_QKV, a));
+      }
+      if (l == last_layer) break;
+      if (mfma_prefill) {
+        const size_t seq_kv = (size_t)ctx->Hkv * ctx->E * hd * es;
+        PrefillAttnArgs a{};
+        a.q = q; a.ldq = H * hd;
+        a.kc = kcl + s0 * seq_kv; a.vc = vcl + s0 * seq_kv;
+        a.kv_entries = ctx->E; a.n_kv_heads = ctx->Hkv; a.n_heads = H; a.head_dim = hd; a.batch = ns;
+        a.prompt_len = P; a.scale = 1.0f / std::sqrt((float)hd); a.out = att; a.out_steps = ctx->ns_hhd;
+        HIPCHK(launch_prefill_attention(a, ctx->stream));
+      } else for (int i = chunk0[c]; i < chunk0[c + 1]; ++i) {
+        const int g_first = chunks[i][0], g_cnt = chunks[i][1], c0 = chunks[i][2], cn = chunks[i][3];
+        AttnArgs a{};
+        a.q = q + (size_t)c0 * H * hd; a.ldq = H * hd;
+        a.kc = kcl; a.vc = vcl;
+        a.kv_entries = ctx->E; a.n_kv_heads = ctx->Hkv; a.n_heads = H; a.head_dim = hd; a.batch = B;
+        a.grp_row0 = dev(g_rel) + g_first; a.grp_nrows = dev(g_nrows) + g_first; a.grp_seq = dev(g_seq) + g_first;
+        a.row_pos = dev(t_pos) + r0 + c0; a.row_nc = dev(t_nc) + r0 + c0; a.row_chain_off = dev(t_zero) + r0 + c0;
+        a.chain = dev(t_zero); a.row_seq = dev(t_seq) + r0 + c0; a.n_rows = cn;
+        a.part = apart; a.stat = split_stats(apart, cn, H, jmax, hd);
+        a.jmax = jmax; a.n_splits = jmax; a.scale = 1.0f / std::sqrt((float)hd);
+        HIPCHK(launch_attention(ctx->dtype, a, g_cnt, ctx->stream));
+        CombineArgs cb{};
+        cb.part = apart; cb.stat = split_stats(apart, cn, H, jmax, hd);
+        cb.row_pos = a.row_pos; cb.jmax = jmax; cb.n_heads = H; cb.head_dim = hd;
+        cb.out = att; cb.out_steps = ctx->ns_hhd; cb.row0 = c0;
+        HIPCHK(launch_combine(ctx->dtype, cb, cn, ctx->stream));
+      }
+      {
+        GemmArgs a{};
+        a.wp = ctx->p_o[l]; a.nsteps_w = ctx->ns_hhd; a.N = d; a.K = H * hd; a.x = att; a.M = R;
+        a.h = h; a.ld_h = d; a.alpha = alpha; a.g_next = (const float *)LW(ctx, l, DEX_P_FFN_NORM); a.xb = xb;
+        a.part_out = part; a.n_part_out = ctx->n_part;
+        HIPCHK(prefill_gemm(EPI_RESID, a));
+      }
+      {
+        GemmArgs a{};
+        a.wp = ctx->p_gu[l]; a.nsteps_w = ctx->ns_d; a.N = ctx->F; a.K = d;
+        a.x = xb; a.M = R; a.part = part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d;
+        a.eps = ctx->eps; a.act = act;
+        HIPCHK(prefill_gemm(EPI_SWIGLU, a));
+      }
+      {
+        GemmArgs a{};
+        a.wp = ctx->p_down[l]; a.nsteps_w = ctx->ns_F; a.N = d; a.K = ctx->F; a.x = act; a.M = R;
+        a.h = h; a.ld_h = d; a.alpha = alpha; a.g_next = (const float *)LW(ctx, l + 1, DEX_P_ATTN_NORM);
+        a.xb = xb; a.part_out = part; a.n_part_out = ctx->n_part;
+        HIPCHK(prefill_gemm(EPI_RESID, a));
+      }
     }
-    {
-      GemmArgs a{};
-      a.wp = ctx->p_o[l]; a.nsteps_w = ctx->ns_hhd; a.N = d; a.K = H * hd; a.x = att; a.M = (int)M;
-      a.h = h; a.ld_h = d; a.alpha = alpha; a.g_next = (const float *)LW(ctx, l, DEX_P_FFN_NORM); a.xb = xb;
-      a.part_out = part; a.n_part_out = ctx->n_part;
-      HIPCHK(prefill_gemm(EPI_RESID, a));
-    }
-    {
-      GemmArgs a{};
-      a.wp = ctx->p_gu[l]; a.nsteps_w = ctx->ns_d; a.N = ctx->F; a.K = d;
-      a.x = xb; a.M = (int)M; a.part = part; a.n_part = ctx->n_part; a.inv_d = 1.0f / d;
-      a.eps = ctx->eps; a.act = act;
-      HIPCHK(prefill_gemm(EPI_SWIGLU, a));
-    }
-    {
-      GemmArgs a{};
-      a.wp = ctx->p_down[l]; a.nsteps_w = ctx->ns_F; a.N = d; a.K = ctx->F; a.x = act; a.M = (int)M;
-      a.h = h; a.ld_h = d; a.alpha = alpha; a.g_next = (const float *)LW(ctx, l + 1, DEX_P_ATTN_NORM);
-      a.xb = xb; a.part_out = part; a.n_part_out = ctx->n_part;
-      HIPCHK(prefill_gemm(EPI_RESID, a));
-    }
+    // the part's last rows, sequence s at row s
+    PrepArgs p{};
+    p.M = ns; p.d = d; p.n_part = ctx->n_part; p.embed_rows = 0; p.row_src = dev(ex_src) + s0; p.bnd_h = h;
+    p.bnd_part = part; p.g = (const float *)LW(ctx, last_layer, DEX_P_ATTN_NORM); p.h = ctx->h_w + (size_t)s0 * d;
+    p.part = ctx->part_w + (size_t)s0 * ctx->n_part; p.xb = ctx->xb_w; p.xb_steps = ctx->ns_d; p.row0 = s0;
+    p.rm = B <= kRowMajorRows;
+    HIPCHK(launch_prep(ctx->dtype, p, ctx->stream));
   }
   {
-    PrepArgs p{};
-    p.M = B; p.d = d; p.n_part = ctx->n_part; p.embed_rows = 0; p.row_src = d_exsrc; p.bnd_h = h; p.bnd_part = part;
-    p.g = (const float *)LW(ctx, last_layer, DEX_P_ATTN_NORM); p.h = ctx->h_w; p.part = ctx->part_w; p.xb = ctx->xb_w;
-    p.xb_steps = ctx->ns_d; p.rm = B <= kRowMajorRows;
-    HIPCHK(launch_prep(ctx->dtype, p, ctx->stream));
     StageTables t{};
-    t.seq = d_exseq; t.pos = d_expos; t.entry = d_expos; t.nc = d_exnc; t.chain_off = d_exzero; t.chain = d_zero;
-    t.g_row0 = d_exseq; t.g_nrows = d_exone; t.g_seq = d_exseq; t.g_nc = d_exnc;
+    t.seq = d_exseq; t.pos = d_expos; t.entry = d_expos; t.nc = dev(ex_nc); t.chain_off = d_exzero; t.chain = d_exzero;
+    t.g_row0 = d_exseq; t.g_nrows = dev(ex_one); t.g_seq = d_exseq; t.g_nc = dev(ex_nc);
     t.n_groups = B; t.n_splits = jmax;
     const bool timing = ctx->timing;
     ctx->timing = false;                             // the kernel times are those of rounds
     const dex_status ls = run_layers(ctx, ctx->stream, last_layer, last_layer, B, t, ctx->h_w, ctx->part_w, ctx->xb_w,
                                      ctx->q_w, ctx->att_w, ctx->act_w, 0, ctx->attn_part, ctx->jmax, false, nullptr);
     ctx->timing = timing;
-    if (ls != DEX_OK) { cleanup(); return ls; }
+    if (ls != DEX_OK) return ls;
   }
   // y_0: final-depth exit head at the last prompt position of every sequence
   dex_status es2 = run_exit(ctx, B, d_exseq, ctx->h_w, ctx->part_w, d_exzero, d_exzero, nullptr, nullptr, d_exseq, d_expos, nullptr,
                             nullptr);
-  if (es2 != DEX_OK) { cleanup(); return fail(ctx, es2); }
+  if (es2 != DEX_OK) return fail(ctx, es2);
   HIPCHK(hipMemcpyAsync(ctx->res_host, ctx->u_dev, B * 4, hipMemcpyDeviceToHost, ctx->stream));
   HIPCHK(hipStreamSynchronize(ctx->stream));
-  cleanup();
+  prefill_trim(ctx);
   harvest_timing(ctx);
   for (int s = 0; s < B; ++s) {
     Seq &q2 = ctx->seqs[s];
