@@ -70,7 +70,7 @@ __device__ __forceinline__ void rec_load(const T *p, bool ok, float (&v)[DPL]) {
 // key s0 + i for the scores and head dimensions [i*DPL, i*DPL + DPL) for the
 // value sum.
 template <typename T, int HD>
-__global__ __launch_bounds__(ATT_THREADS) void attn_kernel(AttnArgs a) {
+__device__ __forceinline__ void attn_item(const AttnArgs &a, int gi, int kvh, int split) {
   constexpr int WORDS = HD * (int)sizeof(T) / 4;     // 32-bit words per key row
   constexpr int V4 = WORDS / 4;                      // 16-byte loads per key row
   constexpr int DPL = HD >= 64 ? HD / 64 : 1;        // value dims per lane
@@ -82,7 +82,6 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) uint32_t vs[ATT_SPLIT][WORDS];
   __shared__ __attribute__((aligned(16))) float es[GMAX][ATT_SPLIT];
 
-  const int gi = blockIdx.x, kvh = blockIdx.y, split = blockIdx.z;
   const int r0 = a.grp_row0[gi], nr = a.grp_nrows[gi], seq = a.grp_seq[gi];
   const int G = a.n_heads / a.n_kv_heads;
   const int lane = threadIdx.x;
@@ -240,7 +239,11 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_kernel(AttnArgs a) {
       if (lane == 0) { a.stat[2 * rec] = m[g]; a.stat[2 * rec + 1] = l[g]; }
     }
   }
+}
 
+template <typename T, int HD>
+__global__ __launch_bounds__(ATT_THREADS) void attn_kernel(AttnArgs a) {
+  attn_item<T, HD>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // out[r][h] = sum_j w_j o_j / sum_j w_j l_j with w_j = e^{m_j - M},
@@ -352,12 +355,63 @@ __global__ __launch_bounds__(64 * CMB_WAVES) void combine_kernel(CombineArgs a) 
   }
 }
 
+// The arguments of segment sg alone: its layer of the cache, its queries,
+// rows and row groups, and the split records of its rows in the launch's
+// row space (records of element type T).
 template <typename T>
-static hipError_t launch_attn_t(const AttnArgs &a, dim3 grid, hipStream_t s) {
+static __host__ __device__ inline void attn_seg_view(AttnArgs &a, const AttnSeg &sg) {
+  const size_t r0 = (size_t)sg.r0;
+  a.kc = sg.kc;
+  a.vc = sg.vc;
+  a.q += r0 * a.ldq;
+  a.row_pos += r0;
+  a.row_nc += r0;
+  a.row_chain_off += r0;
+  a.row_seq += r0;
+  a.grp_row0 += sg.g0;
+  a.grp_nrows += sg.g0;
+  a.grp_seq += sg.g0;
+  if (a.grp_nc != nullptr) a.grp_nc += sg.g0;
+  a.n_rows = sg.M;
+  a.n_splits = sg.n_splits;
+  a.part = (T *)a.part + r0 * a.n_heads * a.jmax * a.head_dim;
+  a.stat += r0 * a.n_heads * a.jmax * 2;
+}
+
+// The segment whose items hold item x.
+__device__ __forceinline__ int find_seg(const AttnSegs &g, int x) {
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < MAX_SEGS; ++i) k += (i < g.n && x >= g.item0[i]) ? 1 : 0;
+  return k;
+}
+
+// Grouped form: block x is row group x - item0 of the segment that holds it
+// (the fp32 model's four stages: one launch instead of four of 7.5 us).
+template <typename T, int HD>
+__global__ __launch_bounds__(ATT_THREADS) void attn_seg_kernel(AttnArgs a, AttnSegs g) {
+  const int k = find_seg(g, blockIdx.x);
+  if ((int)blockIdx.z >= g.s[k].n_splits) return;
+  attn_seg_view<T>(a, g.s[k]);
+  attn_item<T, HD>(a, blockIdx.x - g.item0[k], blockIdx.y, blockIdx.z);
+}
+
+template <typename T>
+static hipError_t launch_attn_t(const AttnArgs &a, const AttnSegs *g, dim3 grid, hipStream_t s) {
+  const dim3 block(ATT_THREADS);
   switch (a.head_dim) {
-    case 32: hipLaunchKernelGGL((attn_kernel<T, 32>), grid, dim3(ATT_THREADS), 0, s, a); break;
-    case 64: hipLaunchKernelGGL((attn_kernel<T, 64>), grid, dim3(ATT_THREADS), 0, s, a); break;
-    case 128: hipLaunchKernelGGL((attn_kernel<T, 128>), grid, dim3(ATT_THREADS), 0, s, a); break;
+    case 32:
+      if (g != nullptr) hipLaunchKernelGGL((attn_seg_kernel<T, 32>), grid, block, 0, s, a, *g);
+      else hipLaunchKernelGGL((attn_kernel<T, 32>), grid, block, 0, s, a);
+      break;
+    case 64:
+      if (g != nullptr) hipLaunchKernelGGL((attn_seg_kernel<T, 64>), grid, block, 0, s, a, *g);
+      else hipLaunchKernelGGL((attn_kernel<T, 64>), grid, block, 0, s, a);
+      break;
+    case 128:
+      if (g != nullptr) hipLaunchKernelGGL((attn_seg_kernel<T, 128>), grid, block, 0, s, a, *g);
+      else hipLaunchKernelGGL((attn_kernel<T, 128>), grid, block, 0, s, a);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -402,39 +456,13 @@ __global__ __launch_bounds__(64) void attn_mfma_kernel(AttnArgs a) {
   attn_mfma_item<HD>(a, blockIdx.x, blockIdx.y, vr, prow, ppos);
 }
 
-// The arguments of segment sg alone: its layer of the cache, its queries,
-// rows and row groups, and the split records of its rows in the launch's
-// row space (records of element type T).
-template <typename T>
-static __host__ __device__ inline void attn_seg_view(AttnArgs &a, const AttnSeg &sg) {
-  const size_t r0 = (size_t)sg.r0;
-  a.kc = sg.kc;
-  a.vc = sg.vc;
-  a.q += r0 * a.ldq;
-  a.row_pos += r0;
-  a.row_nc += r0;
-  a.row_chain_off += r0;
-  a.row_seq += r0;
-  a.grp_row0 += sg.g0;
-  a.grp_nrows += sg.g0;
-  a.grp_seq += sg.g0;
-  if (a.grp_nc != nullptr) a.grp_nc += sg.g0;
-  a.n_rows = sg.M;
-  a.n_splits = sg.n_splits;
-  a.part = (T *)a.part + r0 * a.n_heads * a.jmax * a.head_dim;
-  a.stat += r0 * a.n_heads * a.jmax * 2;
-}
-
 // Grouped form: block x runs item x - item0 of the segment whose items hold it.
 template <int HD>
 __global__ __launch_bounds__(64) void attn_mfma_seg_kernel(AttnArgs a, AttnSegs g) {
   __shared__ __attribute__((aligned(16))) uint16_t vr[ATT_SPLIT][HD + 16];
   __shared__ int prow[ATT_MAX_PAIRS];
   __shared__ int ppos[ATT_MAX_PAIRS];
-  const int x = blockIdx.x;
-  int k = 0;
-#pragma unroll
-  for (int i = 1; i < MAX_SEGS; ++i) k += (i < g.n && x >= g.item0[i]) ? 1 : 0;
+  const int x = blockIdx.x, k = find_seg(g, x);
   attn_seg_view<bf16>(a, g.s[k]);
   attn_mfma_item<HD>(a, x - g.item0[k], blockIdx.y, vr, prow, ppos);
 }
@@ -720,11 +748,10 @@ hipError_t launch_attention(int dtype, const AttnArgs &a, int n_groups, hipStrea
     else hipLaunchKernelGGL(attn_mfma_kernel<64>, g2, dim3(64), 0, s, a);
     return hipGetLastError();
   }
-  return dtype == 1 ? launch_attn_t<bf16>(a, grid, s) : launch_attn_t<float>(a, grid, s);
+  return dtype == 1 ? launch_attn_t<bf16>(a, nullptr, grid, s) : launch_attn_t<float>(a, nullptr, grid, s);
 }
 
-// The matrix-core kernel: up to MAX_SEGS segments per launch, a lone segment
-// as a plain launch; the other kernels: one launch per segment.
+// Up to MAX_SEGS segments per launch, a lone segment as a plain launch.
 hipError_t launch_attention_seg(int dtype, const AttnArgs &a, const AttnSeg *segs, int n, hipStream_t s) {
   if (segs == nullptr || n < 1 || a.n_heads / a.n_kv_heads > 8) return hipErrorInvalidValue;
   for (int i = 0; i < n; ++i) {
@@ -732,44 +759,270 @@ hipError_t launch_attention_seg(int dtype, const AttnArgs &a, const AttnSeg *seg
     if (sg.M < 1 || sg.r0 < 0 || sg.g0 < 0 || sg.n_groups < 1 || sg.n_splits < 1 || sg.n_splits > a.jmax)
       return hipErrorInvalidValue;
   }
-  if (!(dtype == 1 && (a.head_dim == 128 || a.head_dim == 64))) {
-    for (int i = 0; i < n; ++i) {
-      AttnArgs b = a;
-      if (dtype == 1) attn_seg_view<bf16>(b, segs[i]);
-      else attn_seg_view<float>(b, segs[i]);
-      const hipError_t e = launch_attention(dtype, b, segs[i].n_groups, s);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  if (a.row_seq == nullptr) return hipErrorInvalidValue;
+  const bool mfma = dtype == 1 && (a.head_dim == 128 || a.head_dim == 64);
+  if (mfma && a.row_seq == nullptr) return hipErrorInvalidValue;
   for (int i0 = 0; i0 < n; i0 += MAX_SEGS) {
     const int c = n - i0 < MAX_SEGS ? n - i0 : MAX_SEGS;
     if (c == 1) {
       AttnArgs b = a;
-      attn_seg_view<bf16>(b, segs[i0]);
-      const hipError_t e = launch_attention(1, b, segs[i0].n_groups, s);
+      if (dtype == 1) attn_seg_view<bf16>(b, segs[i0]);
+      else attn_seg_view<float>(b, segs[i0]);
+      const hipError_t e = launch_attention(dtype, b, segs[i0].n_groups, s);
       if (e != hipSuccess) return e;
       continue;
     }
     AttnSegs g{};
     g.n = c;
     size_t items = 0;
+    int splits = 0;
     for (int i = 0; i < c; ++i) {
       const AttnSeg &sg = segs[i0 + i];
       g.s[i] = sg;
       g.item0[i] = (int)items;
-      items += 2 * (size_t)sg.M + (size_t)sg.n_groups * sg.n_splits;
+      items += mfma ? 2 * (size_t)sg.M + (size_t)sg.n_groups * sg.n_splits : (size_t)sg.n_groups;
       if (items > 0x7fffffffull) return hipErrorInvalidValue;
+      splits = sg.n_splits > splits ? sg.n_splits : splits;
     }
     for (int i = c; i < MAX_SEGS; ++i) g.item0[i] = (int)items;
-    const dim3 grid((unsigned)items, a.n_kv_heads);
-    if (a.head_dim == 128) hipLaunchKernelGGL(attn_mfma_seg_kernel<128>, grid, dim3(64), 0, s, a, g);
-    else hipLaunchKernelGGL(attn_mfma_seg_kernel<64>, grid, dim3(64), 0, s, a, g);
+    hipError_t e = hipSuccess;
+    if (!mfma) {
+      const dim3 grid((unsigned)items, a.n_kv_heads, splits);
+      e = dtype == 1 ? launch_attn_t<bf16>(a, &g, grid, s) : launch_attn_t<float>(a, &g, grid, s);
+    } else {
+      const dim3 grid((unsigned)items, a.n_kv_heads);
+      if (a.head_dim == 128) hipLaunchKernelGGL(attn_mfma_seg_kernel<128>, grid, dim3(64), 0, s, a, g);
+      else hipLaunchKernelGGL(attn_mfma_seg_kernel<64>, grid, dim3(64), 0, s, a, g);
+      e = hipGetLastError();
+    }
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// ------------------------------------------------------------------------
+// Short contexts (at most SHORT_SPLITS splits a row), bf16, head_dim 64 or
+// 128: attention and split combine in one launch.  Workgroup = (row, kv
+// head), wave j = split j; the split records stay in LDS and the workgroup
+// merges them.  At this length both kernels are chains of memory round trips
+// (6 + 4 us and the gap between them for 0.1 MB of keys), so one launch less
+// is what counts; a row alone reads its keys again for every row of its
+// sequence, and a compute unit fetches all of a row's splits, which is why
+// longer rows keep the split kernels.  Every number is computed as there --
+// the same products, statistics, bf16 records, and the combine's own order of
+// additions -- so a row's bits do not depend on which of the two ran.
+template <int HD, int NS>
+__device__ __forceinline__ void attn_short_row(const AttnArgs &a, const CombineArgs &c, int r, int kvh) {
+  constexpr int KS = HD / 32, DT = HD / 16, NKT = ATT_SPLIT / 16, V4 = HD / 8, RPI = 64 / V4;
+  __shared__ __attribute__((aligned(16))) uint16_t vr[NS][ATT_SPLIT][HD + 16];
+  __shared__ __attribute__((aligned(16))) uint16_t rec[NS][8][HD];
+  __shared__ float2 stat[NS][8];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r16 = lane & 15, grp = lane >> 4;
+  const int G = a.n_heads / a.n_kv_heads;
+  const int pos = a.row_pos[r], nc = a.row_nc[r], coff = a.row_chain_off[r], seq = a.row_seq[r];
+  const int s0 = wave * ATT_SPLIT;
+  if (s0 <= pos) {
+    const uint16_t *kbase = (const uint16_t *)a.kc + ((size_t)seq * a.n_kv_heads + kvh) * a.kv_entries * HD;
+    const uint16_t *vbase = (const uint16_t *)a.vc + ((size_t)seq * a.n_kv_heads + kvh) * a.kv_entries * HD;
+    // Q^T fragment: pair r16 = query head kvh G + r16, dims 32 st + 8 grp .. +8
+    const bool pok = r16 < G;
+    const float *qsrc = a.q + (size_t)r * a.ldq + (kvh * G + (pok ? r16 : 0)) * HD + grp * 8;
+    float4 qv[KS][2];
+#pragma unroll
+    for (int st = 0; st < KS; ++st) {
+      qv[st][0] = pok ? *(const float4 *)(qsrc + st * 32) : make_float4(0.f, 0.f, 0.f, 0.f);
+      qv[st][1] = pok ? *(const float4 *)(qsrc + st * 32 + 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    uint4 kf[NKT][KS], vv[V4];
+    const int vrow = lane / V4, vch = lane % V4;
+    const bool full = s0 + ATT_SPLIT <= nc;
+    if (full) {                                   // consecutive cache entries s0 ..
+      const uint16_t *kb = kbase + (size_t)s0 * HD, *vb = vbase + (size_t)s0 * HD;
+#pragma unroll
+      for (int nt = 0; nt < NKT; ++nt)
+#pragma unroll
+        for (int st = 0; st < KS; ++st) kf[nt][st] = *(const uint4 *)(kb + (nt * 16 + r16) * HD + st * 32 + grp * 8);
+#pragma unroll
+      for (int q = 0; q < V4; ++q) vv[q] = *(const uint4 *)(vb + (q * RPI + vrow) * HD + vch * 8);
+    } else {
+      // lane j looks up the cache entry of key s0 + j: committed below nc,
+      // then the row's chain, -1 past the row
+      const int kp = s0 + lane;
+      const int mine = kp < nc ? kp : (kp <= pos ? a.chain[coff + (kp - nc)] : -1);
+#pragma unroll
+      for (int nt = 0; nt < NKT; ++nt) {
+        const int e = __shfl(mine, nt * 16 + r16, 64);
+#pragma unroll
+        for (int st = 0; st < KS; ++st)
+          kf[nt][st] = e >= 0 ? *(const uint4 *)(kbase + (size_t)e * HD + st * 32 + grp * 8) : make_uint4(0, 0, 0, 0);
+      }
+#pragma unroll
+      for (int q = 0; q < V4; ++q) {
+        const int e = __shfl(mine, q * RPI + vrow, 64);
+        vv[q] = e >= 0 ? *(const uint4 *)(vbase + (size_t)e * HD + vch * 8) : make_uint4(0, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < V4; ++q) *(uint4 *)&vr[wave][q * RPI + vrow][vch * 8] = vv[q];
+    pf_f32x4 sc[NKT];
+#pragma unroll
+    for (int nt = 0; nt < NKT; ++nt) sc[nt] = pf_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < KS; ++st) {
+      const pf_bf16x8 qf = __builtin_bit_cast(
+          pf_bf16x8, make_uint4(pf_pack_bf16(qv[st][0].x, qv[st][0].y), pf_pack_bf16(qv[st][0].z, qv[st][0].w),
+                                pf_pack_bf16(qv[st][1].x, qv[st][1].y), pf_pack_bf16(qv[st][1].z, qv[st][1].w)));
+#pragma unroll
+      for (int nt = 0; nt < NKT; ++nt)
+        sc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pf_bf16x8, kf[nt][st]), qf, sc[nt], 0, 0, 0);
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int nt = 0; nt < NKT; ++nt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float v = sc[nt][i] * a.scale;
+        if (!full && s0 + nt * 16 + grp * 4 + i > pos) v = -INFINITY;
+        sc[nt][i] = v;
+        mx = fmaxf(mx, v);
+      }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    float sum = 0.f;
+#pragma unroll
+    for (int nt = 0; nt < NKT; ++nt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float e = (mx == -INFINITY) ? 0.f : expf(sc[nt][i] - mx);
+        sum += e;
+        sc[nt][i] = e;
+      }
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    wave_lds_sync();                              // this wave's value rows
+    pf_f32x4 o[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) o[dt] = pf_f32x4{0.f, 0.f, 0.f, 0.f};
+    const int tq = lane >> 4, ti = (lane & 15) >> 2, tg = lane & 3;
+#pragma unroll
+    for (int st = 0; st < ATT_SPLIT / 32; ++st) {
+      const pf_bf16x8 pfr = __builtin_bit_cast(
+          pf_bf16x8, make_uint4(pf_pack_bf16(sc[2 * st][0], sc[2 * st][1]), pf_pack_bf16(sc[2 * st][2], sc[2 * st][3]),
+                                pf_pack_bf16(sc[2 * st + 1][0], sc[2 * st + 1][1]),
+                                pf_pack_bf16(sc[2 * st + 1][2], sc[2 * st + 1][3])));
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            tr_frag(&vr[wave][32 * st + 4 * tq + ti][16 * dt + 4 * tg],
+                    &vr[wave][32 * st + 16 + 4 * tq + ti][16 * dt + 4 * tg]),
+            pfr, o[dt], 0, 0, 0);
+    }
+    if (pok) {
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        *(uint2 *)&rec[wave][r16][16 * dt + 4 * grp] =
+            make_uint2(pf_pack_bf16(o[dt][0], o[dt][1]), pf_pack_bf16(o[dt][2], o[dt][3]));
+      if (grp == 0) stat[wave][r16] = make_float2(mx, sum);
+    }
+  }
+  __syncthreads();
+  // the split combine: two dimensions per thread
+  const int nsplit = pos / ATT_SPLIT + 1;
+  const int pk = c.row_pk != nullptr ? c.row_pk[r] : c.row0 + r, rm = c.row_pk != nullptr ? pk < 0 : c.rm;
+  const int ro = c.row_pk != nullptr && rm ? ~pk : pk;
+  for (int e = threadIdx.x; e < G * HD / 2; e += 64 * NS) {
+    const int h = e / (HD / 2), d0 = 2 * (e % (HD / 2));
+    float M = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < NS; ++j)
+      if (j < nsplit) M = fmaxf(M, stat[j][h].x);
+    float lp[4] = {0.f, 0.f, 0.f, 0.f}, v0[4] = {0.f, 0.f, 0.f, 0.f}, v1[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < NS; ++j)
+      if (j < nsplit) {
+        const float w = expf(stat[j][h].x - M);
+        const uint32_t u = *(const uint32_t *)&rec[j][h][d0];
+        lp[j] = fmaf(w, stat[j][h].y, 0.f);
+        v0[j] = fmaf(w, __uint_as_float(u << 16), 0.f);
+        v1[j] = fmaf(w, __uint_as_float(u & 0xffff0000u), 0.f);
+      }
+    const float l = (lp[0] + lp[2]) + (lp[1] + lp[3]);   // the wave butterfly's order
+    const uint32_t lo = pf_f2bf((v0[0] + v0[1] + v0[2] + v0[3]) / l), hi = pf_f2bf((v1[0] + v1[1] + v1[2] + v1[3]) / l);
+    uint16_t *out = (uint16_t *)c.out;
+    const int col = (kvh * G + h) * HD + d0;
+    *(uint32_t *)(out + (c.out_steps > 0 ? act_off<bf16>(ro, col, c.out_steps, rm) : (size_t)r * c.ld_out + col)) =
+        lo | (hi << 16);
+  }
+}
+
+template <int HD, int NS>
+__global__ __launch_bounds__(64 * NS) void attn_short_kernel(AttnArgs a, CombineArgs c, int row0) {
+  attn_short_row<HD, NS>(a, c, row0 + blockIdx.x, blockIdx.y);
+}
+
+// Grouped form: block x is row x - item0 of the segment that holds it.
+template <int HD, int NS>
+__global__ __launch_bounds__(64 * NS) void attn_short_seg_kernel(AttnArgs a, CombineArgs c, AttnSegs g) {
+  const int x = blockIdx.x, k = find_seg(g, x);
+  a.kc = g.s[k].kc;
+  a.vc = g.s[k].vc;
+  attn_short_row<HD, NS>(a, c, g.s[k].r0 + x - g.item0[k], blockIdx.y);
+}
+
+template <int HD, int NS>
+static hipError_t launch_short_t(const AttnArgs &a, const CombineArgs &c, const AttnSeg *segs, int n, hipStream_t s) {
+  for (int i0 = 0; i0 < n; i0 += MAX_SEGS) {
+    const int cnt = n - i0 < MAX_SEGS ? n - i0 : MAX_SEGS;
+    if (cnt == 1) {
+      AttnArgs b = a;
+      b.kc = segs[i0].kc;
+      b.vc = segs[i0].vc;
+      hipLaunchKernelGGL((attn_short_kernel<HD, NS>), dim3(segs[i0].M, a.n_kv_heads), dim3(64 * NS), 0, s, b, c,
+                         segs[i0].r0);
+    } else {
+      AttnSegs g{};
+      g.n = cnt;
+      int rows = 0;
+      for (int i = 0; i < cnt; ++i) {
+        g.s[i] = segs[i0 + i];
+        g.item0[i] = rows;
+        rows += g.s[i].M;
+      }
+      for (int i = cnt; i < MAX_SEGS; ++i) g.item0[i] = rows;
+      hipLaunchKernelGGL((attn_short_seg_kernel<HD, NS>), dim3(rows, a.n_kv_heads), dim3(64 * NS), 0, s, a, c, g);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+static int short_splits(const AttnSeg *segs, int n) {
+  int m = 0;
+  for (int i = 0; i < n; ++i) m = segs[i].n_splits > m ? segs[i].n_splits : m;
+  return m;
+}
+
+bool attention_short_supported(int dtype, const AttnArgs &a, const AttnSeg *segs, int n) {
+  return dtype == 1 && (a.head_dim == 64 || a.head_dim == 128) && short_splits(segs, n) <= SHORT_SPLITS;
+}
+
+hipError_t launch_attention_short(int dtype, const AttnArgs &a, const CombineArgs &c, const AttnSeg *segs, int n,
+                                  hipStream_t s) {
+  if (segs == nullptr || n < 1 || a.row_seq == nullptr || a.n_heads / a.n_kv_heads > 8 ||
+      !attention_short_supported(dtype, a, segs, n))
+    return hipErrorInvalidValue;
+  for (int i = 0; i < n; ++i)
+    if (segs[i].M < 1 || segs[i].r0 < 0 || segs[i].n_splits < 1) return hipErrorInvalidValue;
+  const int m = short_splits(segs, n);
+  if (a.head_dim == 128) {
+    if (m == 1) return launch_short_t<128, 1>(a, c, segs, n, s);
+    if (m == 2) return launch_short_t<128, 2>(a, c, segs, n, s);
+    return launch_short_t<128, 4>(a, c, segs, n, s);
+  }
+  if (m == 1) return launch_short_t<64, 1>(a, c, segs, n, s);
+  if (m == 2) return launch_short_t<64, 2>(a, c, segs, n, s);
+  return launch_short_t<64, 4>(a, c, segs, n, s);
 }
 
 }  // namespace dex

@@ -453,16 +453,20 @@ dex_status run_layers(dex_ctx *ctx, hipStream_t st, int first_layer, int last_la
       a.row_seq = t.seq; a.n_rows = M;
       a.part = apart; a.stat = split_stats(apart, M, H, jmax, hd);
       a.jmax = jmax; a.n_splits = t.n_splits; a.scale = 1.0f / std::sqrt((float)hd);
-      TimedLaunch tl(ctx, 1, t.attn_bytes);
-      HIPCHK(launch_attention(ctx->dtype, a, t.n_groups, st));
-    }
-    {
       CombineArgs c{};
-      c.part = apart; c.stat = split_stats(apart, M, H, jmax, hd);
+      c.part = apart; c.stat = a.stat;
       c.row_pos = t.pos; c.jmax = jmax; c.n_heads = H; c.head_dim = hd;
       c.out = att; c.out_steps = ctx->ns_hhd; c.row0 = p0; c.rm = rm;
-      TimedLaunch tl(ctx, 2, 0.0);
-      HIPCHK(launch_combine(ctx->dtype, c, M, st));
+      const AttnSeg seg{a.kc, a.vc, 0, M, 0, t.n_groups, t.n_splits};
+      const bool one = attention_short_supported(ctx->dtype, a, &seg, 1);
+      {
+        TimedLaunch tl(ctx, 1, t.attn_bytes);
+        HIPCHK(one ? launch_attention_short(ctx->dtype, a, c, &seg, 1, st) : launch_attention(ctx->dtype, a, t.n_groups, st));
+      }
+      if (!one) {
+        TimedLaunch tl(ctx, 2, 0.0);
+        HIPCHK(launch_combine(ctx->dtype, c, M, st));
+      }
     }
     // O projection + residual
     {
@@ -700,12 +704,13 @@ hipError_t launch_attention_call(const AttnCall &c, const AttnTab &t, const int 
   a.chain = dtab + t.o_chain; a.row_seq = dtab + t.o_seq; a.n_rows = c.n_rows; a.part = part;
   a.stat = split_stats(part, c.n_rows, c.n_heads, t.n_splits, c.head_dim);
   a.jmax = t.n_splits; a.n_splits = t.n_splits; a.scale = 1.0f / std::sqrt((float)c.head_dim);
-  hipError_t e = launch_attention(c.dtype, a, t.ng, st);
   CombineArgs cb{};
   cb.part = part; cb.stat = a.stat; cb.row_pos = dtab + t.o_pos; cb.jmax = t.n_splits; cb.n_heads = c.n_heads;
   cb.head_dim = c.head_dim; cb.out = c.out; cb.ld_out = c.n_heads * c.head_dim;
-  if (e == hipSuccess) e = launch_combine(c.dtype, cb, c.n_rows, st);
-  return e;
+  const AttnSeg seg{a.kc, a.vc, 0, c.n_rows, 0, t.ng, t.n_splits};
+  if (attention_short_supported(c.dtype, a, &seg, 1)) return launch_attention_short(c.dtype, a, cb, &seg, 1, st);
+  const hipError_t e = launch_attention(c.dtype, a, t.ng, st);
+  return e == hipSuccess ? launch_combine(c.dtype, cb, c.n_rows, st) : e;
 }
 
 // ------------------------------------------ fixed scratch (no allocation)
@@ -1349,7 +1354,12 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
   std::vector<int> stage_r0(N + 1, 0), stage_g0(N + 1, 0), stage_p0(N, 0);
   int chain_used = 0, ngroups = 0;
   const int G = ctx->H / ctx->Hkv;
-  const int grp_rows = std::max(1, ATT_MAX_PAIRS / G);
+  const int grp_max = std::max(1, ATT_MAX_PAIRS / G);
+  // the matrix-core attention takes a group's rows side by side; the vector
+  // kernel one after another (5 us a row), so its groups shrink while that
+  // leaves under 2048 waves
+  const bool mfma_attn = ctx->dtype == DEX_BF16 && (ctx->hd == 64 || ctx->hd == 128);
+  const int grp_rows = mfma_attn ? grp_max : std::max(1, std::min(grp_max, R * ctx->Hkv * ctx->jmax / 2048));
   for (int r = 0; r < R; ++r) {
     const Row &rw = rows[r];
     const Seq &s = ctx->seqs[rw.seq];
@@ -1470,11 +1480,14 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
     t.n_groups = stage_g0[k + 1] - stage_g0[k];
     t.attn_bytes = 0.0;
     int stage_maxpos = 0;
-    for (int g = stage_g0[k]; g < stage_g0[k + 1]; ++g) {
-      int mp = 0;
-      for (int r = stage_r0[k] + t_g0[g]; r < stage_r0[k] + t_g0[g] + t_gn[g]; ++r) mp = std::max(mp, t_pos[r]);
+    // keys and values once per run of up to grp_max rows that share a prefix
+    for (int r = stage_r0[k]; r < stage_r0[k + 1];) {
+      int mp = 0, e = r;
+      for (; e < stage_r0[k + 1] && t_seq[e] == t_seq[r] && t_nc[e] == t_nc[r] && e - r < grp_max; ++e)
+        mp = std::max(mp, t_pos[e]);
       t.attn_bytes += (double)(mp + 1) * 2.0 * ctx->Hkv * ctx->hd * ctx->es;
       stage_maxpos = std::max(stage_maxpos, mp);
+      r = e;
     }
     t.n_splits = std::min(ctx->jmax, stage_maxpos / ATT_SPLIT + 1);
     t.attn_bytes += (double)M * ctx->H * ctx->hd * (4.0 + ctx->es);
@@ -1589,7 +1602,8 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
         TimedLaunch tl(ctx, 0, bytes);
         HIPCHK(launch_gemm_seg(ctx->dtype, EPI_QKV, a, gs.data(), n, st));
       }
-      // attention
+      // attention (short rows with their combine)
+      bool one = false;
       {
         AttnArgs a{};
         a.q = ctx->q_w; a.ldq = H * hd;
@@ -1612,11 +1626,16 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
           g.n_splits = tabs[k].n_splits;
           bytes += tabs[k].attn_bytes;
         }
+        CombineArgs c{};
+        c.n_heads = H; c.head_dim = hd;
+        c.out = ctx->att_w; c.out_steps = ctx->ns_hhd; c.row_pk = dptr(t_pk);
+        one = attention_short_supported(ctx->dtype, a, as.data(), n);
         TimedLaunch tl(ctx, 1, bytes);
-        HIPCHK(launch_attention_seg(ctx->dtype, a, as.data(), n, st));
+        HIPCHK(one ? launch_attention_short(ctx->dtype, a, c, as.data(), n, st)
+                   : launch_attention_seg(ctx->dtype, a, as.data(), n, st));
       }
       // split combine over each run of consecutive rows
-      for (int i = 0; i < n;) {
+      for (int i = 0; i < n && !one;) {
         const int ra = stage_r0[on[i]];
         int rb = stage_r0[on[i] + 1], e = i + 1;
         while (e < n && stage_r0[on[e]] == rb) rb = stage_r0[on[e++] + 1];

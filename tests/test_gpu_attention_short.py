@@ -1,0 +1,33 @@
+"""GPU: the one-launch attention of short rows (at most four 64-key splits)
+against the split kernels with their combine, which the same rows take when a
+longer row shares their launch: the same bits at every split edge."""
+import numpy as np
+import pytest
+
+from tests.gpu_common import torch_cuda
+from tests.test_gpu_attention import BF16_RTOL, Case, _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("H,Hkv", [(4, 4), (6, 2), (8, 2), (8, 1)])
+def test_short_rows_have_the_bits_of_the_split_kernels(hd, H, Hkv):
+    """Positions at and around every split edge from one key to 256, rows all
+    committed, with chains inside a split and across an edge, several rows
+    of a sequence; one, two and four splits a launch; float64 parity."""
+    torch = torch_cuda()
+    seqs = [(1, [0, 1, 3]), (60, [0, 2, 4, 9]), (63, [1, 2]), (64, [0, 1, 5]), (120, [8, 9, 20]), (127, [1, 30]),
+            (128, [0]), (190, [2, 5, 40]), (250, [0, 6]), (700, [2])]
+    c = Case(1, hd, H, Hkv, seqs, 4200 + hd + H)
+    full, full_bits = _run(torch, c)                    # 11 splits: the split kernels
+    short = [r for r in range(c.R) if c.pos[r] < 256]
+    for top in (64, 128, 256):                          # one, two, four splits
+        rows = [r for r in short if c.pos[r] < top]
+        out, bits = _run(torch, c, rows)
+        assert np.array_equal(bits, full_bits[rows]), top
+        ref = c.reference(rows)
+        err = np.linalg.norm(out - ref, axis=1) / np.linalg.norm(ref, axis=1)
+        assert err.max() <= BF16_RTOL, err.max()
+    for r in (short[0], short[5], short[-1]):           # and of a launch of their own
+        assert np.array_equal(_run(torch, c, [r])[1], full_bits[[r]])
