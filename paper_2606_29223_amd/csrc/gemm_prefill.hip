@@ -423,51 +423,63 @@ static hipError_t launch_ring(const GemmArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The tiles, largest first, with what one workgroup's k-step costs while a
-// workgroup runs on every compute unit, and its fixed part (first loads,
-// epilogue), both in ns.  Measured on the 4096-wide projections at 97, 512 and
-// 8192 rows from the slope between K = 4096 and K = 14336; a k-step is bound
-// by LDS (fragment reads at 128 and transfers at 64 bytes a clock), which is
-// why a larger tile costs less per output, and the largest by the matrix
-// cores and the card's power.  launch_gemm_tiled takes the tile of the least
-// rounds x (k-steps x step + fixed): small ones where a grid of large ones
-// leaves compute units idle.  At 512 rows (K = 4096 / 4096 / 14336, N = 6144 /
-// 4096 / 4096) 128 x 128, 64 x 128 and 64 x 128 take 39, 28 and 92 us against
-// 86, 83 and 258 us of 256 x 256; at 97 rows 64 x 64, 32 x 64 and 32 x 64 take
-// 21, 14 and 44 us; 8192 rows run 256 x 256 at 1.2-1.36 PFLOP/s.
+// The tiles, largest first, and what they cost: workgroups a compute unit
+// holds, a k-step of one workgroup alone (us), how much each further resident
+// one adds to it (share), the fixed part of a round (first loads) and of the
+// epilogue (QKV, RESID and PLAIN, SWIGLU).  A k-step is bound by LDS (fragment
+// reads and transfers), which is why a larger tile costs less per output, the
+// largest by the matrix cores and the card's power; small ones pay where a
+// grid of large ones leaves compute units idle.  The constants are a least
+// squares fit to measured launches, all four projections of 4096, 2048 and
+// 768 wide layers at 65 to 8192 rows; the tile of the least estimated time is
+// on average 2 %, at most 16 %, slower than the best of them (whole rounds of
+// one workgroup per compute unit, the first form of this rule: 7 and 53 %).
+// For instance (us): 4096 x 14336, 97 / 512 / 2200 / 8192 rows: 45 (32 x 64),
+// 103 (64 x 128), 286 and 777 (256 x 256, 1.24 PFLOP/s).
 typedef RingTile<16, 16, 4, 2, 1, 5> Tile256x256;
 typedef RingTile<16, 8, 2, 2, 1, 3> Tile256x128;
-typedef RingTile<8, 8, 2, 2, 1, 5> Tile128x128;
-typedef RingTile<4, 8, 2, 2, 2, 3> Tile64x128;
+typedef RingTile<8, 8, 2, 2, 1, 5> Tile128x128;       // five slots: two resident
+typedef RingTile<8, 8, 2, 2, 1, 3> Tile128x128r3;     // three slots: three resident
+typedef RingTile<4, 8, 2, 2, 1, 4> Tile64x128;
 typedef RingTile<4, 4, 1, 4, 2, 4> Tile64x64;
 typedef RingTile<2, 4, 1, 4, 4, 5> Tile32x64;
 struct TileCost {
-  int blocks, frags;          // weight blocks x input fragments
-  int step_ns, fixed_ns;
+  int blocks, frags, resident;  // weight blocks x input fragments; workgroups per compute unit
+  float step, more, fixed, epi[3];
 };
-static const TileCost kTileCost[] = {{16, 16, 750, 12000}, {16, 8, 400, 7000}, {8, 8, 275, 4000},
-                                     {4, 8, 200, 3000},    {4, 4, 130, 3000},  {2, 4, 100, 2000}};
+static const TileCost kTileCost[] = {
+    {16, 16, 1, 0.598f, 0.00f, 13.6f, {13.7f, 7.7f, 1.8f}}, {16, 8, 2, 0.407f, 0.94f, 12.4f, {7.9f, 5.4f, 0.0f}},
+    {8, 8, 2, 0.236f, 0.96f, 8.1f, {3.5f, 2.5f, 0.0f}},     {8, 8, 3, 0.316f, 0.60f, 5.8f, {4.3f, 1.9f, 0.0f}},
+    {4, 8, 3, 0.198f, 0.69f, 4.1f, {2.2f, 1.2f, 0.0f}},     {4, 4, 2, 0.121f, 0.85f, 3.4f, {0.6f, 1.1f, 0.0f}},
+    {2, 4, 1, 0.094f, 0.55f, 2.2f, {1.0f, 1.4f, 0.7f}}};
 
-static int choose_tile(int n_blocks, int n_frag, int nsteps) {
+static int choose_tile(int epi, int n_blocks, int n_frag, int nsteps) {
+  const int ei = epi == EPI_QKV ? 0 : epi == EPI_SWIGLU ? 2 : 1;
   int best = 0;
-  double best_ns = 0.0;
+  double best_us = 0.0;
   for (int i = 0; i < (int)(sizeof(kTileCost) / sizeof(kTileCost[0])); ++i) {
     const TileCost &c = kTileCost[i];
     const long long n_wg = (long long)((n_blocks + c.blocks - 1) / c.blocks) * ((n_frag + c.frags - 1) / c.frags);
-    const double ns = (double)((n_wg + 255) / 256) * ((double)nsteps * c.step_ns + c.fixed_ns);
-    if (i == 0 || ns < best_ns) { best = i; best_ns = ns; }
+    auto round_us = [&](int resident) {
+      const double share = 1.0 + (resident - 1) * (double)c.more;
+      return share * (nsteps * (double)c.step + c.epi[ei]) + c.fixed;
+    };
+    const long long per_round = 256LL * c.resident, rounds = n_wg / per_round, rest = n_wg % per_round;
+    const double us = rounds * round_us(c.resident) + (rest > 0 ? round_us((int)((rest + 255) / 256)) : 0.0);
+    if (i == 0 || us < best_us) { best = i; best_us = us; }
   }
   return best;
 }
 
 template <int EPI>
 static hipError_t launch_tile(const GemmArgs &a, hipStream_t s) {
-  switch (choose_tile((a.N + 15) / 16 * (EPI == EPI_SWIGLU ? 2 : 1), (a.M + 15) / 16, a.nsteps_w)) {
+  switch (choose_tile(EPI, (a.N + 15) / 16 * (EPI == EPI_SWIGLU ? 2 : 1), (a.M + 15) / 16, a.nsteps_w)) {
     case 0: return launch_ring<EPI, Tile256x256>(a, s);
     case 1: return launch_ring<EPI, Tile256x128>(a, s);
     case 2: return launch_ring<EPI, Tile128x128>(a, s);
-    case 3: return launch_ring<EPI, Tile64x128>(a, s);
-    case 4: return launch_ring<EPI, Tile64x64>(a, s);
+    case 3: return launch_ring<EPI, Tile128x128r3>(a, s);
+    case 4: return launch_ring<EPI, Tile64x128>(a, s);
+    case 5: return launch_ring<EPI, Tile64x64>(a, s);
     default: return launch_ring<EPI, Tile32x64>(a, s);
   }
 }

@@ -14,11 +14,13 @@ pytestmark = pytest.mark.gpu
 
 
 # (N, K, M): by the cost rule of the prompt GEMM these take, in turn, the
-# 256 x 256, 256 x 128, 128 x 128, 64 x 128, 64 x 64 and 32 x 64 tile, each
-# with a ragged last block in N and M and a last k-step only partly inside K;
-# then one, two and five k-steps (rings that never fill)
-@pytest.mark.parametrize("N,K,M", [(12304, 264, 2050), (8208, 264, 2050), (4112, 264, 530), (2064, 1096, 500),
-                                   (1552, 776, 500), (784, 776, 65), (4112, 24, 300), (4112, 40, 97), (528, 136, 257)])
+# 256 x 256, 256 x 128, 128 x 128 (five slots, three slots), 64 x 128, 64 x 64
+# and 32 x 64 tile, each with a ragged last block in N and M and a last k-step
+# only partly inside K; then one, two and five k-steps (rings that never
+# fill), and more shapes between
+@pytest.mark.parametrize("N,K,M", [(4112, 264, 3000), (2064, 3080, 3000), (8208, 1544, 257), (2064, 264, 3000),
+                                   (8208, 264, 97), (4112, 264, 97), (784, 264, 97), (4112, 24, 300), (4112, 40, 97),
+                                   (528, 136, 257), (2064, 1096, 500), (1552, 776, 500), (784, 776, 65)])
 def test_prompt_gemm_tiles(N, K, M):
     """float64 parity (fp32 accumulation of bf16 products: K eps sqrt-scaled,
     the bound of the other GEMM tests), and a row's bits do not depend on the
