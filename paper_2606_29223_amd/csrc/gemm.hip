@@ -79,6 +79,39 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a) {
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) acc[t][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
+  // What the epilogue reads besides the products, requested ahead of the
+  // weights where that is one round per thread (PRE: one tile, one row block,
+  // so at most eight rows of partials in the first pass over them): the norm
+  // partials of this wave's first row, the row-table entries of the thread's
+  // RoPE pair, the residual, next gain and boundary row of its element.  A
+  // launch of a narrow layer is a chain of such round trips (12-layer model:
+  // a round's QKV / O and down / gate-up launches 7.5 / 4.4 / 8.8 us before).
+  constexpr bool PRE = MB == 1 && NTW == 1;
+  constexpr int NPRE = 4;                      // partials per lane requested early (d_model 4096)
+  float pre_part[NPRE];
+  int pre_pos = 0, pre_seq = 0, pre_ent = 0, pre_bnd = 0;
+  float2 pre_cs = make_float2(0.f, 0.f);
+  float pre_h = 0.f, pre_g = 0.f;
+  if constexpr (PRE) {
+    if (EPI != EPI_RESID && a.part != nullptr) {
+      const float *p = a.part + (size_t)(m0 + min(wave, Mloc - 1)) * a.n_part;
+#pragma unroll
+      for (int i = 0; i < NPRE; ++i) pre_part[i] = lane + 64 * i < a.n_part ? p[lane + 64 * i] : 0.f;
+    }
+    if constexpr (EPI == EPI_QKV) {
+      const int m = m0 + min((int)threadIdx.x / 8, Mloc - 1);
+      pre_pos = a.row_pos[m];
+      pre_seq = a.row_seq[m];
+      pre_ent = a.row_entry[m];
+    }
+    if constexpr (EPI == EPI_RESID) {
+      const int m = m0 + min((int)threadIdx.x / 16, Mloc - 1), n = tile0 * 16 + threadIdx.x % 16;
+      pre_h = a.h[(size_t)m * a.ld_h + n];
+      if (a.xb != nullptr) pre_g = a.g_next[n];
+      if (a.row_bnd != nullptr) pre_bnd = a.row_bnd[m];
+    }
+  }
+
   const int nsteps = a.nsteps_w;
   F wa[U][NA], xa[U][MB], wb[U][NA], xb[U][MB];
 
@@ -109,6 +142,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a) {
   int s = wave;
   const int stride = U * GEMM_WAVES;
   if (s < nsteps) load_chunk(s, wa, xa);
+  if constexpr (PRE && EPI == EPI_QKV)
+    pre_cs = a.rope[(size_t)pre_pos * (a.head_dim / 2) + 8 * (tile0 % (a.head_dim / 16)) + threadIdx.x % 8];
   while (s < nsteps) {
     const int sn = s + stride;
     if (sn < nsteps) load_chunk(sn, wb, xb);
@@ -132,7 +167,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a) {
   // RMSNorm scales of this block's rows
   if (a.part != nullptr) {
     for (int ml = wave; ml < Mloc; ml += GEMM_WAVES) {
-      const float r = row_rscale(a.part + (size_t)(m0 + ml) * a.n_part, a.n_part, a.inv_d, a.eps, lane);
+      const float *p = a.part + (size_t)(m0 + ml) * a.n_part;
+      float r;
+      if (PRE && EPI != EPI_RESID && ml < GEMM_WAVES) r = row_rscale<NPRE>(p, a.n_part, a.inv_d, a.eps, lane, pre_part);
+      else r = row_rscale<0>(p, a.n_part, a.inv_d, a.eps, lane, nullptr);
       if (lane == 0) rs[ml] = r;
     }
   }
@@ -166,9 +204,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a) {
       const int c1 = col0 - (col0 % hd) + i;    // column of dim i in this head
       const int c2 = c1 + hd / 2;
       if (c1 < nq + nk) {                        // q or k: rotate
-        const float2 cs = a.rope[(size_t)a.row_pos[m] * (hd / 2) + i];
-        const float y1 = x1 * cs.x - x2 * cs.y;
-        const float y2 = x2 * cs.x + x1 * cs.y;
+        const bool pre = PRE && e < GEMM_THREADS;
+        const float2 cs = pre ? pre_cs : a.rope[(size_t)a.row_pos[m] * (hd / 2) + i];
+        // (which product is fused is stated: every variant has the same bits)
+        const float y1 = fmaf(x1, cs.x, -(x2 * cs.y));
+        const float y2 = fmaf(x2, cs.x, x1 * cs.y);
         x1 = y1;
         x2 = y2;
       }
@@ -180,14 +220,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a) {
         const int cc = isk ? c1 - nq : c1 - nq - nk;
         const int g = cc / hd, dim = cc % hd;
         T *cache = (T *)(isk ? a.kc : a.vc);
-        const size_t base = (((size_t)a.row_seq[m] * a.n_kv_heads + g) * a.kv_entries + a.row_entry[m]) * hd;
+        const bool pre = PRE && e < GEMM_THREADS;
+        const int sq = pre ? pre_seq : a.row_seq[m], ent = pre ? pre_ent : a.row_entry[m];
+        const size_t base = (((size_t)sq * a.n_kv_heads + g) * a.kv_entries + ent) * hd;
         cache[base + dim] = to_t<T>(x1);
         cache[base + dim + hd / 2] = to_t<T>(x2);
       }
     }
   } else if constexpr (EPI == EPI_RESID) {
     __shared__ float sq[16][16 * MB];
-    epi_resid<T, MB>(a, tile, m0, Mloc, vt[0], sq);
+    epi_resid<T, MB, PRE>(a, tile, m0, Mloc, vt[0], sq, pre_h, pre_g, pre_bnd);
   } else if constexpr (EPI == EPI_SWIGLU) {
     for (int e = threadIdx.x; e < 16 * Mloc; e += GEMM_THREADS) {
       const int ml = e / 16, nl = e % 16;

@@ -57,10 +57,15 @@ __device__ __forceinline__ u32x4_t load16_cached(const void *p, bool ok) {
 
 // RMSNorm reciprocal scale of one row from its sum-of-squares partials.  The
 // single definition used by every consumer: lane j sums partials j, j+64, ...
-// in order, then a fixed butterfly across the wave.
-__device__ __forceinline__ float row_rscale(const float *part, int n_part, float inv_d, float eps, int lane) {
+// in order, then a fixed butterfly across the wave.  The lane's first NPRE
+// partials may come loaded (zeros past the row's end).
+template <int NPRE>
+__device__ __forceinline__ float row_rscale(const float *part, int n_part, float inv_d, float eps, int lane,
+                                            const float *pre) {
   float s = 0.f;
-  for (int t = lane; t < n_part; t += 64) s += part[t];
+#pragma unroll
+  for (int i = 0; i < NPRE; ++i) s += pre[i];
+  for (int t = lane + 64 * NPRE; t < n_part; t += 64) s += part[t];
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
   return 1.0f / sqrtf(s * inv_d + eps);
@@ -87,20 +92,25 @@ __device__ __forceinline__ void reduce_block(const float (*red)[MB][64][4], floa
 // RESID epilogue of one 16-column tile for rows m0 .. m0 + Mloc: h += alpha *
 // acc (+ bias), the next RMSNorm's input g * h in the matrix-core type, and the
 // tile's sum-of-squares partial of each row; with row_bnd the results go to
-// the rows' boundary storage instead.  sq: [16][16 * MB] LDS scratch.  Ends
-// with a workgroup barrier.
-template <typename T, int MB>
+// the rows' boundary storage instead.  sq: [16][16 * MB] LDS scratch.  With
+// PRE (one row block) the thread's first element brings its residual, next
+// gain and boundary row along.  Ends with a workgroup barrier.
+template <typename T, int MB, bool PRE>
 __device__ __forceinline__ void epi_resid(const GemmArgs &a, int tile, int m0, int Mloc,
-                                          const float (*vt)[16 * MB], float (*sq)[16 * MB]) {
+                                          const float (*vt)[16 * MB], float (*sq)[16 * MB], float pre_h, float pre_g,
+                                          int pre_bnd) {
   for (int e = threadIdx.x; e < 16 * Mloc; e += GEMM_THREADS) {
     const int ml = e / 16, nl = e % 16;
     const int m = m0 + ml, n = tile * 16 + nl;
     const float *hin = a.h + (size_t)m * a.ld_h;
-    float *hout = (a.row_bnd != nullptr) ? a.bnd_h + (size_t)a.row_bnd[m] * a.ld_h : a.h + (size_t)m * a.ld_h;
+    // (one row block has at most 256 elements: one per thread)
+    float *hout = a.h + (size_t)m * a.ld_h;
+    if (a.row_bnd != nullptr) hout = a.bnd_h + (size_t)(PRE ? pre_bnd : a.row_bnd[m]) * a.ld_h;
     const float br = (a.bias != nullptr) ? a.alpha * (vt[nl][ml] + a.bias[n]) : a.alpha * vt[nl][ml];
-    const float hn = hin[n] + br;
+    const float hn = (PRE ? pre_h : hin[n]) + br;
     hout[n] = hn;
-    if (a.xb != nullptr) ((T *)a.xb)[act_off<T>(a.row0 + m, n, a.pk_steps, a.rm)] = to_t<T>(a.g_next[n] * hn);
+    if (a.xb != nullptr)
+      ((T *)a.xb)[act_off<T>(a.row0 + m, n, a.pk_steps, a.rm)] = to_t<T>((PRE ? pre_g : a.g_next[n]) * hn);
     sq[nl][ml] = hn * hn;
   }
   __syncthreads();

@@ -98,3 +98,34 @@ def test_prompt_attention_bits_do_not_depend_on_the_batch(hd, H, Hkv, P, B):
     for i, b in ((1, 0), (2, B - 1)):
         assert got[i][0][0] == got[0][0][b]
         assert torch.equal(got[i][1][0], got[0][1][b]) and torch.equal(got[i][2][0], got[0][2][b])
+
+
+@pytest.mark.parametrize("name", ["tiny-4L-d128-fp32", "small-12L-d768-bf16"])
+def test_keys_have_the_same_bits_at_every_row_count(name):
+    """Prompts of up to 64 positions run the decode GEMMs, whose variants load
+    the epilogue's inputs early or late and hold one to four row blocks: the
+    rotated keys and the values of the first positions are the same bits in
+    all of them."""
+    torch = torch_cuda()
+    from paper_2606_29223_amd import dexlib
+    cfg = configs.scaled_down(configs.get(name), n_layers=2, d_model=256, d_ffn=256, vocab=512)
+    cfg.update(n_heads=4, n_kv_heads=2, head_dim=64)
+    w = dexlib.device_weights(cfg, gen.generate_model(cfg))
+    prompt = np.random.default_rng(11).integers(0, 512, (1, 64)).astype(np.int32)
+    el = 2 if cfg["dtype"] == "bf16" else 4
+    want = None
+    for P in (64, 33, 32, 17, 16, 9, 8, 3):
+        dec = dexlib.Decoder(dict(cfg, prompt_len=P), w, explored=[2], width_cap=1, batch=1, max_context=P + 2)
+        dec.prefill(prompt[:, :P])
+        k, v, E = dec.kv_layout()
+        n = 2 * E * 64 * el                      # layer 0
+        got = []
+        for base in (k, v):
+            buf = torch.empty(n, dtype=torch.uint8, device="cuda")
+            assert dexlib.load().dex_debug_copy(buf.data_ptr(), base, n, dec.stream.cuda_stream) == 0
+            torch.cuda.synchronize()
+            got.append(buf.view(2, E, 64 * el)[:, :P].clone())
+        dec.close()
+        want = want or got
+        for a, b in zip(got, want):
+            assert torch.equal(a, b[:, :P]), P
