@@ -69,8 +69,11 @@ __device__ __forceinline__ void rec_load(const T *p, bool ok, float (&v)[DPL]) {
 // One wave per (row group, kv head, split of 64 logical keys).  Lane i owns
 // key s0 + i for the scores and head dimensions [i*DPL, i*DPL + DPL) for the
 // value sum.
-template <typename T, int HD>
-__device__ __forceinline__ void attn_item(const AttnArgs &a, int gi, int kvh, int split) {
+// ONE: every row of the launch has one split, whose combine (weight
+// e^0 = 1) is the division by its sum: the row goes out at once, row r of the
+// group's rows as row out0 + r of c.
+template <typename T, int HD, bool ONE>
+__device__ __forceinline__ void attn_item(const AttnArgs &a, int gi, int kvh, int split, const CombineArgs &c, int out0) {
   constexpr int WORDS = HD * (int)sizeof(T) / 4;     // 32-bit words per key row
   constexpr int V4 = WORDS / 4;                      // 16-byte loads per key row
   constexpr int DPL = HD >= 64 ? HD / 64 : 1;        // value dims per lane
@@ -230,6 +233,17 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, int gi, int kvh, in
 #pragma unroll
     for (int g = 0; g < GMAX; ++g) {
       if (g >= G) break;
+      if constexpr (ONE) {
+        const int pk = c.row_pk != nullptr ? c.row_pk[out0 + r] : c.row0 + out0 + r;
+        const int rm = c.row_pk != nullptr ? pk < 0 : c.rm, ro = c.row_pk != nullptr && rm ? ~pk : pk;
+        const int col = (kvh * G + g) * HD + d0;
+        T *out = (T *)c.out + (c.out_steps > 0 ? act_off<T>(ro, col, c.out_steps, rm) : (size_t)(out0 + r) * c.ld_out + col);
+        if (dims_ok) {
+#pragma unroll
+          for (int q = 0; q < DPL; ++q) out[q] = rec_elem<T>(rec_val<T>(rec_elem<T>(o[g][q])) / l[g]);
+        }
+        continue;
+      }
       const size_t rec = ((size_t)r * a.n_heads + kvh * G + g) * a.jmax + split;
       T *dst = (T *)a.part + rec * HD;
       if (dims_ok) {
@@ -243,7 +257,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, int gi, int kvh, in
 
 template <typename T, int HD>
 __global__ __launch_bounds__(ATT_THREADS) void attn_kernel(AttnArgs a) {
-  attn_item<T, HD>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+  attn_item<T, HD, false>(a, blockIdx.x, blockIdx.y, blockIdx.z, CombineArgs{}, 0);
 }
 
 // out[r][h] = sum_j w_j o_j / sum_j w_j l_j with w_j = e^{m_j - M},
@@ -393,7 +407,15 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_seg_kernel(AttnArgs a, AttnS
   const int k = find_seg(g, blockIdx.x);
   if ((int)blockIdx.z >= g.s[k].n_splits) return;
   attn_seg_view<T>(a, g.s[k]);
-  attn_item<T, HD>(a, blockIdx.x - g.item0[k], blockIdx.y, blockIdx.z);
+  attn_item<T, HD, false>(a, blockIdx.x - g.item0[k], blockIdx.y, blockIdx.z, CombineArgs{}, 0);
+}
+
+// Rows of one split (see ONE): attention and combine in one launch.
+template <typename T, int HD>
+__global__ __launch_bounds__(ATT_THREADS) void attn_one_seg_kernel(AttnArgs a, CombineArgs c, AttnSegs g) {
+  const int k = find_seg(g, blockIdx.x);
+  attn_seg_view<T>(a, g.s[k]);
+  attn_item<T, HD, true>(a, blockIdx.x - g.item0[k], blockIdx.y, 0, c, g.s[k].r0);
 }
 
 template <typename T>
@@ -1003,8 +1025,35 @@ static int short_splits(const AttnSeg *segs, int n) {
   return m;
 }
 
+template <typename T>
+static hipError_t launch_one_t(const AttnArgs &a, const CombineArgs &c, const AttnSeg *segs, int n, hipStream_t s) {
+  for (int i0 = 0; i0 < n; i0 += MAX_SEGS) {
+    AttnSegs g{};
+    g.n = n - i0 < MAX_SEGS ? n - i0 : MAX_SEGS;
+    int groups = 0;
+    for (int i = 0; i < MAX_SEGS; ++i) {
+      g.item0[i] = groups;
+      if (i >= g.n) continue;
+      g.s[i] = segs[i0 + i];
+      groups += g.s[i].n_groups;
+    }
+    const dim3 grid(groups, a.n_kv_heads), block(ATT_THREADS);
+    switch (a.head_dim) {
+      case 32: hipLaunchKernelGGL((attn_one_seg_kernel<T, 32>), grid, block, 0, s, a, c, g); break;
+      case 64: hipLaunchKernelGGL((attn_one_seg_kernel<T, 64>), grid, block, 0, s, a, c, g); break;
+      case 128: hipLaunchKernelGGL((attn_one_seg_kernel<T, 128>), grid, block, 0, s, a, c, g); break;
+      default: return hipErrorInvalidValue;
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+static bool mfma_attention(int dtype, int head_dim) { return dtype == 1 && (head_dim == 64 || head_dim == 128); }
+
 bool attention_short_supported(int dtype, const AttnArgs &a, const AttnSeg *segs, int n) {
-  return dtype == 1 && (a.head_dim == 64 || a.head_dim == 128) && short_splits(segs, n) <= SHORT_SPLITS;
+  return short_splits(segs, n) <= (mfma_attention(dtype, a.head_dim) ? SHORT_SPLITS : 1);
 }
 
 hipError_t launch_attention_short(int dtype, const AttnArgs &a, const CombineArgs &c, const AttnSeg *segs, int n,
@@ -1013,7 +1062,10 @@ hipError_t launch_attention_short(int dtype, const AttnArgs &a, const CombineArg
       !attention_short_supported(dtype, a, segs, n))
     return hipErrorInvalidValue;
   for (int i = 0; i < n; ++i)
-    if (segs[i].M < 1 || segs[i].r0 < 0 || segs[i].n_splits < 1) return hipErrorInvalidValue;
+    if (segs[i].M < 1 || segs[i].r0 < 0 || segs[i].n_splits < 1 || segs[i].g0 < 0 || segs[i].n_groups < 1)
+      return hipErrorInvalidValue;
+  if (!mfma_attention(dtype, a.head_dim))
+    return dtype == 1 ? launch_one_t<bf16>(a, c, segs, n, s) : launch_one_t<float>(a, c, segs, n, s);
   const int m = short_splits(segs, n);
   if (a.head_dim == 128) {
     if (m == 1) return launch_short_t<128, 1>(a, c, segs, n, s);

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from tests.gpu_common import torch_cuda
-from tests.test_gpu_attention import BF16_RTOL, Case, _run
+from tests.test_gpu_attention import BF16_RTOL, F32_RTOL, Case, _run
 
 pytestmark = pytest.mark.gpu
 
@@ -31,3 +31,20 @@ def test_short_rows_have_the_bits_of_the_split_kernels(hd, H, Hkv):
         assert err.max() <= BF16_RTOL, err.max()
     for r in (short[0], short[5], short[-1]):           # and of a launch of their own
         assert np.array_equal(_run(torch, c, [r])[1], full_bits[[r]])
+
+
+@pytest.mark.parametrize("dtype,hd", [(0, 32), (0, 64), (0, 128), (1, 32)])
+@pytest.mark.parametrize("H,Hkv", [(4, 4), (6, 2), (8, 1)])
+def test_one_split_rows_have_the_bits_of_the_split_kernels(dtype, hd, H, Hkv):
+    """The vector kernel writes rows of at most 64 keys out at once; with a
+    longer row in the launch they go through split records and the combine."""
+    torch = torch_cuda()
+    c = Case(dtype, hd, H, Hkv, [(1, [0, 1]), (17, [0, 3, 7]), (60, [1, 4]), (64, [0]), (90, [2])], 4300 + hd + H)
+    full, full_bits = _run(torch, c)
+    rows = [r for r in range(c.R) if c.pos[r] < 64]
+    out, bits = _run(torch, c, rows)
+    assert np.array_equal(bits, full_bits[rows])
+    assert np.array_equal(_run(torch, c, rows[2:3])[1], full_bits[rows[2:3]])
+    ref = c.reference(rows)
+    err = np.linalg.norm(out - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert err.max() <= (BF16_RTOL if dtype == 1 else F32_RTOL), err.max()
