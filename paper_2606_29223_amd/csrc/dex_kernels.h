@@ -334,7 +334,7 @@ hipError_t launch_prep(int dtype, const PrepArgs &a, hipStream_t s);
 struct ArgmaxArgs {
   const float2 *amax;
   int n_tiles, M;
-  int *u_out;                 // [M]
+  int *u_out;                 // [M], in host memory, as commit_out: stored past the caches
   int *cand;                  // [..][N] candidate table (nullable)
   const int *row_cand;        // [M] index into cand (slot*N + stage)
   // verify/commit of the rows that complete an anchor's final stage
@@ -347,7 +347,8 @@ hipError_t launch_argmax(const ArgmaxArgs &a, hipStream_t s);
 
 struct CollapseArgs {
   int n_jobs;
-  const int *job;             // [n_jobs][6]: seq, src entry, dst entry, src slot, dst slot, kind (0 kv only, 1 kv + slot state)
+  const int *job;             // [n_jobs][6] in host memory: seq, src entry, dst entry, src slot, dst slot, kind (0 kv only, 1 kv + slot state)
+  int *job_dev;               // room for them on the device
   void *kc, *vc;              // cache base
   int n_layers, batch, n_kv_heads, kv_entries, head_dim;
   int elem_bytes;
@@ -356,6 +357,10 @@ struct CollapseArgs {
   int slots2, d, n_part, N, max_ctx, S;
 };
 hipError_t launch_collapse(const CollapseArgs &a, hipStream_t s);
+
+// n ints from host memory to the device, in stream order; src is free to be
+// reused at once if it is pageable, or once the stream has passed if pinned.
+hipError_t launch_upload(int *dst, const int *src, size_t n, hipStream_t s);
 
 hipError_t launch_gumbel(unsigned long long seed, int seq, int pos, int V, float *out, hipStream_t s);
 hipError_t launch_copy(void *dst, const void *src, int64_t bytes, hipStream_t s);

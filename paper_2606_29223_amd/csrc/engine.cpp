@@ -161,12 +161,12 @@ struct dex_ctx {
   float *ex_h = nullptr, *ex_part = nullptr;
   void *ex_xb = nullptr;
   float2 *amax = nullptr;
-  int *u_dev = nullptr;          // [R] decoded candidates, then [2 * commits] (token, k*)
   int *tab_dev = nullptr;
   size_t tab_cap = 0;
   int *job_dev = nullptr;
   // pinned host staging
-  int *tab_host = nullptr, *res_host = nullptr, *job_host = nullptr;
+  int *tab_host = nullptr, *job_host = nullptr;
+  int *res_host = nullptr;       // [R] decoded candidates, then [2 * commits] (token, k*); the GPU writes it
   // prompt scratch and its pinned row tables, kept between prompts
   void *pf_dev = nullptr;
   size_t pf_bytes = 0;
@@ -590,9 +590,9 @@ dex_status run_exit(dex_ctx *ctx, int M, const int *row_src, const float *src_h,
   }
   {
     ArgmaxArgs g{};
-    g.amax = ctx->amax; g.n_tiles = n_tiles; g.M = M; g.u_out = ctx->u_dev;
+    g.amax = ctx->amax; g.n_tiles = n_tiles; g.M = M; g.u_out = ctx->res_host;
     g.cand = cand; g.row_cand = cand_idx;
-    g.row_commit = row_commit; g.N = ctx->N; g.commit_out = ctx->u_dev + M;
+    g.row_commit = row_commit; g.N = ctx->N; g.commit_out = ctx->res_host + M;
     TimedLaunch tl(ctx, 7, 0.0);
     HIPCHK(launch_argmax(g, st));
   }
@@ -921,7 +921,6 @@ dex_status dex_create(const dex_model *m, const dex_config *c, dex_ctx **out) {
   A(&ctx->ex_xb, blocks * ctx->ns_d * blk);
   if (c->adapter_dim > 0) A(&ctx->ad_act, blocks * ctx->ns_m * blk);
   A((void **)&ctx->amax, R * ((ctx->V + 15) / 16) * sizeof(float2));
-  A((void **)&ctx->u_dev, (R + 2 * (size_t)ctx->B) * 4 + 256);
   A((void **)&ctx->job_dev, (size_t)(ctx->B * (ctx->S + 1)) * 6 * 4 + 256);
   ctx->tab_cap = (size_t)R * (16 + 2 * N + ctx->CH_MAX) + 4 * ctx->B + 1024;
   A((void **)&ctx->tab_dev, ctx->tab_cap * 4);
@@ -932,7 +931,8 @@ dex_status dex_create(const dex_model *m, const dex_config *c, dex_ctx **out) {
     return st;
   }
   if (hipHostMalloc((void **)&ctx->tab_host, ctx->tab_cap * 4) != hipSuccess ||
-      hipHostMalloc((void **)&ctx->res_host, (R + 2 * ctx->B + 64) * 4) != hipSuccess ||
+      hipHostMalloc((void **)&ctx->res_host, (R + 2 * ctx->B + 64) * 4, hipHostMallocMapped | hipHostMallocCoherent) !=
+          hipSuccess ||
       hipHostMalloc((void **)&ctx->job_host, (size_t)(ctx->B * (ctx->S + 1)) * 6 * 4 + 256) != hipSuccess) {
     g_create_error = "hipHostMalloc failed";
     dex_destroy(ctx);
@@ -1149,7 +1149,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   }
   int *tab = (int *)(base + o_tab);
   auto dev = [&](const int *t) -> const int * { return tab + (t - T); };
-  HIPCHK(hipMemcpyAsync(tab, T, tab_ints * 4, hipMemcpyHostToDevice, ctx->stream));
+  HIPCHK(launch_upload(tab, T, tab_ints, ctx->stream));
   const int *d_exseq = dev(ex_seq), *d_exzero = dev(ex_zero), *d_expos = dev(ex_pos);
   const size_t layer_kv = (size_t)B * ctx->Hkv * ctx->E * hd * es;
   // a normed tiled GEMM first gets its row scales
@@ -1271,7 +1271,6 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   dex_status es2 = run_exit(ctx, B, d_exseq, ctx->h_w, ctx->part_w, d_exzero, d_exzero, nullptr, nullptr, d_exseq, d_expos, nullptr,
                             nullptr);
   if (es2 != DEX_OK) return fail(ctx, es2);
-  HIPCHK(hipMemcpyAsync(ctx->res_host, ctx->u_dev, B * 4, hipMemcpyDeviceToHost, ctx->stream));
   HIPCHK(hipStreamSynchronize(ctx->stream));
   prefill_trim(ctx);
   harvest_timing(ctx);
@@ -1425,7 +1424,7 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
     ctx->rt_ms[6] += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_call).count();
     HIPCHK(hipEventRecord(rt[0], ctx->stream));
   }
-  HIPCHK(hipMemcpyAsync(ctx->tab_dev, T, tab_ints * 4, hipMemcpyHostToDevice, ctx->stream));
+  HIPCHK(launch_upload(ctx->tab_dev, T, tab_ints, ctx->stream));
   if (rt) HIPCHK(hipEventRecord(rt[1], ctx->stream));
   const int *D = ctx->tab_dev;
   auto dptr = [&](const int *hp) { return D + (hp - T); };
@@ -1768,9 +1767,6 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
                            dptr(t_cidx), ctx->cand, dptr(t_seq), dptr(t_pos), stage_r0.data(), dptr(t_rcommit));
   if (xs != DEX_OK) return fail(ctx, xs);
   if (rt) HIPCHK(hipEventRecord(rt[3], ctx->stream));
-  // candidates, then (token, k*) of the committing sequences, in one copy
-  HIPCHK(hipMemcpyAsync(ctx->res_host, ctx->u_dev, (R + 2 * commit_seqs.size()) * 4, hipMemcpyDeviceToHost,
-                        ctx->stream));
   if (rt) HIPCHK(hipEventRecord(rt[4], ctx->stream));
   HIPCHK(hipStreamSynchronize(ctx->stream));
   if (rt) {
@@ -1878,9 +1874,8 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
     if ((int)s.committed.size() >= ctx->max_ctx) s.active = false;
   }
   if (njobs > 0) {
-    HIPCHK(hipMemcpyAsync(ctx->job_dev, J, njobs * 6 * 4, hipMemcpyHostToDevice, ctx->stream));
     CollapseArgs c{};
-    c.n_jobs = njobs; c.job = ctx->job_dev; c.kc = ctx->kc; c.vc = ctx->vc;
+    c.n_jobs = njobs; c.job = J; c.job_dev = ctx->job_dev; c.kc = ctx->kc; c.vc = ctx->vc;
     c.n_layers = ctx->L; c.batch = B; c.n_kv_heads = ctx->Hkv; c.kv_entries = ctx->E; c.head_dim = ctx->hd;
     c.elem_bytes = ctx->es; c.bnd_h = ctx->bnd_h; c.bnd_part = ctx->bnd_part; c.cand = ctx->cand;
     c.slots2 = 2 * ctx->S; c.d = ctx->d; c.n_part = ctx->n_part; c.N = N; c.max_ctx = ctx->max_ctx; c.S = ctx->S;
@@ -2122,7 +2117,7 @@ dex_status dex_debug_attention(int32_t dtype, int32_t head_dim, int32_t n_heads,
   float *part = nullptr;
   if (hipMalloc((void **)&dtab, t.n_ints * 4) != hipSuccess) return DEX_E_NOMEM;
   if (hipMalloc((void **)&part, t.part_bytes) != hipSuccess) { (void)hipFree(dtab); return DEX_E_NOMEM; }
-  hipError_t e = hipMemcpyAsync(dtab, tab.data(), t.n_ints * 4, hipMemcpyHostToDevice, st);
+  hipError_t e = launch_upload(dtab, tab.data(), t.n_ints, st);
   if (e == hipSuccess) e = launch_attention_call(c, t, dtab, part, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   else (void)hipStreamSynchronize(st);
@@ -2163,7 +2158,7 @@ dex_status dex_debug_attention_noalloc(int32_t dtype, int32_t head_dim, int32_t 
   const hipStream_t st = (hipStream_t)stream;
   int *dtab = (int *)base;
   float *part = (float *)((char *)base + kScratchTableBytes);
-  e = hipMemcpyAsync(dtab, tab, t.n_ints * 4, hipMemcpyHostToDevice, st);
+  e = launch_upload(dtab, tab, t.n_ints, st);
   if (e == hipSuccess) e = launch_attention_call(c, t, dtab, part, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   else (void)hipStreamSynchronize(st);

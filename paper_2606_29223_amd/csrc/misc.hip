@@ -4,6 +4,8 @@
 // traffic counters.
 #include "dex_kernels.h"
 
+#include <cstring>
+
 namespace dex {
 
 constexpr int PREP_THREADS = 64;              // 16-column groups per prep workgroup
@@ -144,7 +146,9 @@ __global__ __launch_bounds__(AMAX_THREADS) void argmax_kernel(ArgmaxArgs a) {
   __syncthreads();
   if (tid == 0) {
     for (int w = 1; w < AMAX_THREADS / 64; ++w) amax_take(bv, bi, sv[w], si[w]);
-    a.u_out[m] = bi;
+    // the results go straight to host memory: a copy command behind this
+    // kernel took 6 us of a round
+    __hip_atomic_store(a.u_out + m, bi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (a.cand != nullptr) a.cand[a.row_cand[m]] = bi;
     // Validate and commit (Section 3.2, commit process) when this row is an
     // anchor's final-depth node: its candidates u_0..u_{N-2} (earlier rounds)
@@ -155,8 +159,9 @@ __global__ __launch_bounds__(AMAX_THREADS) void argmax_kernel(ArgmaxArgs a) {
       int k = a.N - 1;
       for (int j = 0; j < a.N - 1; ++j)
         if (u[j] == bi) { k = j; break; }
-      a.commit_out[2 * a.row_commit[m]] = bi;
-      a.commit_out[2 * a.row_commit[m] + 1] = k;
+      int *out = a.commit_out + 2 * a.row_commit[m];
+      __hip_atomic_store(out, bi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(out + 1, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
 }
@@ -167,16 +172,43 @@ hipError_t launch_argmax(const ArgmaxArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// A few words as a kernel argument: a launch is a third of what the host and
+// the stream spend on a copy command of this size (6 us), and most tables of
+// a round fit.  960 words are the most that the 4 KB of arguments hold.
+template <int N> struct Words { int v[N]; };
+constexpr int WORDS_SMALL = 240, WORDS_MAX = 960;
+template <int N>
+__global__ __launch_bounds__(N) void words_kernel(int *dst, int n, Words<N> w) {
+  const int i = threadIdx.x;
+  if (i < n) dst[i] = w.v[i];
+}
+template <int N>
+static hipError_t launch_words_t(int *dst, const int *src, int n, hipStream_t s) {
+  Words<N> w;
+  std::memcpy(w.v, src, (size_t)n * 4);
+  if (n < N) std::memset(w.v + n, 0, (size_t)(N - n) * 4);
+  hipLaunchKernelGGL(words_kernel<N>, dim3(1), dim3(N), 0, s, dst, n, w);
+  return hipGetLastError();
+}
+
+hipError_t launch_upload(int *dst, const int *src, size_t n, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  if (n <= WORDS_SMALL) return launch_words_t<WORDS_SMALL>(dst, src, (int)n, s);
+  if (n <= WORDS_MAX) return launch_words_t<WORDS_MAX>(dst, src, (int)n, s);
+  return hipMemcpyAsync(dst, src, n * 4, hipMemcpyHostToDevice, s);
+}
+
 // Collapse gather.  Job (seq, src entry, dst entry, src slot, dst slot, kind):
 // copy the keys/values of one cache entry (every layer, every kv head) and,
 // for kind 1, the slot's boundary state and candidate list.  The old anchor
 // goes to its committed position (kind 0); retained slots move to the
 // other half of the lattice region in canonical order (kind 1), so source
 // and destination never overlap.
-template <int ELEM>
-__global__ __launch_bounds__(256) void collapse_kernel(CollapseArgs a) {
+// Up to 40 jobs ride in the kernel arguments (ARGS).
+template <int ELEM, bool ARGS>
+__global__ __launch_bounds__(256) void collapse_kernel(CollapseArgs a, Words<WORDS_SMALL> w) {
   const int jb = blockIdx.x, l = blockIdx.y;
-  const int *j = a.job + 6 * jb;
+  const int *j = ARGS ? w.v + 6 * jb : a.job_dev + 6 * jb;
   const int seq = j[0], se = j[1], de = j[2], ss = j[3], ds = j[4], kind = j[5];
   if (l < a.n_layers) {
     const int n16 = a.head_dim * ELEM / 16;
@@ -203,8 +235,17 @@ __global__ __launch_bounds__(256) void collapse_kernel(CollapseArgs a) {
 hipError_t launch_collapse(const CollapseArgs &a, hipStream_t s) {
   if (a.n_jobs <= 0) return hipSuccess;
   dim3 grid(a.n_jobs, a.n_layers + 1);
-  if (a.elem_bytes == 2) hipLaunchKernelGGL(collapse_kernel<2>, grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(collapse_kernel<4>, grid, dim3(256), 0, s, a);
+  Words<WORDS_SMALL> w{};
+  if (6 * a.n_jobs <= WORDS_SMALL) {
+    std::memcpy(w.v, a.job, (size_t)a.n_jobs * 24);
+    if (a.elem_bytes == 2) hipLaunchKernelGGL((collapse_kernel<2, true>), grid, dim3(256), 0, s, a, w);
+    else hipLaunchKernelGGL((collapse_kernel<4, true>), grid, dim3(256), 0, s, a, w);
+    return hipGetLastError();
+  }
+  const hipError_t e = launch_upload(a.job_dev, a.job, (size_t)a.n_jobs * 6, s);
+  if (e != hipSuccess) return e;
+  if (a.elem_bytes == 2) hipLaunchKernelGGL((collapse_kernel<2, false>), grid, dim3(256), 0, s, a, w);
+  else hipLaunchKernelGGL((collapse_kernel<4, false>), grid, dim3(256), 0, s, a, w);
   return hipGetLastError();
 }
 

@@ -48,3 +48,19 @@ def test_one_split_rows_have_the_bits_of_the_split_kernels(dtype, hd, H, Hkv):
     ref = c.reference(rows)
     err = np.linalg.norm(out - ref, axis=1) / np.linalg.norm(ref, axis=1)
     assert err.max() <= (BF16_RTOL if dtype == 1 else F32_RTOL), err.max()
+
+
+@pytest.mark.parametrize("words", [240, 960])
+def test_row_tables_of_every_upload_size(words):
+    """Row tables of up to 240 and 960 words go to the GPU as kernel arguments
+    of two sizes, longer ones by a copy: a row whose chain entries are the
+    table's last words has the same bits on both sides of either size."""
+    torch = torch_cuda()
+    c = Case(1, 64, 4, 2, [(40, [9])], 4400)
+    _, want = _run(torch, c)
+    chain, coff = c.chain.copy(), c.coff.copy()
+    assert np.linalg.norm(_run(torch, c)[0] - c.reference()) <= BF16_RTOL * np.linalg.norm(c.reference())
+    for pad in range(words - 24, words + 2):            # a one-row table holds 8 words besides its chain
+        c.chain = np.concatenate([np.full(pad, c.E - 1, np.int32), chain])
+        c.coff = coff + np.int32(pad)
+        assert np.array_equal(_run(torch, c)[1], want), pad
