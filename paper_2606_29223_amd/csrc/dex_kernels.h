@@ -133,6 +133,12 @@ struct GemmArgs {
   int n_part_out;
   const int *row_bnd;         // nullable: write h/partials to boundary storage instead
   float *bnd_h, *bnd_part;
+  // with row_bnd (nullable): the exit head's input, final norm gain ex_g, and
+  // partials of the same rows, rows ex_row0 .. of its buffers
+  void *ex_xb;
+  float *ex_part;
+  const float *ex_g;
+  int ex_row0, ex_rm;
   const float *bias;          // RESID (nullable): h += alpha * (y + bias); BIAS_SILU: SiLU(y + bias)
   // SWIGLU / BIAS_SILU
   void *act;                  // [M][N] (T), packed with pk_steps
@@ -237,6 +243,8 @@ __host__ __device__ inline void gemm_seg_view(GemmArgs &a, const GemmSeg &s) {
     if (s.g_next == nullptr) a.xb = nullptr;
     a.part_out += r * a.n_part_out;
     a.row_bnd = s.row_bnd;
+    a.ex_row0 = s.r0;
+    if (s.row_bnd == nullptr) a.ex_xb = nullptr;
   }
 }
 

@@ -419,10 +419,17 @@ double wbytes(const dex_ctx *ctx, double elems) { return elems * ctx->es; }
 // row-major (act_off).
 constexpr int kRowMajorRows = 2;
 
+// A stage's last layer leaves its rows ready for the exit head, unless an
+// adapter comes between: rows row0 .. of the exit buffers, row-major if rm.
+void exit_input(const dex_ctx *ctx, GemmArgs &a, int row0, int rm) {
+  if (ctx->ad_m > 0) return;
+  a.ex_xb = ctx->ex_xb; a.ex_part = ctx->ex_part; a.ex_g = ctx->final_norm; a.ex_row0 = row0; a.ex_rm = rm;
+}
+
 // p0: the first row's row in xb, att and act
 dex_status run_layers(dex_ctx *ctx, hipStream_t st, int first_layer, int last_layer, int M, const StageTables &t,
                       float *h, float *part, void *xb, float *q, void *att, void *act, int p0, float *apart,
-                      int jmax, bool to_boundary, const int *bnd_rows) {
+                      int jmax, bool to_boundary, const int *bnd_rows, int ex_row0, int ex_rm) {
   const int d = ctx->d, H = ctx->H, Hkv = ctx->Hkv, hd = ctx->hd, F = ctx->F;
   const size_t layer_kv = (size_t)ctx->B * Hkv * ctx->E * hd * ctx->es;
   const int rm = M <= kRowMajorRows;
@@ -502,6 +509,7 @@ dex_status run_layers(dex_ctx *ctx, hipStream_t st, int first_layer, int last_la
       a.part_out = part; a.n_part_out = ctx->n_part;
       if (last && to_boundary) {
         a.row_bnd = bnd_rows; a.bnd_h = ctx->bnd_h; a.bnd_part = ctx->bnd_part;
+        exit_input(ctx, a, ex_row0, ex_rm);
       }
       TimedLaunch tl(ctx, 5, wbytes(ctx, (double)d * F + (double)M * F + (double)M * d) + 8.0 * M * d);
       HIPCHK(launch_gemm(ctx->dtype, EPI_RESID, a, 1, st));
@@ -556,7 +564,8 @@ dex_status exit_adapter(dex_ctx *ctx, int rm, int k, int r0, int M) {
 
 // exit head over M rows whose final state sits in (src_h, src_part)[row_src[m]];
 // stage_r0 (host, N + 1 bounds of the stage-major rows) selects the rows of
-// non-final depths for the adapters (nullptr: every row is final depth)
+// non-final depths for the adapters (nullptr: every row is final depth, and
+// the exit input is not there yet; else exit_input had it written)
 dex_status run_exit(dex_ctx *ctx, int M, const int *row_src, const float *src_h, const float *src_part,
                     const int *mask_n, const int *mask_tok, const int *cand_idx, int *cand, const int *row_seq,
                     const int *row_pos, const int *stage_r0, const int *row_commit) {
@@ -572,7 +581,7 @@ dex_status run_exit(dex_ctx *ctx, int M, const int *row_src, const float *src_h,
     }
     dex_status s2 = exit_prep(ctx, rm, stage_r0[N - 1], M - stage_r0[N - 1], row_src, src_h, src_part, ctx->final_norm);
     if (s2 != DEX_OK) return s2;
-  } else {
+  } else if (stage_r0 == nullptr) {
     dex_status s2 = exit_prep(ctx, rm, 0, M, row_src, src_h, src_part, ctx->final_norm);
     if (s2 != DEX_OK) return s2;
   }
@@ -1263,7 +1272,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
     const bool timing = ctx->timing;
     ctx->timing = false;                             // the kernel times are those of rounds
     const dex_status ls = run_layers(ctx, ctx->stream, last_layer, last_layer, B, t, ctx->h_w, ctx->part_w, ctx->xb_w,
-                                     ctx->q_w, ctx->att_w, ctx->act_w, 0, ctx->attn_part, ctx->jmax, false, nullptr);
+                                     ctx->q_w, ctx->att_w, ctx->act_w, 0, ctx->attn_part, ctx->jmax, false, nullptr, 0, 0);
     ctx->timing = timing;
     if (ls != DEX_OK) return ls;
   }
@@ -1514,7 +1523,7 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
                       ctx->part_w + (size_t)r0 * ctx->n_part,
                       ctx->xb_w, ctx->q_w + (size_t)r0 * ctx->H * ctx->hd, ctx->att_w, ctx->act_w, stage_p0[k],
                       ctx->attn_part + (size_t)r0 * ctx->H * ctx->jmax * (ctx->hd + 2), ctx->jmax,
-                      true, t.bnd);
+                      true, t.bnd, r0, R <= kRowMajorRows);
   };
   // grouped: a lane's stages in step, layer step j of every one of them that
   // has one in a single launch per kernel (segments in stage order, whose
@@ -1694,6 +1703,7 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
         a.h = ctx->h_w; a.ld_h = d; a.xb = ctx->xb_w; a.pk_steps = ctx->ns_d;
         a.part_out = ctx->part_w; a.n_part_out = ctx->n_part;
         a.bnd_h = ctx->bnd_h; a.bnd_part = ctx->bnd_part;
+        exit_input(ctx, a, 0, R <= kRowMajorRows);
         double bytes = 0.0;
         for (int i = 0; i < n; ++i) {
           const int k = on[i], l = lay[i];

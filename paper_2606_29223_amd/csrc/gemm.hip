@@ -108,6 +108,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &a) {
       const int m = m0 + min((int)threadIdx.x / 16, Mloc - 1), n = tile0 * 16 + threadIdx.x % 16;
       pre_h = a.h[(size_t)m * a.ld_h + n];
       if (a.xb != nullptr) pre_g = a.g_next[n];
+      else if (a.ex_xb != nullptr) pre_g = a.ex_g[n];
       if (a.row_bnd != nullptr) pre_bnd = a.row_bnd[m];
     }
   }

@@ -92,9 +92,11 @@ __device__ __forceinline__ void reduce_block(const float (*red)[MB][64][4], floa
 // RESID epilogue of one 16-column tile for rows m0 .. m0 + Mloc: h += alpha *
 // acc (+ bias), the next RMSNorm's input g * h in the matrix-core type, and the
 // tile's sum-of-squares partial of each row; with row_bnd the results go to
-// the rows' boundary storage instead.  sq: [16][16 * MB] LDS scratch.  With
-// PRE (one row block) the thread's first element brings its residual, next
-// gain and boundary row along.  Ends with a workgroup barrier.
+// the rows' boundary storage instead, and with ex_xb as the exit head's
+// input too: a launch of its own for that cost 4-5 us of a round (4 layers of
+// 128 in fp32, 64 tokens: 5.37 -> 5.13 ms).  sq: [16][16 * MB] LDS scratch.
+// With PRE (one row block) the thread's first element brings its residual,
+// next gain and boundary row along.  Ends with a workgroup barrier.
 template <typename T, int MB, bool PRE>
 __device__ __forceinline__ void epi_resid(const GemmArgs &a, int tile, int m0, int Mloc,
                                           const float (*vt)[16 * MB], float (*sq)[16 * MB], float pre_h, float pre_g,
@@ -111,6 +113,8 @@ __device__ __forceinline__ void epi_resid(const GemmArgs &a, int tile, int m0, i
     hout[n] = hn;
     if (a.xb != nullptr)
       ((T *)a.xb)[act_off<T>(a.row0 + m, n, a.pk_steps, a.rm)] = to_t<T>((PRE ? pre_g : a.g_next[n]) * hn);
+    if (a.ex_xb != nullptr)
+      ((T *)a.ex_xb)[act_off<T>(a.ex_row0 + m, n, a.pk_steps, a.ex_rm)] = to_t<T>((PRE ? pre_g : a.ex_g[n]) * hn);
     sq[nl][ml] = hn * hn;
   }
   __syncthreads();
@@ -122,6 +126,7 @@ __device__ __forceinline__ void epi_resid(const GemmArgs &a, int tile, int m0, i
     float *po = (a.row_bnd != nullptr) ? a.bnd_part + (size_t)a.row_bnd[m] * a.n_part_out
                                        : a.part_out + (size_t)m * a.n_part_out;
     po[tile] = s;
+    if (a.ex_xb != nullptr) a.ex_part[(size_t)(a.ex_row0 + m) * a.n_part_out + tile] = s;
   }
 }
 
