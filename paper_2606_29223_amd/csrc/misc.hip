@@ -146,8 +146,9 @@ __global__ __launch_bounds__(AMAX_THREADS) void argmax_kernel(ArgmaxArgs a) {
   __syncthreads();
   if (tid == 0) {
     for (int w = 1; w < AMAX_THREADS / 64; ++w) amax_take(bv, bi, sv[w], si[w]);
-    // the results go straight to host memory: a copy command behind this
-    // kernel took 6 us of a round
+    // the results go straight to host memory: a copy kernel behind this one
+    // took 4.6 us of a round (with the tables as arguments, 4 layers of 128 in
+    // fp32, 64 tokens: 5.61 -> 5.37 ms)
     __hip_atomic_store(a.u_out + m, bi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (a.cand != nullptr) a.cand[a.row_cand[m]] = bi;
     // Validate and commit (Section 3.2, commit process) when this row is an
@@ -172,9 +173,10 @@ hipError_t launch_argmax(const ArgmaxArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// A few words as a kernel argument: a launch is a third of what the host and
-// the stream spend on a copy command of this size (6 us), and most tables of
-// a round fit.  960 words are the most that the 4 KB of arguments hold.
+// A few words as a kernel argument: 2.4 us on the stream, where the runtime's
+// copy of this size took 4.6 us and, from pageable memory, host time besides
+// (stand-alone attention at 700 keys: 37 -> 35 us a call).  Most tables of a
+// round fit; 960 words are the most that the 4 KB of arguments hold.
 template <int N> struct Words { int v[N]; };
 constexpr int WORDS_SMALL = 240, WORDS_MAX = 960;
 template <int N>
