@@ -275,11 +275,11 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_kernel(AttnArgs a) {
 #ifndef CMB_WAVES
 #define CMB_WAVES 4
 #endif
-template <typename T, int HD, int DW>
+template <typename T, typename REC, int HD, int DW>
 __global__ __launch_bounds__(64 * CMB_WAVES) void combine_kernel(CombineArgs a) {
   // dimensions per lane: 4-byte record loads for bf16 (whole heads: 64
   // lanes x 2; half heads: 32 lanes x 2)
-  constexpr int DPL = sizeof(T) == 2 ? (DW >= 128 ? DW / 64 : 2) : (DW >= 64 ? DW / 64 : 1);
+  constexpr int DPL = sizeof(REC) == 2 ? (DW >= 128 ? DW / 64 : 2) : (DW >= 64 ? DW / 64 : 1);
   constexpr int CH = 16;                       // splits per value chunk
   constexpr int NT = 64 * CMB_WAVES;
   extern __shared__ float ws[];                // [jmax] split weights
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(64 * CMB_WAVES) void combine_kernel(CombineArgs a) 
   const int r = blockIdx.x, h = blockIdx.y, tid = threadIdx.x, lane = tid & 63, s = tid >> 6;
   const int nsplit = a.row_pos[r] / ATT_SPLIT + 1;
   const int nmine = nsplit > s ? (nsplit - s + CMB_WAVES - 1) / CMB_WAVES : 0;
-  const T *src = (const T *)a.part + ((size_t)r * a.n_heads + h) * a.jmax * HD;
+  const REC *src = (const REC *)a.part + ((size_t)r * a.n_heads + h) * a.jmax * HD;
   const float *sst = a.stat + ((size_t)r * a.n_heads + h) * a.jmax * 2;
   const int dl = lane * DPL;                   // this lane's first dimension in the slice
   const int d0 = blockIdx.z * DW + dl;
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(64 * CMB_WAVES) void combine_kernel(CombineArgs a) 
 #pragma unroll
     for (int jj = 0; jj < CH; ++jj) {
       const int j = s + (i0 + jj) * CMB_WAVES;
-      rec_load<T, DPL>(src + (size_t)j * HD + d0, dok && i0 + jj < nmine, v[jj]);
+      rec_load<REC, DPL>(src + (size_t)j * HD + d0, dok && i0 + jj < nmine, v[jj]);
     }
   };
   load_chunk(0, va);
@@ -439,20 +439,20 @@ static hipError_t launch_attn_t(const AttnArgs &a, const AttnSegs *g, dim3 grid,
   return hipGetLastError();
 }
 
-template <typename T>
+template <typename T, typename REC>
 static hipError_t launch_comb_t(const CombineArgs &a, int rows, hipStream_t s) {
   const size_t smem = (size_t)a.jmax * 4;
   const dim3 block(64 * CMB_WAVES);
   switch (a.head_dim) {
-    case 32: hipLaunchKernelGGL((combine_kernel<T, 32, 32>), dim3(rows, a.n_heads), block, smem, s, a); break;
-    case 64: hipLaunchKernelGGL((combine_kernel<T, 64, 64>), dim3(rows, a.n_heads), block, smem, s, a); break;
+    case 32: hipLaunchKernelGGL((combine_kernel<T, REC, 32, 32>), dim3(rows, a.n_heads), block, smem, s, a); break;
+    case 64: hipLaunchKernelGGL((combine_kernel<T, REC, 64, 64>), dim3(rows, a.n_heads), block, smem, s, a); break;
     case 128:
       // up to 512 (row, head) pairs: half a head per workgroup (latency-bound
       // launches); beyond, a whole head (bandwidth-bound, fewer statistics reads)
       if ((size_t)rows * a.n_heads <= 512)
-        hipLaunchKernelGGL((combine_kernel<T, 128, 64>), dim3(rows, a.n_heads, 2), block, smem, s, a);
+        hipLaunchKernelGGL((combine_kernel<T, REC, 128, 64>), dim3(rows, a.n_heads, 2), block, smem, s, a);
       else
-        hipLaunchKernelGGL((combine_kernel<T, 128, 128>), dim3(rows, a.n_heads, 1), block, smem, s, a);
+        hipLaunchKernelGGL((combine_kernel<T, REC, 128, 128>), dim3(rows, a.n_heads, 1), block, smem, s, a);
       break;
     default: return hipErrorInvalidValue;
   }
@@ -462,20 +462,19 @@ static hipError_t launch_comb_t(const CombineArgs &a, int rows, hipStream_t s) {
 hipError_t launch_combine(int dtype, const CombineArgs &a, int rows, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   if (a.jmax > ATT_MAX_SPLITS) return hipErrorInvalidValue;
-  return dtype == 1 ? launch_comb_t<bf16>(a, rows, s) : launch_comb_t<float>(a, rows, s);
+  if (dtype != 1) return launch_comb_t<float, float>(a, rows, s);
+  return a.rec_f32 ? launch_comb_t<bf16, float>(a, rows, s) : launch_comb_t<bf16, bf16>(a, rows, s);
 }
-
-
 
 // ------------------------------------------------------------------------
 // Decode attention on the matrix cores (bf16 caches, head_dim 64 or 128): one
 // wave per work item (attn_mfma_item in attn_decode.h).
-template <int HD>
+template <int HD, typename REC>
 __global__ __launch_bounds__(64) void attn_mfma_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t vr[ATT_SPLIT][HD + 16];
   __shared__ int prow[ATT_MAX_PAIRS];
   __shared__ int ppos[ATT_MAX_PAIRS];
-  attn_mfma_item<HD>(a, blockIdx.x, blockIdx.y, vr, prow, ppos);
+  attn_mfma_item<HD, REC>(a, blockIdx.x, blockIdx.y, vr, prow, ppos);
 }
 
 // Grouped form: block x runs item x - item0 of the segment whose items hold it.
@@ -486,7 +485,7 @@ __global__ __launch_bounds__(64) void attn_mfma_seg_kernel(AttnArgs a, AttnSegs 
   __shared__ int ppos[ATT_MAX_PAIRS];
   const int x = blockIdx.x, k = find_seg(g, x);
   attn_seg_view<bf16>(a, g.s[k]);
-  attn_mfma_item<HD>(a, x - g.item0[k], blockIdx.y, vr, prow, ppos);
+  attn_mfma_item<HD, bf16>(a, x - g.item0[k], blockIdx.y, vr, prow, ppos);
 }
 
 // Causal prompt attention on the matrix cores (bf16, head_dim 64 or 128).
@@ -757,17 +756,25 @@ hipError_t launch_prefill_attention(const PrefillAttnArgs &a, hipStream_t s) {
   }
 }
 
+static bool mfma_attention(int dtype, int head_dim) { return dtype == 1 && (head_dim == 64 || head_dim == 128); }
+
 hipError_t launch_attention(int dtype, const AttnArgs &a, int n_groups, hipStream_t s) {
   if (n_groups <= 0 || a.n_heads / a.n_kv_heads > 8) return hipErrorInvalidValue;
   if (a.n_splits < 1 || a.n_splits > a.jmax) return hipErrorInvalidValue;
   dim3 grid(n_groups, a.n_kv_heads, a.n_splits);
-  if (dtype == 1 && (a.head_dim == 128 || a.head_dim == 64)) {
+  if (a.rec_f32 && !mfma_attention(dtype, a.head_dim)) return hipErrorInvalidValue;
+  if (mfma_attention(dtype, a.head_dim)) {
     if (a.n_rows < 1 || a.row_seq == nullptr) return hipErrorInvalidValue;
     const size_t items = 2 * (size_t)a.n_rows + (size_t)n_groups * a.n_splits;
     if (items > 0x7fffffffull) return hipErrorInvalidValue;
     dim3 g2((unsigned)items, a.n_kv_heads);
-    if (a.head_dim == 128) hipLaunchKernelGGL(attn_mfma_kernel<128>, g2, dim3(64), 0, s, a);
-    else hipLaunchKernelGGL(attn_mfma_kernel<64>, g2, dim3(64), 0, s, a);
+    if (a.rec_f32) {
+      if (a.head_dim == 128) hipLaunchKernelGGL((attn_mfma_kernel<128, float>), g2, dim3(64), 0, s, a);
+      else hipLaunchKernelGGL((attn_mfma_kernel<64, float>), g2, dim3(64), 0, s, a);
+    } else {
+      if (a.head_dim == 128) hipLaunchKernelGGL((attn_mfma_kernel<128, bf16>), g2, dim3(64), 0, s, a);
+      else hipLaunchKernelGGL((attn_mfma_kernel<64, bf16>), g2, dim3(64), 0, s, a);
+    }
     return hipGetLastError();
   }
   return dtype == 1 ? launch_attn_t<bf16>(a, nullptr, grid, s) : launch_attn_t<float>(a, nullptr, grid, s);
@@ -775,7 +782,7 @@ hipError_t launch_attention(int dtype, const AttnArgs &a, int n_groups, hipStrea
 
 // Up to MAX_SEGS segments per launch, a lone segment as a plain launch.
 hipError_t launch_attention_seg(int dtype, const AttnArgs &a, const AttnSeg *segs, int n, hipStream_t s) {
-  if (segs == nullptr || n < 1 || a.n_heads / a.n_kv_heads > 8) return hipErrorInvalidValue;
+  if (segs == nullptr || n < 1 || a.n_heads / a.n_kv_heads > 8 || a.rec_f32) return hipErrorInvalidValue;
   for (int i = 0; i < n; ++i) {
     const AttnSeg &sg = segs[i];
     if (sg.M < 1 || sg.r0 < 0 || sg.g0 < 0 || sg.n_groups < 1 || sg.n_splits < 1 || sg.n_splits > a.jmax)
@@ -832,11 +839,11 @@ hipError_t launch_attention_seg(int dtype, const AttnArgs &a, const AttnSeg *seg
 // longer rows keep the split kernels.  Every number is computed as there --
 // the same products, statistics, bf16 records, and the combine's own order of
 // additions -- so a row's bits do not depend on which of the two ran.
-template <int HD, int NS>
+template <int HD, int NS, typename REC>
 __device__ __forceinline__ void attn_short_row(const AttnArgs &a, const CombineArgs &c, int r, int kvh) {
   constexpr int KS = HD / 32, DT = HD / 16, NKT = ATT_SPLIT / 16, V4 = HD / 8, RPI = 64 / V4;
   __shared__ __attribute__((aligned(16))) uint16_t vr[NS][ATT_SPLIT][HD + 16];
-  __shared__ __attribute__((aligned(16))) uint16_t rec[NS][8][HD];
+  __shared__ __attribute__((aligned(16))) REC rec[NS][8][HD];
   __shared__ float2 stat[NS][8];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r16 = lane & 15, grp = lane >> 4;
@@ -941,9 +948,7 @@ __device__ __forceinline__ void attn_short_row(const AttnArgs &a, const CombineA
     }
     if (pok) {
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        *(uint2 *)&rec[wave][r16][16 * dt + 4 * grp] =
-            make_uint2(pf_pack_bf16(o[dt][0], o[dt][1]), pf_pack_bf16(o[dt][2], o[dt][3]));
+      for (int dt = 0; dt < DT; ++dt) rec_store4(&rec[wave][r16][16 * dt + 4 * grp], o[dt]);
       if (grp == 0) stat[wave][r16] = make_float2(mx, sum);
     }
   }
@@ -963,10 +968,11 @@ __device__ __forceinline__ void attn_short_row(const AttnArgs &a, const CombineA
     for (int j = 0; j < NS; ++j)
       if (j < nsplit) {
         const float w = expf(stat[j][h].x - M);
-        const uint32_t u = *(const uint32_t *)&rec[j][h][d0];
+        float o2[2];
+        rec_load<REC, 2>(&rec[j][h][d0], true, o2);
         lp[j] = fmaf(w, stat[j][h].y, 0.f);
-        v0[j] = fmaf(w, __uint_as_float(u << 16), 0.f);
-        v1[j] = fmaf(w, __uint_as_float(u & 0xffff0000u), 0.f);
+        v0[j] = fmaf(w, o2[0], 0.f);
+        v1[j] = fmaf(w, o2[1], 0.f);
       }
     const float l = (lp[0] + lp[2]) + (lp[1] + lp[3]);   // the wave butterfly's order
     const uint32_t lo = pf_f2bf((v0[0] + v0[1] + v0[2] + v0[3]) / l), hi = pf_f2bf((v1[0] + v1[1] + v1[2] + v1[3]) / l);
@@ -977,9 +983,9 @@ __device__ __forceinline__ void attn_short_row(const AttnArgs &a, const CombineA
   }
 }
 
-template <int HD, int NS>
+template <int HD, int NS, typename REC>
 __global__ __launch_bounds__(64 * NS) void attn_short_kernel(AttnArgs a, CombineArgs c, int row0) {
-  attn_short_row<HD, NS>(a, c, row0 + blockIdx.x, blockIdx.y);
+  attn_short_row<HD, NS, REC>(a, c, row0 + blockIdx.x, blockIdx.y);
 }
 
 // Grouped form: block x is row x - item0 of the segment that holds it.
@@ -988,7 +994,7 @@ __global__ __launch_bounds__(64 * NS) void attn_short_seg_kernel(AttnArgs a, Com
   const int x = blockIdx.x, k = find_seg(g, x);
   a.kc = g.s[k].kc;
   a.vc = g.s[k].vc;
-  attn_short_row<HD, NS>(a, c, g.s[k].r0 + x - g.item0[k], blockIdx.y);
+  attn_short_row<HD, NS, bf16>(a, c, g.s[k].r0 + x - g.item0[k], blockIdx.y);
 }
 
 template <int HD, int NS>
@@ -999,8 +1005,9 @@ static hipError_t launch_short_t(const AttnArgs &a, const CombineArgs &c, const 
       AttnArgs b = a;
       b.kc = segs[i0].kc;
       b.vc = segs[i0].vc;
-      hipLaunchKernelGGL((attn_short_kernel<HD, NS>), dim3(segs[i0].M, a.n_kv_heads), dim3(64 * NS), 0, s, b, c,
-                         segs[i0].r0);
+      const dim3 grid(segs[i0].M, a.n_kv_heads), block(64 * NS);
+      if (a.rec_f32) hipLaunchKernelGGL((attn_short_kernel<HD, NS, float>), grid, block, 0, s, b, c, segs[i0].r0);
+      else hipLaunchKernelGGL((attn_short_kernel<HD, NS, bf16>), grid, block, 0, s, b, c, segs[i0].r0);
     } else {
       AttnSegs g{};
       g.n = cnt;
@@ -1050,8 +1057,6 @@ static hipError_t launch_one_t(const AttnArgs &a, const CombineArgs &c, const At
   return hipSuccess;
 }
 
-static bool mfma_attention(int dtype, int head_dim) { return dtype == 1 && (head_dim == 64 || head_dim == 128); }
-
 bool attention_short_supported(int dtype, const AttnArgs &a, const AttnSeg *segs, int n) {
   return short_splits(segs, n) <= (mfma_attention(dtype, a.head_dim) ? SHORT_SPLITS : 1);
 }
@@ -1059,7 +1064,7 @@ bool attention_short_supported(int dtype, const AttnArgs &a, const AttnSeg *segs
 hipError_t launch_attention_short(int dtype, const AttnArgs &a, const CombineArgs &c, const AttnSeg *segs, int n,
                                   hipStream_t s) {
   if (segs == nullptr || n < 1 || a.row_seq == nullptr || a.n_heads / a.n_kv_heads > 8 ||
-      !attention_short_supported(dtype, a, segs, n))
+      !attention_short_supported(dtype, a, segs, n) || (a.rec_f32 && (n > 1 || !mfma_attention(dtype, a.head_dim))))
     return hipErrorInvalidValue;
   for (int i = 0; i < n; ++i)
     if (segs[i].M < 1 || segs[i].r0 < 0 || segs[i].n_splits < 1 || segs[i].g0 < 0 || segs[i].n_groups < 1)

@@ -33,6 +33,12 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+// Four consecutive elements of a split record.
+__device__ __forceinline__ void rec_store4(bf16 *dst, const pf_f32x4 &o) {
+  *(uint2 *)dst = make_uint2(pf_pack_bf16(o[0], o[1]), pf_pack_bf16(o[2], o[3]));
+}
+__device__ __forceinline__ void rec_store4(float *dst, const pf_f32x4 &o) { *(pf_f32x4 *)dst = o; }
+
 // LDS written by some lanes of a wave and read by others: the wave's LDS
 // operations complete in order once counted out; no other wave takes part.
 __device__ __forceinline__ void wave_lds_sync() {
@@ -100,7 +106,7 @@ __device__ __forceinline__ pf_bf16x8 tr_frag(const uint16_t *lo, const uint16_t 
   return __builtin_bit_cast(pf_bf16x8, make_uint4(ua.x, ua.y, ub.x, ub.y));
 }
 
-template <int HD>
+template <int HD, typename REC>
 __device__ void attn_mfma_item(const AttnArgs &a, int item, int kvh, uint16_t (*vr)[HD + 16], int *prow, int *ppos) {
   constexpr int KS = HD / 32;                 // k-steps of S over head dims
   constexpr int DT = HD / 16;                 // 16-dim tiles of O
@@ -299,14 +305,13 @@ __device__ void attn_mfma_item(const AttnArgs &a, int item, int kvh, uint16_t (*
             tr_frag(&vr[32 * st + 4 * tq + ti][16 * dt + 4 * tg], &vr[32 * st + 16 + 4 * tq + ti][16 * dt + 4 * tg]),
             pfr, o[dt], 0, 0, 0);
     }
-    // pair pa's record: O[pa][16 dt + 4 grp .. + 3] rounded to bf16, one
-    // 8-byte store per tile, and its statistics from the first quarter
+    // pair pa's record: O[pa][16 dt + 4 grp .. + 3] (REC bf16: rounded), one
+    // store per tile, and its statistics from the first quarter
     if (pok) {
       const size_t rec = ((size_t)(r0 + prow[pa / G]) * a.n_heads + kvh * G + pa % G) * a.jmax + split;
-      uint16_t *dst = (uint16_t *)a.part + rec * HD + 4 * grp;
+      REC *dst = (REC *)a.part + rec * HD + 4 * grp;
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        *(uint2 *)(dst + 16 * dt) = make_uint2(pf_pack_bf16(o[dt][0], o[dt][1]), pf_pack_bf16(o[dt][2], o[dt][3]));
+      for (int dt = 0; dt < DT; ++dt) rec_store4(dst + 16 * dt, o[dt]);
       if (grp == 0) *(float2 *)(a.stat + 2 * rec) = make_float2(mx, sum);
     }
   }

@@ -173,11 +173,12 @@ struct AttnArgs {
   const int *row_pos, *row_nc, *row_chain_off, *chain;
   const int *row_seq;         // sequence of each row (matrix-core kernel)
   int n_rows;                 // rows of the launch (matrix-core kernel)
-  void *part;                 // [R][H][jmax][hd] split outputs o (element type of the cache)
+  void *part;                 // [R][H][jmax][hd] split outputs o (element type of the cache, or float)
   float *stat;                // [R][H][jmax][2] their (max, sum)
   int jmax;                   // split stride of `part` and `stat`
   int n_splits;               // splits the launch covers: max over its rows of pos / 64 + 1 (<= jmax)
   float scale;
+  int rec_f32;                // matrix-core kernels: float records (plain launches only)
 };
 
 struct CombineArgs {
@@ -185,6 +186,7 @@ struct CombineArgs {
   const float *stat;
   const int *row_pos;
   int jmax, n_heads, head_dim;
+  int rec_f32;                // as AttnArgs
   void *out;                  // [R][H*hd] (T): an activation buffer of out_steps k-steps,
   int ld_out;                 // or rows ld_out apart where out_steps is 0
   int out_steps;

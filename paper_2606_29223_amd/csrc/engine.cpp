@@ -411,6 +411,7 @@ struct StageTables {
   int n_groups;
   int n_splits;         // 64-key splits up to the stage's deepest row
   double attn_bytes;    // keys/values a layer's attention reads (algorithmic)
+  int rec_f32;          // split outputs kept in fp32 (AttnArgs)
 };
 
 double wbytes(const dex_ctx *ctx, double elems) { return elems * ctx->es; }
@@ -459,10 +460,10 @@ dex_status run_layers(dex_ctx *ctx, hipStream_t st, int first_layer, int last_la
       a.row_pos = t.pos; a.row_nc = t.nc; a.row_chain_off = t.chain_off; a.chain = t.chain;
       a.row_seq = t.seq; a.n_rows = M;
       a.part = apart; a.stat = split_stats(apart, M, H, jmax, hd);
-      a.jmax = jmax; a.n_splits = t.n_splits; a.scale = 1.0f / std::sqrt((float)hd);
+      a.jmax = jmax; a.n_splits = t.n_splits; a.scale = 1.0f / std::sqrt((float)hd); a.rec_f32 = t.rec_f32;
       CombineArgs c{};
       c.part = apart; c.stat = a.stat;
-      c.row_pos = t.pos; c.jmax = jmax; c.n_heads = H; c.head_dim = hd;
+      c.row_pos = t.pos; c.jmax = jmax; c.n_heads = H; c.head_dim = hd; c.rec_f32 = t.rec_f32;
       c.out = att; c.out_steps = ctx->ns_hhd; c.row0 = p0; c.rm = rm;
       const AttnSeg seg{a.kc, a.vc, 0, M, 0, t.n_groups, t.n_splits};
       const bool one = attention_short_supported(ctx->dtype, a, &seg, 1);
@@ -1269,6 +1270,10 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
     t.seq = d_exseq; t.pos = d_expos; t.entry = d_expos; t.nc = dev(ex_nc); t.chain_off = d_exzero; t.chain = d_exzero;
     t.g_row0 = d_exseq; t.g_nrows = dev(ex_one); t.g_seq = d_exseq; t.g_nc = dev(ex_nc);
     t.n_groups = B; t.n_splits = jmax;
+    // the attention of every other position keeps its sum over all keys in
+    // fp32, and so does this one: bf16 records (of a round's rows) would
+    // round it at every 64 keys
+    t.rec_f32 = mfma_prefill;
     const bool timing = ctx->timing;
     ctx->timing = false;                             // the kernel times are those of rounds
     const dex_status ls = run_layers(ctx, ctx->stream, last_layer, last_layer, B, t, ctx->h_w, ctx->part_w, ctx->xb_w,

@@ -129,3 +129,52 @@ def test_keys_have_the_same_bits_at_every_row_count(name):
         want = want or got
         for a, b in zip(got, want):
             assert torch.equal(a, b[:, :P]), P
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("P,B", [(46, 1), (60, 3), (200, 2), (2100, 2)])
+def test_first_token_attends_with_fp32_partial_sums(hd, P, B):
+    """Every row's attention is a plain mean of the values here (no query),
+    each value +-1 +- 1/64, and the parts of size 1 cancel over the whole
+    prompt but not within 64 keys: an output rounded to bf16 before all keys
+    are in is off by about a tenth, one rounded at the end by 2^-9.  Logits
+    are the final state's own components, so y_0's row shows the output."""
+    torch = torch_cuda()
+    from paper_2606_29223_amd import dexlib
+    H, Hkv, V = 4, 2, 1024
+    d, half = H * hd, V // 2
+    rng = np.random.default_rng(100 * hd + P)
+    x = rng.choice([-1.0, 1.0], size=(V, d))
+    x[half:, d // 2:] = x[:half, d // 2:]        # token t + half: t with its first components negated
+    x[half:, :d // 2] = -x[:half, :d // 2]
+    wv = np.zeros((Hkv * hd, d))
+    i = np.arange(Hkv * hd)
+    wv[i, i % (d // 2)] = 1.0
+    wv[i, d // 2 + rng.permutation(d // 2)[i % (d // 2)]] = 1.0 / 64
+    alpha = 2.0 ** round(np.log2(8 * 64 * np.sqrt(P / 2.0)))
+    cfg = dict(configs.get("small-12L-d768-bf16"), n_layers=1, d_model=d, n_heads=H, n_kv_heads=Hkv, head_dim=hd,
+               d_ffn=16, vocab=V, rms_eps=1e-12, residual_scale=alpha, prompt_len=P, batch=B, explored=[1])
+    z = lambda *s: np.zeros(s)  # noqa: E731
+    one = torch.ones(d, device="cuda")
+    mats = {"embed": x, "lm_head": np.eye(V, d), "layers.0.wq": z(d, d), "layers.0.wk": z(Hkv * hd, d),
+            "layers.0.wv": wv, "layers.0.wo": np.eye(d), "layers.0.w_gate": z(16, d), "layers.0.w_up": z(16, d),
+            "layers.0.w_down": z(d, 16)}
+    w = {n: torch.as_tensor(m, dtype=torch.bfloat16, device="cuda") for n, m in mats.items()}
+    w.update({"final_norm": one, "layers.0.attn_norm": one, "layers.0.ffn_norm": one})
+    prompts = np.empty((B, P), np.int32)
+    prompts[:, :P // 2] = rng.integers(0, half, (B, P // 2))
+    prompts[:, P // 2:] = prompts[:, :P // 2] + half
+    dec = dexlib.Decoder(cfg, w, width_cap=1, batch=B, max_context=P + 2)
+    tap = torch.zeros((B, V), dtype=torch.float32, device="cuda")
+    dec.set_logits_tap(tap)
+    dec.prefill(prompts)
+    got = tap.cpu().numpy()[:, :d].astype(np.float64)
+    dec.close()
+    for b in range(B):
+        att = np.repeat((x[prompts[b]] @ wv.T).mean(0).reshape(Hkv, hd), H // Hkv, axis=0).reshape(-1)
+        h = x[prompts[b, -1]] + alpha * att
+        r = 1.0 / np.sqrt(np.mean(h * h))
+        # att and the head's input are each rounded to bf16 (2^-9 of the value), which moves the
+        # scale r by as much at most; a tenth for the fp32 operations beside them
+        bound = 1.1 * 2.0 ** -9 * r * (alpha * np.abs(att) + 2 * np.abs(h)) + 1e-6
+        assert (np.abs(got[b] - r * h) <= bound).all(), (np.abs(got[b] - r * h) / bound).max()
