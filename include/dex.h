@@ -34,7 +34,13 @@
  *     gains stay borrowed: keep them alive and unchanged until dex_destroy
  *     (the caller's projection and LM-head arrays may be freed once
  *     dex_create has returned).  The library also owns the key/value caches,
- *     the lattice state and all scratch memory.
+ *     the lattice state and all scratch memory.  A context's first
+ *     dex_prefill allocates prompt scratch (activations of about 8192 prompt
+ *     rows at a time, or of one longer prompt: 0.65 GB at d_model 4096, d_ffn
+ *     14336), and the context holds up to 1 GiB of it, with 1 MiB of pinned
+ *     host memory, for further prompts until dex_destroy; a larger one is
+ *     freed before dex_prefill returns.  Plan for it where several contexts
+ *     share a GPU or memory is allocated after a prompt.
  *   - Host arrays passed in or out are caller-owned and only accessed during
  *     the call.
  *   - All device work is enqueued on config.hip_stream (NULL = the default

@@ -167,11 +167,10 @@ struct dex_ctx {
   // pinned host staging
   int *tab_host = nullptr, *job_host = nullptr;
   int *res_host = nullptr;       // [R] decoded candidates, then [2 * commits] (token, k*); the GPU writes it
-  // prompt scratch and its pinned row tables, kept between prompts
+  // prompt scratch and pinned row tables, kept between prompts
   void *pf_dev = nullptr;
   size_t pf_bytes = 0;
-  int *pf_host = nullptr;
-  size_t pf_ints = 0;
+  int *pf_host = nullptr;        // kPrefillPinned ints, or none yet
   // state
   std::vector<Seq> seqs;
   bool prefilled = false;
@@ -238,13 +237,16 @@ void dfree(dex_ctx *ctx, void *p) {
   (void)hipFree(p);
 }
 
-// Prompt scratch of at least `bytes` on the device and `ints` pinned on the
-// host.  A context keeps it from prompt to prompt (allocating and freeing cost
-// about 0.1 ms of a 0.8 ms prompt) up to kPrefillKeep bytes, and frees what
-// is larger when the call is done.
+// Prompt scratch of at least `bytes` on the device and room for `ints` row
+// table entries on the host.  A context keeps the scratch from prompt to prompt
+// (allocating and freeing cost about 0.1 ms of a 0.8 ms prompt) up to
+// kPrefillKeep bytes, and frees what is larger when the call is done.  Tables
+// of up to kPrefillPinned ints (87 thousand rows; 1 MiB) go into a pinned
+// buffer that it keeps too, longer ones into `pageable`, the caller's.
 constexpr int kPrefillRows = 8192;
 constexpr size_t kPrefillKeep = 1ull << 30;
-dex_status prefill_room(dex_ctx *ctx, size_t bytes, size_t ints) {
+constexpr size_t kPrefillPinned = 1u << 18;
+dex_status prefill_room(dex_ctx *ctx, size_t bytes, size_t ints, std::vector<int> &pageable, int **tables) {
   if (ctx->pf_bytes < bytes) {
     dfree(ctx, ctx->pf_dev);
     ctx->pf_dev = nullptr;
@@ -253,18 +255,26 @@ dex_status prefill_room(dex_ctx *ctx, size_t bytes, size_t ints) {
     if (st != DEX_OK) return st;
     ctx->pf_bytes = bytes;
   }
-  if (ctx->pf_ints < ints) {
-    if (ctx->pf_host) (void)hipHostFree(ctx->pf_host);
-    ctx->pf_host = nullptr;
-    ctx->pf_ints = 0;
-    const hipError_t e = hipHostMalloc((void **)&ctx->pf_host, ints * 4);
+  if (ints > kPrefillPinned) {
+    try {
+      pageable.resize(ints);
+    } catch (const std::bad_alloc &) {
+      ctx->err = "out of host memory for the prompt tables";
+      return DEX_E_NOMEM;
+    }
+    *tables = pageable.data();
+    return DEX_OK;
+  }
+  if (ctx->pf_host == nullptr) {
+    const hipError_t e = hipHostMalloc((void **)&ctx->pf_host, kPrefillPinned * 4);
     if (e != hipSuccess) {
+      (void)hipGetLastError();
       ctx->pf_host = nullptr;
       ctx->err = std::string("hipHostMalloc of the prompt tables failed: ") + hipGetErrorString(e);
       return DEX_E_NOMEM;
     }
-    ctx->pf_ints = ints;
   }
+  *tables = ctx->pf_host;
   return DEX_OK;
 }
 void prefill_trim(dex_ctx *ctx) {
@@ -1114,8 +1124,13 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
                o_xb = room(blocks * ctx->ns_d * 1024), o_q = room(rows * H * hd * 4),
                o_att = room(blocks * ctx->ns_hhd * 1024), o_act = room(blocks * ctx->ns_F * 1024),
                o_rsc = room(rows * 4), o_apart = room(mfma_prefill ? 0 : chunk * per_row);
-  const dex_status rs = prefill_room(ctx, slab, tab_ints);
-  if (rs != DEX_OK) return rs;                  // nothing changed yet: not poisoned
+  std::vector<int> pageable;
+  int *T = nullptr;
+  const dex_status rs = prefill_room(ctx, slab, tab_ints, pageable, &T);
+  if (rs != DEX_OK) {                           // nothing changed yet: not poisoned
+    prefill_trim(ctx);
+    return rs;
+  }
   char *base = (char *)ctx->pf_dev;
   float *h = (float *)(base + o_h), *part = (float *)(base + o_part), *q = (float *)(base + o_q),
         *rsc = (float *)(base + o_rsc), *apart = (float *)(base + o_apart);
@@ -1123,7 +1138,6 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
 
   // row tables: rows ordered (seq, position); then per sequence the tables of
   // its last row; then what only the split kernel reads
-  int *T = ctx->pf_host;
   int *t_seq = T, *t_pos = t_seq + M, *t_tok = t_pos + M;
   int *ex_src = t_tok + M, *ex_zero = ex_src + B, *ex_cidx = ex_zero + B, *ex_seq = ex_cidx + B, *ex_pos = ex_seq + B,
       *ex_one = ex_pos + B, *ex_nc = ex_one + B;

@@ -178,3 +178,30 @@ def test_first_token_attends_with_fp32_partial_sums(hd, P, B):
         # scale r by as much at most; a tenth for the fp32 operations beside them
         bound = 1.1 * 2.0 ** -9 * r * (alpha * np.abs(att) + 2 * np.abs(h)) + 1e-6
         assert (np.abs(got[b] - r * h) <= bound).all(), (np.abs(got[b] - r * h) / bound).max()
+
+
+def _pinned_bytes(torch):
+    """GPU driver mappings of this process beyond the device memory in use."""
+    spans = [line.split()[0].split("-") for line in open("/proc/self/maps") if "/dev/dri/renderD" in line]
+    free, total = torch.cuda.mem_get_info()
+    return sum(int(hi, 16) - int(lo, 16) for lo, hi in spans) - (total - free)
+
+
+def test_prompt_keeps_no_host_memory_that_grows_with_it():
+    """Row tables of a million prompt rows (12 MB) are gone after the call: a
+    context keeps 1 MiB of pinned tables at most."""
+    torch = torch_cuda()
+    from paper_2606_29223_amd import dexlib
+    B, P = 64, 16384
+    cfg = configs.scaled_down(configs.get("small-12L-d768-bf16"), n_layers=1, d_model=64, d_ffn=64, vocab=512)
+    cfg.update(n_heads=1, n_kv_heads=1, head_dim=64, prompt_len=P)
+    w = dexlib.device_weights(cfg, gen.generate_model(cfg))
+    dec = dexlib.Decoder(cfg, w, explored=[1], width_cap=1, batch=B, max_context=P + 2)
+    long = np.random.default_rng(4).integers(0, 512, (B, P)).astype(np.int32)
+    short = np.ascontiguousarray(long[:, :64])
+    first = dec.prefill(short)
+    before = _pinned_bytes(torch)
+    dec.prefill(long)
+    assert np.array_equal(dec.prefill(short), first)
+    assert _pinned_bytes(torch) - before < 4 << 20
+    dec.close()
