@@ -218,10 +218,18 @@ void hip_failed(dex_ctx *ctx, const char *expr, hipError_t e) {
     }                                                                         \
   } while (0)
 
+// An allocation that failed, reported by the caller: the error must not stay
+// behind for the check after the next launch.
+bool alloc_failed(hipError_t e) {
+  if (e == hipSuccess) return false;
+  (void)hipGetLastError();
+  return true;
+}
+
 dex_status dalloc(dex_ctx *ctx, void **p, size_t bytes) {
   if (bytes == 0) bytes = 16;
   hipError_t e = hipMalloc(p, bytes);
-  if (e != hipSuccess) {
+  if (alloc_failed(e)) {
     ctx->err = "hipMalloc of " + std::to_string(bytes) + " bytes failed: " + hipGetErrorString(e);
     *p = nullptr;
     return DEX_E_NOMEM;
@@ -267,8 +275,7 @@ dex_status prefill_room(dex_ctx *ctx, size_t bytes, size_t ints, std::vector<int
   }
   if (ctx->pf_host == nullptr) {
     const hipError_t e = hipHostMalloc((void **)&ctx->pf_host, kPrefillPinned * 4);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
+    if (alloc_failed(e)) {
       ctx->pf_host = nullptr;
       ctx->err = std::string("hipHostMalloc of the prompt tables failed: ") + hipGetErrorString(e);
       return DEX_E_NOMEM;
@@ -950,10 +957,10 @@ dex_status dex_create(const dex_model *m, const dex_config *c, dex_ctx **out) {
     dex_destroy(ctx);
     return st;
   }
-  if (hipHostMalloc((void **)&ctx->tab_host, ctx->tab_cap * 4) != hipSuccess ||
-      hipHostMalloc((void **)&ctx->res_host, (R + 2 * ctx->B + 64) * 4, hipHostMallocMapped | hipHostMallocCoherent) !=
-          hipSuccess ||
-      hipHostMalloc((void **)&ctx->job_host, (size_t)(ctx->B * (ctx->S + 1)) * 6 * 4 + 256) != hipSuccess) {
+  if (alloc_failed(hipHostMalloc((void **)&ctx->tab_host, ctx->tab_cap * 4)) ||
+      alloc_failed(hipHostMalloc((void **)&ctx->res_host, (R + 2 * ctx->B + 64) * 4,
+                                 hipHostMallocMapped | hipHostMallocCoherent)) ||
+      alloc_failed(hipHostMalloc((void **)&ctx->job_host, (size_t)(ctx->B * (ctx->S + 1)) * 6 * 4 + 256))) {
     g_create_error = "hipHostMalloc failed";
     dex_destroy(ctx);
     return DEX_E_NOMEM;
@@ -2111,7 +2118,7 @@ dex_status dex_debug_gemm(int32_t dtype, const void *W, int32_t N, int32_t K, co
   // the kernels take x in the packed layout too
   const size_t wbytes_packed = packed_bytes(dtype, N, K, 0), xbytes = packed_bytes(dtype, M, K, 0);
   void *wp = nullptr;
-  if (hipMalloc(&wp, wbytes_packed + xbytes) != hipSuccess) return DEX_E_NOMEM;
+  if (alloc_failed(hipMalloc(&wp, wbytes_packed + xbytes))) return DEX_E_NOMEM;
   PackArgs pa{};
   pa.w0 = W; pa.n0 = N; pa.N = N; pa.K = K; pa.mode = 0; pa.head_dim = 16; pa.out = wp;
   hipError_t e = launch_pack(dtype, pa, (hipStream_t)stream);
@@ -2144,8 +2151,8 @@ dex_status dex_debug_attention(int32_t dtype, int32_t head_dim, int32_t n_heads,
   const hipStream_t st = (hipStream_t)stream;
   int *dtab = nullptr;
   float *part = nullptr;
-  if (hipMalloc((void **)&dtab, t.n_ints * 4) != hipSuccess) return DEX_E_NOMEM;
-  if (hipMalloc((void **)&part, t.part_bytes) != hipSuccess) { (void)hipFree(dtab); return DEX_E_NOMEM; }
+  if (alloc_failed(hipMalloc((void **)&dtab, t.n_ints * 4))) return DEX_E_NOMEM;
+  if (alloc_failed(hipMalloc((void **)&part, t.part_bytes))) { (void)hipFree(dtab); return DEX_E_NOMEM; }
   hipError_t e = launch_upload(dtab, tab.data(), t.n_ints, st);
   if (e == hipSuccess) e = launch_attention_call(c, t, dtab, part, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);

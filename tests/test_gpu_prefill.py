@@ -205,3 +205,31 @@ def test_prompt_keeps_no_host_memory_that_grows_with_it():
     assert np.array_equal(dec.prefill(short), first)
     assert _pinned_bytes(torch) - before < 4 << 20
     dec.close()
+
+
+def test_prompt_after_one_that_found_no_memory():
+    """A prompt whose scratch (1.2 GB) does not fit fails with DEX_E_NOMEM and
+    leaves the context as it was: the next one, with memory back, succeeds."""
+    torch = torch_cuda()
+    from paper_2606_29223_amd import dexlib
+    P = 8192
+    cfg = configs.scaled_down(configs.get("small-12L-d768-bf16"), n_layers=1, d_model=128, d_ffn=65536, vocab=512)
+    cfg.update(n_heads=2, n_kv_heads=1, head_dim=64, prompt_len=P)
+    w = dexlib.device_weights(cfg, gen.generate_model(cfg))
+    prompt = np.random.default_rng(6).integers(0, 512, (1, P)).astype(np.int32)
+    dec = dexlib.Decoder(cfg, w, explored=[1], width_cap=1, batch=1, max_context=P + 2)
+    torch.cuda.empty_cache()
+    held = torch.empty(torch.cuda.mem_get_info()[0] - (64 << 20), dtype=torch.uint8, device="cuda")
+    try:
+        with pytest.raises(dexlib.DexError) as e:
+            dec.prefill(prompt)
+        assert e.value.status == dexlib.DEX_E_NOMEM
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    first = dec.prefill(prompt)
+    dec.step()
+    dec.close()
+    fresh = dexlib.Decoder(cfg, w, explored=[1], width_cap=1, batch=1, max_context=P + 2)
+    assert np.array_equal(fresh.prefill(prompt), first)
+    fresh.close()
