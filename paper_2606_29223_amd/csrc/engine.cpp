@@ -1389,11 +1389,6 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
   int chain_used = 0, ngroups = 0;
   const int G = ctx->H / ctx->Hkv;
   const int grp_max = std::max(1, ATT_MAX_PAIRS / G);
-  // the matrix-core attention takes a group's rows side by side; the vector
-  // kernel one after another (5 us a row), so its groups shrink while that
-  // leaves under 2048 waves
-  const bool mfma_attn = ctx->dtype == DEX_BF16 && (ctx->hd == 64 || ctx->hd == 128);
-  const int grp_rows = mfma_attn ? grp_max : std::max(1, std::min(grp_max, R * ctx->Hkv * ctx->jmax / 2048));
   for (int r = 0; r < R; ++r) {
     const Row &rw = rows[r];
     const Seq &s = ctx->seqs[rw.seq];
@@ -1425,6 +1420,14 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
     for (int i = 0; i < n; ++i) t_pk[stage_r0[k] + i] = n <= kRowMajorRows ? ~(p0 + i) : p0 + i;
     p0 += (n + 15) / 16 * 16;
   }
+  // the matrix-core attention takes a group's rows side by side; the vector
+  // kernel one after another (5 us a row), so its groups shrink while that
+  // leaves under 2048 waves at the splits that the round's rows reach (with
+  // the context's capacity in their place, 15 rows, 8 kv heads of 64 and 16
+  // positions ran 17 us in a context of 96 and 33 us in one of 16384)
+  const bool mfma_attn = ctx->dtype == DEX_BF16 && (ctx->hd == 64 || ctx->hd == 128);
+  const int round_splits = *std::max_element(t_pos, t_pos + R) / ATT_SPLIT + 1;
+  const int grp_rows = mfma_attn ? grp_max : std::max(1, std::min(grp_max, R * ctx->Hkv * round_splits / 2048));
   // attention row groups per stage: consecutive rows of one sequence
   for (int k = 0; k < N; ++k) {
     stage_g0[k] = ngroups;

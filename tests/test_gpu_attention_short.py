@@ -4,6 +4,7 @@ longer row shares their launch: the same bits at every split edge."""
 import numpy as np
 import pytest
 
+from synth import configs, gen
 from tests.gpu_common import torch_cuda
 from tests.test_gpu_attention import BF16_RTOL, F32_RTOL, Case, _run
 
@@ -64,3 +65,33 @@ def test_row_tables_of_every_upload_size(words):
         c.chain = np.concatenate([np.full(pad, c.E - 1, np.int32), chain])
         c.coff = coff + np.int32(pad)
         assert np.array_equal(_run(torch, c)[1], want), pad
+
+
+def test_short_rows_take_as_long_in_a_long_context():
+    """The vector kernel's row groups follow the positions that a round's rows
+    reach, not what the context could hold: the attention launches of short
+    fp32 rows take the same time in either context (about twice as long with
+    groups sized for the context), and the tokens are the same."""
+    torch_cuda()
+    from paper_2606_29223_amd import dexlib
+    cfg = configs.scaled_down(configs.get("tiny-4L-d128-fp32"), vocab=512)
+    cfg.update(n_heads=32, n_kv_heads=8, head_dim=64)
+    w = dexlib.device_weights(cfg, gen.generate_model(cfg))
+    prompts = np.random.default_rng(9).integers(0, 512, (4, 16)).astype(np.int32)
+    took, toks = {}, {}
+    for ctx in (64, 16384):
+        dec = dexlib.Decoder(cfg, w, width_cap=8, batch=4, max_context=ctx)
+        runs = []
+        for _ in range(3):
+            dec.prefill(prompts)
+            for _ in range(4):
+                dec.step()
+            dec.set_timing(True)
+            toks[ctx] = [dec.step().tolist() for _ in range(24)]
+            ms, _, _ = dec.kernel_times()
+            dec.set_timing(False)
+            runs.append(ms[1] + ms[2])           # attention and combine
+        dec.close()
+        took[ctx] = sorted(runs)[1]
+    assert toks[64] == toks[16384]
+    assert took[16384] < 1.4 * took[64], took
