@@ -1057,8 +1057,36 @@ static hipError_t launch_one_t(const AttnArgs &a, const CombineArgs &c, const At
   return hipSuccess;
 }
 
+// Rows that share no keys (a row each per group) always gain from the one
+// launch.  Rows of a group share theirs in the split kernels, where the one
+// launch fetches them for every row, so it loses once its workgroups (row, kv
+// head) are many, the sooner the more splits each holds and the fewer (row,
+// head) pairs the split kernels fill their columns with.  Stand-alone calls of
+// 1 to 256 rows, one launch against split kernels and combine (us), 8 or 12 kv
+// heads.  Three or four splits, heads of 128: 256 workgroups 30 / 30 (G 1) and
+// 30 / 31 (G 4), 512 42 / 32 and 42 / 36, 2048 88 / 51 and 89 / 72; G 8: 1024
+// 59 / 64, 2048 106 / 97 at worst; heads of 64, G 1: 576 31 / 31, 1152 39 / 33,
+// 3072 56 / 48; G 4: 2048 55 / 58.  Two splits, heads of 128, G 1: 768 30 / 32,
+// 1024 37 / 33; no loss at G 4 and 8, at heads of 64 and with one split.
+// Rounds of 176 rows in 64 sequences, four splits, few rows a group, two
+// layers' attention: heads of 128, G 1 109 / 80, G 4 111 / 107, G 8 124 / 135;
+// heads of 64, G 1 46 / 52; two splits, heads of 128, G 1 47 / 55.
+static bool short_pays(const AttnArgs &a, int splits, const AttnSeg *segs, int n) {
+  const int G = a.n_heads / a.n_kv_heads;
+  long long rows = 0, groups = 0;
+  for (int i = 0; i < n; ++i) { rows += segs[i].M; groups += segs[i].n_groups; }
+  const long long wgs = rows * a.n_kv_heads;
+  if (splits == 1 || rows == groups) return true;
+  const bool few = rows < 2 * groups;          // rows a group
+  if (a.head_dim == 64) return splits == 2 || G >= 4 || few || wgs <= 512;
+  if (splits == 2) return G >= 4 || few || wgs <= 768;
+  return G >= 8 ? few || wgs <= 1024 : wgs <= 256;
+}
+
 bool attention_short_supported(int dtype, const AttnArgs &a, const AttnSeg *segs, int n) {
-  return short_splits(segs, n) <= (mfma_attention(dtype, a.head_dim) ? SHORT_SPLITS : 1);
+  const int splits = short_splits(segs, n);
+  if (!mfma_attention(dtype, a.head_dim)) return splits == 1;
+  return splits <= SHORT_SPLITS && short_pays(a, splits, segs, n);
 }
 
 hipError_t launch_attention_short(int dtype, const AttnArgs &a, const CombineArgs &c, const AttnSeg *segs, int n,

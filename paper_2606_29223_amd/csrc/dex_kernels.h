@@ -311,9 +311,9 @@ hipError_t launch_combine(int dtype, const CombineArgs &a, int rows, hipStream_t
 hipError_t launch_gemm_seg(int dtype, int epi, const GemmArgs &a, const GemmSeg *segs, int n, hipStream_t s);
 hipError_t launch_attention_seg(int dtype, const AttnArgs &a, const AttnSeg *segs, int n, hipStream_t s);
 // Attention and combine of short rows in one launch (every segment at most
-// SHORT_SPLITS splits on the matrix cores, one in the vector kernel): rows,
-// queries, row tables and c's output rows are all indexed by the launch's row
-// space.
+// SHORT_SPLITS splits on the matrix cores, and few enough rows; one in the
+// vector kernel): rows, queries, row tables and c's output rows are all
+// indexed by the launch's row space.
 constexpr int SHORT_SPLITS = 4;
 bool attention_short_supported(int dtype, const AttnArgs &a, const AttnSeg *segs, int n);
 hipError_t launch_attention_short(int dtype, const AttnArgs &a, const CombineArgs &c, const AttnSeg *segs, int n,

@@ -34,6 +34,21 @@ def test_short_rows_have_the_bits_of_the_split_kernels(hd, H, Hkv):
         assert np.array_equal(_run(torch, c, [r])[1], full_bits[[r]])
 
 
+@pytest.mark.parametrize("hd,H,Hkv,nc,R", [(64, 12, 12, 200, 5), (64, 12, 12, 200, 6), (128, 4, 4, 100, 24),
+                                            (128, 4, 4, 100, 25), (128, 32, 8, 150, 4), (128, 32, 8, 150, 5),
+                                            (128, 64, 8, 230, 16), (128, 64, 8, 230, 17)])
+def test_many_rows_of_a_prefix_have_the_bits_of_a_few(hd, H, Hkv, nc, R):
+    """Eight sequences of R rows, on both sides of the row counts from which
+    rows that share keys go to the split kernels: any one row of each has the
+    bits it has in a launch of one row a sequence."""
+    torch = torch_cuda()
+    c = Case(1, hd, H, Hkv, [(nc + s, [i % 4 for i in range(R)]) for s in range(8)], 4250 + hd + R)
+    _, bits = _run(torch, c)
+    for i in (0, R - 1):
+        rows = [s * R + i for s in range(8)]
+        assert np.array_equal(_run(torch, c, rows)[1], bits[rows])
+
+
 @pytest.mark.parametrize("dtype,hd", [(0, 32), (0, 64), (0, 128), (1, 32)])
 @pytest.mark.parametrize("H,Hkv", [(4, 4), (6, 2), (8, 1)])
 def test_one_split_rows_have_the_bits_of_the_split_kernels(dtype, hd, H, Hkv):
