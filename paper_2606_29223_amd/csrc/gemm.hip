@@ -387,13 +387,22 @@ static hipError_t launch_t(const GemmArgs &a, const GemmSegs *g, int M, int nseg
   if constexpr (EPI == EPI_QKV || EPI == EPI_RESID) {
     // the projections of a 4096-wide layer (256 tiles: O, down; 384: QKV):
     // alone, one tile per workgroup occupies the chip; grouped over segments
-    // or row blocks the grid has room for several
-    if (n_tiles >= 256 && n_tiles <= 512) {
-      constexpr bool qkv = EPI == EPI_QKV;
+    // or row blocks the grid has room for several.  The QKV choices hold up
+    // to 512 tiles.  O and down of 5120 to 8192-wide layers keep the general
+    // ones (one row, down of 4096 columns, us: 5120 wide 52.8 against 58.0,
+    // 8192 wide 61.5 against 66.1; 32 rows 82 / 86 and 85 / 99), but for
+    // grouped launches of more than 32 bf16 rows a segment (O, 6144 wide,
+    // 62.9 against 69.7; in fp32 196 against 187)
+    constexpr bool qkv = EPI == EPI_QKV;
+    const int table_tiles = qkv || (sizeof(T) == 2 && nseg > 1 && M > 32) ? 512 : 256;
+    if (n_tiles >= 256 && n_tiles <= table_tiles) {
       if (M <= 16) {
         if (qkv && nseg > 1) go<T, EPI, 1, 2, 1>(a, g, dim3(tiles(1)), s);
         else if (qkv && M <= 8) go<T, EPI, 1, 4, 1>(a, g, dim3(tiles(1)), s);
         else if (!qkv && nseg == 1) go<T, EPI, 1, 8, 1>(a, g, dim3(tiles(1)), s);
+        // (segments of one to four rows: a short K, O's, at two steps a chunk
+        // 17.1 against 17.7 us, down's 14336 at four 45.1 against 45.8)
+        else if (!qkv && M <= 4 && a.nsteps_w <= 256) go<T, EPI, 1, 2, 1>(a, g, dim3(tiles(1)), s);
         else if (!qkv && M <= 8) go<T, EPI, 1, 4, 1>(a, g, dim3(tiles(1)), s);
         else if (qkv || nseg == 2 || nseg == 4) go<T, EPI, 1, 4, 2>(a, g, dim3(tiles(2)), s);
         else go<T, EPI, 1, 2, 4>(a, g, dim3(tiles(4)), s);
