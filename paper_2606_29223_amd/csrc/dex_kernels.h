@@ -357,7 +357,7 @@ hipError_t launch_argmax(const ArgmaxArgs &a, hipStream_t s);
 
 struct CollapseArgs {
   int n_jobs;
-  const int *job;             // [n_jobs][6] in host memory: seq, src entry, dst entry, src slot, dst slot, kind (0 kv only, 1 kv + slot state)
+  const int *job;             // [n_jobs][6] in pinned host memory: seq, src entry, dst entry, src slot, dst slot, kind (0 kv only, 1 kv + slot state)
   int *job_dev;               // room for them on the device
   void *kc, *vc;              // cache base
   int n_layers, batch, n_kv_heads, kv_entries, head_dim;
@@ -368,8 +368,8 @@ struct CollapseArgs {
 };
 hipError_t launch_collapse(const CollapseArgs &a, hipStream_t s);
 
-// n ints from host memory to the device, in stream order; src is free to be
-// reused at once if it is pageable, or once the stream has passed if pinned.
+// n ints from pageable host memory to the device, in stream order; src is free
+// to be reused at once.
 hipError_t launch_upload(int *dst, const int *src, size_t n, hipStream_t s);
 
 hipError_t launch_gumbel(unsigned long long seed, int seq, int pos, int V, float *out, hipStream_t s);

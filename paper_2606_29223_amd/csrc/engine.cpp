@@ -1180,7 +1180,7 @@ dex_status dex_prefill(dex_ctx *ctx, const int32_t *prompts, int32_t P, int32_t 
   }
   int *tab = (int *)(base + o_tab);
   auto dev = [&](const int *t) -> const int * { return tab + (t - T); };
-  HIPCHK(launch_upload(tab, T, tab_ints, ctx->stream));
+  HIPCHK(hipMemcpyAsync(tab, T, tab_ints * 4, hipMemcpyHostToDevice, ctx->stream));
   const int *d_exseq = dev(ex_seq), *d_exzero = dev(ex_zero), *d_expos = dev(ex_pos);
   const size_t layer_kv = (size_t)B * ctx->Hkv * ctx->E * hd * es;
   // a normed tiled GEMM first gets its row scales
@@ -1462,7 +1462,7 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
     ctx->rt_ms[6] += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_call).count();
     HIPCHK(hipEventRecord(rt[0], ctx->stream));
   }
-  HIPCHK(launch_upload(ctx->tab_dev, T, tab_ints, ctx->stream));
+  HIPCHK(hipMemcpyAsync(ctx->tab_dev, T, tab_ints * 4, hipMemcpyHostToDevice, ctx->stream));
   if (rt) HIPCHK(hipEventRecord(rt[1], ctx->stream));
   const int *D = ctx->tab_dev;
   auto dptr = [&](const int *hp) { return D + (hp - T); };

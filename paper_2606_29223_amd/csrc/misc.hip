@@ -146,9 +146,9 @@ __global__ __launch_bounds__(AMAX_THREADS) void argmax_kernel(ArgmaxArgs a) {
   __syncthreads();
   if (tid == 0) {
     for (int w = 1; w < AMAX_THREADS / 64; ++w) amax_take(bv, bi, sv[w], si[w]);
-    // the results go straight to host memory: a copy kernel behind this one
-    // took 4.6 us of a round (with the tables as arguments, 4 layers of 128 in
-    // fp32, 64 tokens: 5.61 -> 5.37 ms)
+    // the results go straight to host memory: a copy behind this kernel cost a
+    // round 2 us (two lattices on 4 layers of 128 in fp32: 72.9 -> 70.8 us; one
+    // on 12 layers of 768: 140 -> 138 us; 64 rows: the same)
     __hip_atomic_store(a.u_out + m, bi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (a.cand != nullptr) a.cand[a.row_cand[m]] = bi;
     // Validate and commit (Section 3.2, commit process) when this row is an
@@ -173,31 +173,29 @@ hipError_t launch_argmax(const ArgmaxArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// A few words as a kernel argument: 2.4 us on the stream, where the runtime's
-// copy of this size took 4.6 us and, from pageable memory, host time besides
-// (stand-alone attention at 700 keys: 37 -> 35 us a call).  Most tables of a
-// round fit; 960 words are the most that the 4 KB of arguments hold.
-template <int N> struct Words { int v[N]; };
-constexpr int WORDS_SMALL = 240, WORDS_MAX = 960;
-template <int N>
-__global__ __launch_bounds__(N) void words_kernel(int *dst, int n, Words<N> w) {
+// A few words as a kernel argument.  From pageable memory that is cheaper than
+// the runtime's copy (stand-alone attention of 4 and 8 rows at 700 keys, whole
+// calls: 29.2 and 30.3 against 29.8 and 30.9 us).  From pinned memory it is
+// not: a round's tables as an argument of 960 words took 13.2 us against 8.5 as
+// a copy, and of 240 words made no round faster (4 layers of 128 in fp32, 1 / 8
+// rows: 157 / 161.3 against 155.1 / 159.3 us a round).
+constexpr int WORDS = 240;
+struct Words { int v[WORDS]; };
+static Words words_of(const int *src, int n) {
+  Words w{};
+  std::memcpy(w.v, src, (size_t)n * 4);
+  return w;
+}
+__global__ __launch_bounds__(WORDS) void words_kernel(int *dst, int n, Words w) {
   const int i = threadIdx.x;
   if (i < n) dst[i] = w.v[i];
-}
-template <int N>
-static hipError_t launch_words_t(int *dst, const int *src, int n, hipStream_t s) {
-  Words<N> w;
-  std::memcpy(w.v, src, (size_t)n * 4);
-  if (n < N) std::memset(w.v + n, 0, (size_t)(N - n) * 4);
-  hipLaunchKernelGGL(words_kernel<N>, dim3(1), dim3(N), 0, s, dst, n, w);
-  return hipGetLastError();
 }
 
 hipError_t launch_upload(int *dst, const int *src, size_t n, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  if (n <= WORDS_SMALL) return launch_words_t<WORDS_SMALL>(dst, src, (int)n, s);
-  if (n <= WORDS_MAX) return launch_words_t<WORDS_MAX>(dst, src, (int)n, s);
-  return hipMemcpyAsync(dst, src, n * 4, hipMemcpyHostToDevice, s);
+  if (n > WORDS) return hipMemcpyAsync(dst, src, n * 4, hipMemcpyHostToDevice, s);
+  hipLaunchKernelGGL(words_kernel, dim3(1), dim3(WORDS), 0, s, dst, (int)n, words_of(src, (int)n));
+  return hipGetLastError();
 }
 
 // Collapse gather.  Job (seq, src entry, dst entry, src slot, dst slot, kind):
@@ -206,9 +204,9 @@ hipError_t launch_upload(int *dst, const int *src, size_t n, hipStream_t s) {
 // goes to its committed position (kind 0); retained slots move to the
 // other half of the lattice region in canonical order (kind 1), so source
 // and destination never overlap.
-// Up to 40 jobs ride in the kernel arguments (ARGS).
+// Up to 40 jobs ride in the kernel arguments (ARGS): one command instead of two.
 template <int ELEM, bool ARGS>
-__global__ __launch_bounds__(256) void collapse_kernel(CollapseArgs a, Words<WORDS_SMALL> w) {
+__global__ __launch_bounds__(256) void collapse_kernel(CollapseArgs a, Words w) {
   const int jb = blockIdx.x, l = blockIdx.y;
   const int *j = ARGS ? w.v + 6 * jb : a.job_dev + 6 * jb;
   const int seq = j[0], se = j[1], de = j[2], ss = j[3], ds = j[4], kind = j[5];
@@ -237,15 +235,15 @@ __global__ __launch_bounds__(256) void collapse_kernel(CollapseArgs a, Words<WOR
 hipError_t launch_collapse(const CollapseArgs &a, hipStream_t s) {
   if (a.n_jobs <= 0) return hipSuccess;
   dim3 grid(a.n_jobs, a.n_layers + 1);
-  Words<WORDS_SMALL> w{};
-  if (6 * a.n_jobs <= WORDS_SMALL) {
-    std::memcpy(w.v, a.job, (size_t)a.n_jobs * 24);
+  if (6 * a.n_jobs <= WORDS) {
+    const Words w = words_of(a.job, 6 * a.n_jobs);
     if (a.elem_bytes == 2) hipLaunchKernelGGL((collapse_kernel<2, true>), grid, dim3(256), 0, s, a, w);
     else hipLaunchKernelGGL((collapse_kernel<4, true>), grid, dim3(256), 0, s, a, w);
     return hipGetLastError();
   }
-  const hipError_t e = launch_upload(a.job_dev, a.job, (size_t)a.n_jobs * 6, s);
+  const hipError_t e = hipMemcpyAsync(a.job_dev, a.job, (size_t)a.n_jobs * 24, hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return e;
+  const Words w{};
   if (a.elem_bytes == 2) hipLaunchKernelGGL((collapse_kernel<2, false>), grid, dim3(256), 0, s, a, w);
   else hipLaunchKernelGGL((collapse_kernel<4, false>), grid, dim3(256), 0, s, a, w);
   return hipGetLastError();

@@ -68,9 +68,9 @@ def test_one_split_rows_have_the_bits_of_the_split_kernels(dtype, hd, H, Hkv):
 
 @pytest.mark.parametrize("words", [240, 960])
 def test_row_tables_of_every_upload_size(words):
-    """Row tables of up to 240 and 960 words go to the GPU as kernel arguments
-    of two sizes, longer ones by a copy: a row whose chain entries are the
-    table's last words has the same bits on both sides of either size."""
+    """A call's row tables of up to 240 words go to the GPU as a kernel argument,
+    longer ones by a copy: a row whose chain entries are the table's last words
+    has the same bits on both sides of that size and at four times it."""
     torch = torch_cuda()
     c = Case(1, 64, 4, 2, [(40, [9])], 4400)
     _, want = _run(torch, c)
