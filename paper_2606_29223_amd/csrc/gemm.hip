@@ -425,8 +425,12 @@ static hipError_t launch_t(const GemmArgs &a, const GemmSegs *g, int M, int nseg
   if (M <= 16) {
     // deeper prefetch when a workgroup per CU streams a long tile, shallower
     // when many workgroups share each CU; above 8 rows a lone wide launch
-    // takes two tiles per workgroup
-    if (M > 8 && nseg == 1 && n_tiles > 512) go<T, EPI, 1, 2, 2>(a, g, dim3(tiles(2)), s);
+    // takes two tiles per workgroup, and above 4 where up to 1024 tiles are
+    // too shallow to fill one (LM head at 8 rows, us, two against one: 1000
+    // tiles, 768 columns 10.1 / 11.5, 3072 21.3 / 21.8, 4096 27.9 / 26.5; 563
+    // tiles, 768 9.6 / 10.1, 2560 16.5 / 15.4)
+    const bool shallow = n_tiles <= 1024 && a.nsteps_w <= (n_tiles > 768 ? 96 : 64);
+    if (M > (shallow ? 4 : 8) && nseg == 1 && n_tiles > 512) go<T, EPI, 1, 2, 2>(a, g, dim3(tiles(2)), s);
     else if (n_tiles <= 256) go<T, EPI, 1, 8, 1>(a, g, dim3(tiles(1)), s);
     else if (n_tiles <= 1024) go<T, EPI, 1, 4, 1>(a, g, dim3(tiles(1)), s);
     else go<T, EPI, 1, 2, 1>(a, g, dim3(tiles(1)), s);
