@@ -264,8 +264,9 @@ dex_status dex_debug_kernel_times(dex_ctx *ctx, int32_t n, double *ms, int64_t *
  * at its boundaries.  dex_debug_round_times fills, summed over the rounds
  * since the last enable (*rounds of them), in milliseconds:
  *   ms[0] row-table upload           ms[1] stage sweep (all lanes joined)
- *   ms[2] exit head, verify/commit    ms[3] result copy to the host
- *   ms[4] host commit handling and the collapse gather (from the copy's
+ *   ms[2] exit head, verify/commit, the results' stores to the host
+ *   ms[3] 0: those stores leave no copy to time
+ *   ms[4] host commit handling and the collapse gather (from the exit's
  *         end to the collapse's end; one round fewer than *rounds)
  *   ms[5] the gap before a round: from the previous round's last device
  *         work to this round's upload (return to the caller, the caller's

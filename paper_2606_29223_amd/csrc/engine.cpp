@@ -189,7 +189,7 @@ struct dex_ctx {
   // round phases: events on the decode stream at the round's boundaries
   // (two sets, the previous round's last event opens the gap before this one)
   bool round_timing = false;
-  hipEvent_t rt_ev[2][6] = {};
+  hipEvent_t rt_ev[2][5] = {};
   int rt_cur = 0;
   bool rt_prev = false;
   double rt_ms[kRoundPhases] = {0};
@@ -1805,22 +1805,21 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
   dex_status xs = run_exit(ctx, R, dptr(t_bnd), ctx->bnd_h, ctx->bnd_part, dptr(t_maskn), dptr(t_mask),
                            dptr(t_cidx), ctx->cand, dptr(t_seq), dptr(t_pos), stage_r0.data(), dptr(t_rcommit));
   if (xs != DEX_OK) return fail(ctx, xs);
-  if (rt) HIPCHK(hipEventRecord(rt[3], ctx->stream));
-  if (rt) HIPCHK(hipEventRecord(rt[4], ctx->stream));
+  if (rt) HIPCHK(hipEventRecord(rt[3], ctx->stream));   // the argmax has stored the results on the host
   HIPCHK(hipStreamSynchronize(ctx->stream));
   if (rt) {
     // this round's device phases; the previous round's collapse (its host
     // commit handling and the gather) and the gap before this round
     float ms = 0.f;
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 3; ++i) {
       HIPCHK(hipEventElapsedTime(&ms, rt[i], rt[i + 1]));
       ctx->rt_ms[i] += ms;
     }
     if (ctx->rt_prev) {
       hipEvent_t *pv = ctx->rt_ev[1 - ctx->rt_cur];
-      HIPCHK(hipEventElapsedTime(&ms, pv[4], pv[5]));
+      HIPCHK(hipEventElapsedTime(&ms, pv[3], pv[4]));
       ctx->rt_ms[4] += ms;
-      HIPCHK(hipEventElapsedTime(&ms, pv[5], rt[0]));
+      HIPCHK(hipEventElapsedTime(&ms, pv[4], rt[0]));
       ctx->rt_ms[5] += ms;
     }
     ctx->rt_rounds += 1;
@@ -1922,7 +1921,7 @@ dex_status dex_step(dex_ctx *ctx, int32_t *committed_out, dex_step_info *info) {
     HIPCHK(launch_collapse(c, ctx->stream));
   }
   if (rt) {
-    HIPCHK(hipEventRecord(rt[5], ctx->stream));
+    HIPCHK(hipEventRecord(rt[4], ctx->stream));
     ctx->rt_prev = true;
     ctx->rt_cur = 1 - ctx->rt_cur;
   }

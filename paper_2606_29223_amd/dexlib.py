@@ -329,7 +329,7 @@ class Decoder:
 
     def round_times(self):
         """(per-phase milliseconds summed over the timed rounds, rounds); see
-        ROUND_PHASES."""
+        ROUND_PHASES ("copy" is 0: the exit phase stores the results)."""
         ms = (ctypes.c_double * 7)()
         n = ctypes.c_int64()
         _check(self.lib, self.ctx, self.lib.dex_debug_round_times(self.ctx, 7, ms, ctypes.byref(n)))

@@ -15,7 +15,8 @@
     commit takes exactly N rounds from a fresh anchor, and the tokens are
     still AR's (Algorithm 1 with no parallel branch is sequential
     early-exit verification at every depth);
-  * the binding's generate helper and the generation module.
+  * the binding's generate helper and the generation module;
+  * the round phases add up to the timed rounds, with nothing under "copy".
 """
 import numpy as np
 import pytest
@@ -159,3 +160,28 @@ def test_generate_helper_and_cli(capsys, monkeypatch):
     gen_cli.main()
     out = json.loads(capsys.readouterr().out.strip().splitlines()[-1])
     assert out["equals_ar"] and out["tokens"] == toks and out["commits"] == T - 1
+
+
+def test_round_phases_add_up():
+    """The phases of the timed rounds sum to the wall clock around them (the
+    last round's commit and the caller's last return are outside), and no time
+    goes to a result copy, which a round does not have."""
+    import time
+    from paper_2606_29223_amd import dexlib
+    cfg, _ = host_weights(TINY)
+    dec = decoder(TINY, max_context=cfg["prompt_len"] + 96)
+    dec.prefill(gen.prompts(cfg))
+    for _ in range(8):
+        dec.step()
+    dec.set_round_timing(True)
+    t0 = time.perf_counter()
+    for _ in range(64):
+        dec.step()
+    wall = 1e3 * (time.perf_counter() - t0)
+    ms, n = dec.round_times()
+    dec.close()
+    assert n == 64
+    phases = dict(zip(dexlib.ROUND_PHASES, ms))
+    assert phases["copy"] == 0.0
+    assert all(phases[p] > 0.0 for p in dexlib.ROUND_PHASES if p != "copy")
+    assert 0.8 * wall < sum(ms[:6]) < 1.05 * wall, (wall, phases)
