@@ -740,10 +740,14 @@ static hipError_t launch_prefill_t(const PrefillAttnArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Two query tiles a wave once that leaves four workgroups per compute unit,
-// one below: 2 x 1100 with 12 heads of 64 (216 workgroups of two) takes 18
-// against 23 us, 8 x 2048 (1536) 99 against 86 us; 1 x 2048 with 32 / 8 heads
-// of 128 (512) 74 against 82 us, 8 x 1024 (2048) 132 against 116 us.
+// Two query tiles a wave once that leaves four workgroups per compute unit, one
+// below (one against two, us; launches of up to 8192 rows, as prompts make them,
+// and of one prompt of 16384): 32 / 8 heads of 128, 560 workgroups 43.4 / 48.7,
+// 1024 63.6 to 207 / 56.6 to 179, 2048 120 to 790 / 106 to 652; 8 / 8 heads
+// of 128, 512 137 / 159, 1024 818 / 705; 12 / 12 heads of 64, 768 14.6 to 170 /
+// 15.5 to 181, 1536 642 / 532; 16 / 8 heads of 64, 512 72 / 87, 1024 36 to 214 /
+// 35 to 200.  Of 112 shapes the rule misses by at most 2 %, but for 6 % at one
+// prompt of 16384 with 8 heads of 128 per kv head (1446 / 1540).
 hipError_t launch_prefill_attention(const PrefillAttnArgs &a, hipStream_t s) {
   const int G = a.n_heads / a.n_kv_heads;
   if (G < 1 || G > 8 || a.prompt_len < 1 || a.batch < 1 || a.out_steps < 1) return hipErrorInvalidValue;

@@ -413,9 +413,8 @@ def test_gqa128_prefill_ragged_prompts(P, G):
     prompt), at batch 2: y_0 and the
     next tokens follow the oracle (near ties aside) and every decoded row's
     exit logits agree within 2e-2 (max relative).  At 2 x 3100 prompt rows
-    all four prompt GEMMs (QKV with RoPE and the cache write, O and down with
-    the residual, gate/up with SwiGLU) take the 256 x 256 LDS-staged form
-    (150, 100, 400 and 100 workgroups)."""
+    the gate/up GEMM takes the 256 x 256 tile and the other three the 128 x 128
+    one with three ring slots."""
     torch = torch_cuda()
     from paper_2606_29223_amd import dexlib
     cfg = configs.scaled_down(configs.get("llama-32L-d4096-x8-w4"), n_layers=2, d_model=1024, d_ffn=2048,

@@ -39,8 +39,8 @@ def test_prompt_gemm_tiles(N, K, M):
                                              (96, 64, 5, 1, 64, 201), (64, 96, 7, 1, 128, 131)])
 def test_prompt_with_unfilled_k_steps(d, F, H, Hkv, hd, P):
     """bf16 models whose widths do not fill 32-column k-steps (the packed
-    activations end in zeros), with head_dim 32 (whose attention writes
-    row-major and is packed afterwards) and odd numbers of query heads per kv head:
+    activations end in zeros), with head_dim 32 (whose attention is the split
+    kernel with its combine) and odd numbers of query heads per kv head:
     y_0 and the next tokens follow the oracle, exit logits within 2e-2."""
     torch = torch_cuda()
     from paper_2606_29223_amd import dexlib
@@ -69,32 +69,171 @@ def test_prompt_with_unfilled_k_steps(d, F, H, Hkv, hd, P):
         check_tokens_teacher_forced(z[:, -1], seq)
 
 
-@pytest.mark.parametrize("hd,H,Hkv,P,B", [(128, 8, 2, 2110, 8), (64, 6, 6, 1310, 16)])
-def test_prompt_attention_bits_do_not_depend_on_the_batch(hd, H, Hkv, P, B):
-    """The batch decides how many queries a wave of the prompt attention
-    takes (one 16-query tile alone; two from 1024 workgroups on: 1056 and
-    1056 here): the keys and values of the second layer, which the first
-    layer's attention feeds, and y_0 are the same bits either way."""
+def _second_layer(torch, hd, H, Hkv, prompts, cfg, w):
+    """y_0 and the second layer's keys and values (bf16 bits), which the first
+    layer's attention feeds."""
+    from paper_2606_29223_amd import dexlib
+    B, P = prompts.shape
+    dec = dexlib.Decoder(cfg, w, explored=[2], width_cap=1, batch=B, max_context=P + 2)
+    first = dec.prefill(prompts)
+    k, v, E = dec.kv_layout()
+    n = 2 * B * Hkv * E * hd * 2
+    caches = []
+    for base in (k, v):
+        buf = torch.empty(n, dtype=torch.uint8, device="cuda")
+        assert dexlib.load().dex_debug_copy(buf.data_ptr(), base, n, dec.stream.cuda_stream) == 0
+        torch.cuda.synchronize()
+        caches.append(buf.view(torch.int16).view(2, B, Hkv, E, hd)[1, :, :, :P].clone())
+    dec.close()
+    return first, caches[0], caches[1]
+
+
+def _attention_workgroups(H, Hkv, B, P):
+    """Workgroups of a prompt's largest attention launch, two query tiles a
+    wave: a launch takes whole sequences, about 8192 rows of them."""
+    parts = -(-B // max(1, 8192 // P))
+    span = 32 * max(1, 4 // (H // Hkv))
+    return -(-P // span) * Hkv * -(-B // parts)
+
+
+def _two_layer_model(hd, H, Hkv, P, d=256, F=256):
+    from paper_2606_29223_amd import dexlib
+    cfg = configs.scaled_down(configs.get("small-12L-d768-bf16"), n_layers=2, d_model=d, d_ffn=F, vocab=512)
+    cfg.update(n_heads=H, n_kv_heads=Hkv, head_dim=hd, prompt_len=P)
+    return cfg, dexlib.device_weights(cfg, gen.generate_model(cfg))
+
+
+def _second_layer_f64(torch, cfg, w, tokens):
+    """The second layer's keys and values [Hkv][P][hd] of one prompt in float64."""
+    d, H, Hkv, hd = cfg["d_model"], cfg["n_heads"], cfg["n_kv_heads"], cfg["head_dim"]
+    P = len(tokens)
+    W = {n: (t.view(torch.bfloat16) if t.dtype == torch.int16 else t).double() for n, t in w.items()}
+    ang = torch.arange(P, device="cuda").double()[:, None] * cfg["rope_theta"] ** (
+        -2.0 * torch.arange(hd // 2, device="cuda").double() / hd)
+    c, s = torch.cos(ang)[:, None], torch.sin(ang)[:, None]
+
+    def norm(h, g):
+        return h * torch.rsqrt(h.pow(2).mean(-1, keepdim=True) + cfg["rms_eps"]) * g
+
+    def rope(y):
+        y = y.view(P, -1, hd)
+        a, b = y[..., :hd // 2], y[..., hd // 2:]
+        return torch.cat((a * c - b * s, b * c + a * s), -1)
+
+    h = W["embed"][torch.as_tensor(tokens, device="cuda", dtype=torch.long)]
+    for l in range(2):
+        p = f"layers.{l}."
+        x = norm(h, W[p + "attn_norm"])
+        k, v = rope(x @ W[p + "wk"].T), (x @ W[p + "wv"].T).view(P, Hkv, hd)
+        if l == 1:
+            return k.transpose(0, 1), v.transpose(0, 1)
+        q = rope(x @ W[p + "wq"].T)
+        mask = torch.ones(P, P, device="cuda", dtype=torch.bool).triu(1)
+        att = torch.empty_like(q)
+        for i in range(H):
+            sc = (q[:, i] @ k[:, i // (H // Hkv)].T / hd ** 0.5).masked_fill(mask, -float("inf"))
+            att[:, i] = torch.softmax(sc, -1) @ v[:, i // (H // Hkv)]
+        alpha = cfg["residual_scale"] / cfg["n_layers"]
+        h = h + alpha * (att.reshape(P, -1) @ W[p + "wo"].T)
+        x = norm(h, W[p + "ffn_norm"])
+        h = h + alpha * ((torch.nn.functional.silu(x @ W[p + "w_gate"].T) * (x @ W[p + "w_up"].T)) @ W[p + "w_down"].T)
+
+
+@pytest.mark.parametrize("hd,H,Hkv,P,B", [(128, 32, 8, 1010, 8), (64, 32, 8, 1010, 8), (64, 24, 12, 1000, 8)])
+def test_prompt_attention_of_one_and_two_query_tiles(hd, H, Hkv, P, B):
+    """The batch decides how many queries a wave of the prompt attention takes
+    (one 16-query tile; two once the launch has 1024 workgroups): the keys and
+    values of the second layer and y_0 are the same bits either way, and
+    those of the two-tile launch follow float64 (bf16 inputs, weights and
+    caches: 2^-9 each over a layer, about 3e-3 of the norm)."""
+    torch = torch_cuda()
+    assert _attention_workgroups(H, Hkv, B, P) >= 1024 > _attention_workgroups(H, Hkv, 1, P)
+    cfg, w = _two_layer_model(hd, H, Hkv, P)
+    prompts = np.random.default_rng(hd + H).integers(0, 512, (B, P)).astype(np.int32)
+    both = _second_layer(torch, hd, H, Hkv, prompts, cfg, w)
+    for b in (0, B - 1):
+        first, k, v = _second_layer(torch, hd, H, Hkv, prompts[b:b + 1], cfg, w)
+        assert first[0] == both[0][b]
+        assert torch.equal(k[0], both[1][b]) and torch.equal(v[0], both[2][b])
+    for got, ref in zip(both[1:], _second_layer_f64(torch, cfg, w, prompts[B - 1])):
+        d = got[B - 1].view(torch.bfloat16).double() - ref
+        assert float(d.norm() / ref.norm()) <= 1e-2
+        rows = d.pow(2).sum((0, 2)).sqrt() / ref.pow(2).sum((0, 2)).sqrt()
+        assert float(rows.max()) <= 2e-2, int(rows.argmax())
+
+
+def test_prompt_layer_on_the_largest_tile():
+    """A 2048-wide layer at 8 x 775 rows: by the cost rule of the prompt GEMM all
+    four projections take the 256 x 256 tile (QKV with RoPE and the cache write,
+    O and down with the residual, gate/up with SwiGLU), one sequence alone
+    smaller ones.  The second layer's keys and values, which pass through
+    every one of them, are the same bits and follow float64."""
+    torch = torch_cuda()
+    hd, H, Hkv, P, B = 128, 16, 8, 775, 8
+    cfg, w = _two_layer_model(hd, H, Hkv, P, 2048, 4096)
+    prompts = np.random.default_rng(12).integers(0, 512, (B, P)).astype(np.int32)
+    both = _second_layer(torch, hd, H, Hkv, prompts, cfg, w)
+    first, k, v = _second_layer(torch, hd, H, Hkv, prompts[B - 1:], cfg, w)
+    assert first[0] == both[0][B - 1]
+    assert torch.equal(k[0], both[1][B - 1]) and torch.equal(v[0], both[2][B - 1])
+    for got, ref in zip(both[1:], _second_layer_f64(torch, cfg, w, prompts[B - 1])):
+        assert float((got[B - 1].view(torch.bfloat16).double() - ref).norm() / ref.norm()) <= 1e-2
+
+
+@pytest.mark.parametrize("name,P,B", [("tiny-4L-d128-fp32", 1500, 7), ("hd32-bf16", 1500, 7), ("tiny-4L-d128-fp32", 9001, 1),
+                                      ("hd32-bf16", 300, 64)])
+def test_split_kernel_prompts_in_parts(name, P, B):
+    """Prompts whose attention is the vector split kernel (fp32; bf16 with
+    head_dim 32), of more than 8192 rows: parts of whole sequences, each with
+    its own row groups and chunks (4 + 3 sequences, one long one, 22 + 22 + 20).
+    Every sequence has the caches and y_0 of itself alone, and the first
+    follows float64."""
     torch = torch_cuda()
     from paper_2606_29223_amd import dexlib
-    cfg = configs.scaled_down(configs.get("small-12L-d768-bf16"), n_layers=2, d_model=256, d_ffn=256, vocab=512)
-    cfg.update(n_heads=H, n_kv_heads=Hkv, head_dim=hd, prompt_len=P)
+    if name == "hd32-bf16":
+        cfg = configs.scaled_down(configs.get("small-12L-d768-bf16"), n_layers=2, d_model=128, d_ffn=256, vocab=512)
+        cfg.update(n_heads=4, n_kv_heads=2, head_dim=32)
+    else:
+        cfg = configs.scaled_down(configs.get(name), n_layers=2)
+    bf16, Hkv, hd = cfg["dtype"] == "bf16", cfg["n_kv_heads"], cfg["head_dim"]
+    cfg["prompt_len"] = P
     w = dexlib.device_weights(cfg, gen.generate_model(cfg))
-    prompts = np.random.default_rng(hd).integers(0, 512, (B, P)).astype(np.int32)
-    got = []
-    for rows in (prompts, prompts[:1], prompts[B - 1:]):
+    prompts = np.random.default_rng(P + B).integers(0, cfg["vocab"], (B, P)).astype(np.int32)
+
+    def prefill(rows):
         dec = dexlib.Decoder(cfg, w, explored=[2], width_cap=1, batch=len(rows), max_context=P + 2)
         first = dec.prefill(rows)
-        k, v, E = dec.kv_layout()
-        n = 2 * len(rows) * Hkv * E * hd * 2
-        caches = []
-        for base in (k, v):
+        kp, vp, E = dec.kv_layout()
+        n = 2 * len(rows) * Hkv * E * hd * (2 if bf16 else 4)
+        out = []
+        for base in (kp, vp):
             buf = torch.empty(n, dtype=torch.uint8, device="cuda")
             assert dexlib.load().dex_debug_copy(buf.data_ptr(), base, n, dec.stream.cuda_stream) == 0
             torch.cuda.synchronize()
-            caches.append(buf.view(torch.int16).view(2, len(rows), Hkv, E, hd)[1, :, :, :P].clone())
+            t = buf.view(torch.int16 if bf16 else torch.int32).view(2, len(rows), Hkv, E, hd)
+            out.append(t[1, :, :, :P].clone())
         dec.close()
-        got.append((first, *caches))
+        return first, out[0], out[1]
+
+    both = prefill(prompts)
+    for b in sorted({0, B // 2, B - 1}):
+        first, k, v = prefill(prompts[b:b + 1])
+        assert first[0] == both[0][b]
+        assert torch.equal(k[0], both[1][b]) and torch.equal(v[0], both[2][b])
+    for got, ref in zip(both[1:], _second_layer_f64(torch, cfg, w, prompts[0])):
+        d = got[0].view(torch.bfloat16 if bf16 else torch.float32).double() - ref
+        assert float(d.norm() / ref.norm()) <= (1e-2 if bf16 else 2e-6)
+
+
+@pytest.mark.parametrize("hd,H,Hkv,P,B", [(128, 8, 2, 2110, 8), (64, 6, 6, 1310, 16)])
+def test_prompt_attention_bits_do_not_depend_on_the_batch(hd, H, Hkv, P, B):
+    """Batches of more than 8192 rows run in parts of whole sequences (3 + 3 + 2
+    and 6 + 6 + 4 here): the keys and values of the second layer, which the first
+    layer's attention feeds, and y_0 have the bits of each sequence alone."""
+    torch = torch_cuda()
+    cfg, w = _two_layer_model(hd, H, Hkv, P)
+    prompts = np.random.default_rng(hd).integers(0, 512, (B, P)).astype(np.int32)
+    got = [_second_layer(torch, hd, H, Hkv, rows, cfg, w) for rows in (prompts, prompts[:1], prompts[B - 1:])]
     for i, b in ((1, 0), (2, B - 1)):
         assert got[i][0][0] == got[0][0][b]
         assert torch.equal(got[i][1][0], got[0][1][b]) and torch.equal(got[i][2][0], got[0][2][b])
