@@ -291,7 +291,10 @@ def mfma(args):
     GRBM_GUI_ACTIVE: busy cycles summed over the SIMDs over active cycles x
     SIMDs (GRBM_GUI_ACTIVE reads as the sum of the per-XCD instances, hence
     the division by --xcds), and achieved bf16 matrix flops (MOPS x 512) over
-    the kernels' duration."""
+    the kernels' duration.  With SQ_LDS_IDX_ACTIVE and SQ_LDS_BANK_CONFLICT in
+    the pass, also the share of the active cycles that a CU's LDS spends on
+    reads and writes by instructions (direct transfers into it are not among
+    them), and on bank conflicts."""
     rows = _counter_rows(args.pmc_dir)
     per = {}
     for r in rows:
@@ -300,22 +303,33 @@ def mfma(args):
         d[r["Counter_Name"]] = float(r["Counter_Value"])
     agg = {}
     for (_, name), d in per.items():
-        a = agg.setdefault(name, {"n": 0, "busy": 0.0, "gui": 0.0, "mops": 0.0, "dur": 0.0})
+        a = agg.setdefault(name, {"n": 0, "busy": 0.0, "gui": 0.0, "mops": 0.0, "dur": 0.0, "lds": 0.0, "conf": 0.0})
         a["n"] += 1
         a["busy"] += d.get("SQ_VALU_MFMA_BUSY_CYCLES", 0.0)
         a["gui"] += d.get("GRBM_GUI_ACTIVE", 0.0)
         a["mops"] += d.get("SQ_INSTS_VALU_MFMA_MOPS_BF16", 0.0)
         a["dur"] += d["dur"]
+        a["lds"] += d.get("SQ_LDS_IDX_ACTIVE", 0.0)
+        a["conf"] += d.get("SQ_LDS_BANK_CONFLICT", 0.0)
     simds = args.simds
+    lds = any(r["Counter_Name"] == "SQ_LDS_IDX_ACTIVE" for r in rows)
     lines = [f"command: {args.command}", "",
              f"matrix-core utilisation per kernel ({simds} SIMDs; util = MFMA busy cycles / (active cycles x SIMDs),",
              f"active cycles = GRBM_GUI_ACTIVE / {args.xcds} XCD instances;",
-             "bf16 TFLOP/s = SQ_INSTS_VALU_MFMA_MOPS_BF16 x 512 / kernel time; dense bf16 peak 2500 TFLOP/s)", "",
-             f"{'kernel':44s} {'launches':>8s} {'time_ms':>9s} {'mfma_util_%':>11s} {'bf16_TFLOP/s':>12s}"]
+             "bf16 TFLOP/s = SQ_INSTS_VALU_MFMA_MOPS_BF16 x 512 / kernel time; dense bf16 peak 2500 TFLOP/s"
+             + (";" if lds else ")")]
+    if lds:
+        lines.append(f"LDS = SQ_LDS_IDX_ACTIVE, conflicts = SQ_LDS_BANK_CONFLICT over active cycles x {simds // 4} CUs)")
+    lines += ["", f"{'kernel':58s} {'launches':>8s} {'time_ms':>9s} {'mfma_util_%':>11s} {'bf16_TFLOP/s':>12s}"
+              + (f" {'lds_%':>7s} {'conflict_%':>10s}" if lds else "")]
     for name, a in sorted(agg.items(), key=lambda kv: -kv[1]["dur"])[: args.top]:
         util = 100.0 * a["busy"] / (a["gui"] / args.xcds * simds) if a["gui"] else 0.0
         tf = a["mops"] * 512 / a["dur"] / 1e12 if a["dur"] else 0.0
-        lines.append(f"{name[:44]:44s} {a['n']:8d} {a['dur'] * 1e3:9.2f} {util:11.2f} {tf:12.2f}")
+        row = f"{name[:58]:58s} {a['n']:8d} {a['dur'] * 1e3:9.2f} {util:11.2f} {tf:12.2f}"
+        if lds:
+            cyc = a["gui"] / args.xcds * (simds // 4)
+            row += f" {100.0 * a['lds'] / cyc if cyc else 0.0:7.2f} {100.0 * a['conf'] / cyc if cyc else 0.0:10.2f}"
+        lines.append(row)
     open(args.out, "w").write("\n".join(lines) + "\n")
     print("\n".join(lines))
 
