@@ -299,7 +299,7 @@ hipError_t launch_gemm(int dtype, int epi, const GemmArgs &a, int m_blocks, hipS
 bool gemm_tiled_supported(int epi, const GemmArgs &a);
 hipError_t launch_gemm_tiled(int epi, const GemmArgs &a, hipStream_t s);
 // out[m] = 1 / sqrt(sum(part[m][0..n_part)) * inv_d + eps), m < M: the RMSNorm
-// scales launch_gemm_tiled reads, summed in index order.
+// scales launch_gemm_tiled reads, summed as the decode kernels sum them.
 hipError_t launch_row_scale(const float *part, int n_part, int M, float inv_d, float eps, float *out, hipStream_t s);
 hipError_t launch_attention(int dtype, const AttnArgs &a, int n_groups, hipStream_t s);
 hipError_t launch_combine(int dtype, const CombineArgs &a, int rows, hipStream_t s);

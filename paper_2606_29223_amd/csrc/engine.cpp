@@ -13,8 +13,8 @@
 //   round scratch rows x {h, partials, norm input, q, attention out, SwiGLU
 //                 out}, attention split partials, LM-head tile winners; a
 //                 stage works in its own row range, so stages may overlap.
-// One host->device copy of the round's row tables, one device->host copy of
-// the decoded candidates and commits per round.
+// A round copies its row tables to the device once; its argmax stores the
+// decoded candidates and commits straight to pinned host memory.
 #include <algorithm>
 #include <array>
 #include <chrono>
